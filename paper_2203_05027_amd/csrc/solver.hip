@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "../../include/uvadmm.h"
+#include "binned.hpp"
 #include "common.hpp"
 #include "setup.hpp"
 #include "spmv.hpp"
@@ -253,15 +254,17 @@ __device__ __forceinline__ T x_step(int cnt, T xo, T zo, T atu, T dm, T cj, doub
     return (p + zo + dm - cj * (T)inv_mu) / (T)(1 + cnt);
 }
 
-// A'u for column col: the L-lane segment product over the column (S == 1)
-// or the tree sum of the S slab partials P[s * n + col] (S > 1).
+// A'u for column col: the L-lane segment product over the column (S == 1),
+// the tree sum of the S slab partials P[s * n + col] (S > 1) or the whole
+// product P[col] (S == 0).
 template <int L, int E, int S, typename T>
 __device__ __forceinline__ T col_atu(int col, int beg, int end, int lane, const int *__restrict__ ri,
                                      const T *__restrict__ vc, const T *__restrict__ u, const T *__restrict__ P,
                                      int n)
 {
-    if (S == 1) return seg_dot<L, E>(beg, end, lane, ri, vc, u);
-    return slab_tree_sum<S>(P, n, col);
+    if constexpr (S == 0) return P[col];
+    else if constexpr (S == 1) return seg_dot<L, E>(beg, end, lane, ri, vc, u);
+    else return slab_tree_sum<S>(P, n, col);
 }
 
 // x-step, projection onto the orthant and delta update of one column.
@@ -507,6 +510,52 @@ k_row_combine(int m, const TP *__restrict__ P, const double *__restrict__ Pz, co
     if (MODE != 2 && blockIdx.x == 0 && threadIdx.x == 0) st->iter += 1;
     if (MODE == 1) uv::block_sum_max<3, 2>(acc, mx, part + blockIdx.x, pstride);
 }
+
+// Epilogues of the binned product (k_bin_sum): the whole column update of an
+// orthant problem, and the row update of an iteration (not a check).
+template <typename T>
+struct BinOrth {
+    T *__restrict__ x, *__restrict__ z;
+    double *__restrict__ delta;
+    const T *__restrict__ c;
+    double mu, inv_mu;
+    T xo, zo, cj;
+    double d;
+    __device__ void load(int j)
+    {
+        xo = x[j];
+        zo = z[j];
+        cj = c[j];
+        d = delta[j];
+    }
+    __device__ void put(int j, int cnt, T atu) { orth_step<T>(j, cnt, xo, zo, cj, d, atu, x, z, delta, mu, inv_mu); }
+    __device__ void once() {}
+};
+
+template <typename T>
+struct BinRow {
+    const T *__restrict__ b, *__restrict__ fu;
+    double *__restrict__ lam;
+    T *__restrict__ u;
+    double mu, inv_mu;
+    DevStatus *st;
+    T bi, fi;
+    double l0;
+    __device__ void load(int i)
+    {
+        bi = b[i];
+        fi = fu[i];
+        l0 = lam[i];
+    }
+    __device__ void put(int i, int, T q)
+    {
+        const T e = fi * (bi - q);
+        const double li = l0 - mu * (double)e;
+        lam[i] = li;
+        u[i] = (T)((double)e - li * inv_mu);
+    }
+    __device__ void once() { st->iter += 1; }
+};
 
 template <typename T, int L, int E, int S>
 __global__ void __launch_bounds__(kWG)
@@ -1087,6 +1136,7 @@ struct uv_solver {
     int E_row = 4, E_col = 4;   // gathers in flight per lane
     int S_row = 1, S_col = 1;   // XCD slabs of x (row pass) and of u (column pass)
     bool chunked = true;        // slab passes by 64-segment chunks (else lane groups)
+    bool forced = false;        // a launch shape of the sweep kernels was asked for
     bool batch8 = true;         // chunk batches of eight 64-entry steps (else four)
     int *srp = nullptr, *sci = nullptr;  // row-pass slab copy (S_row * m + 1 offsets)
     void *sva = nullptr;
@@ -1095,6 +1145,8 @@ struct uv_solver {
     void *P_row = nullptr, *P_col = nullptr;  // slab partials (2 S_row m, S_col n)
     double *sva64 = nullptr, *svc64 = nullptr;  // FP64 values of the slab copies
     double *P_res = nullptr;    // FP64 slab partials of the mixed form's checks
+    BinPlan bin_row, bin_col;   // binned products (in place of the slab copies where on)
+    double *Q = nullptr;        // products of a binned pass (nnz FP64 values)
     int nblk_row_fused = 0;     // row-residual partial blocks written by the check row pass
     bool resident = false;      // iterate with k_resident (the whole problem in one workgroup's LDS)
     bool need_start = false;    // b changed (solver_set_rhs): no iteration before a new start
@@ -1209,10 +1261,43 @@ void row_slab_launch(uv_solver *s, hipStream_t st, int mode)
 #undef UV_COMB_ARGS
 }
 
+// The row pass by the binned product: the update in the product's second
+// launch, or (checks and the resume mapping) in a launch of its own.
+template <typename T>
+void row_bin_launch(uv_solver *s, hipStream_t st, int mode)
+{
+    const BinPlan &p = s->bin_row;
+    const unsigned gc = blocks_for(s->m, kWG);
+    const double mu = s->o.mu, im = 1.0 / s->o.mu;
+    const int *done = mode == 2 ? nullptr : &s->st->done;
+    if (mode == 1) {
+        double *px = check_px<T>(s), *pz = row_pz<T, 1>(s);
+        bin_mult<double, double, T>(p, p.val64, (const T *)s->z, s->Q, done, st);
+        bin_sum(p, s->Q, BinStore<double>{pz}, done, st);
+        bin_mult<double, double, T>(p, p.val64, (const T *)s->x, s->Q, done, st);
+        bin_sum(p, s->Q, BinStore<double>{px}, done, st);
+        k_row_combine<T, double, 1, 1><<<gc, kWG, 0, st>>>(s->m, px, pz, (const T *)s->b, s->b64, (const T *)s->fu,
+                                                           s->lam, (T *)s->u, mu, im, s->part_row, s->nblk_row_fused,
+                                                           s->st);
+        return;
+    }
+    bin_mult<T, T, T>(p, (const T *)p.val, (const T *)s->x, (T *)s->Q, done, st);
+    if (mode == 0) {
+        bin_sum(p, (const T *)s->Q,
+                BinRow<T>{(const T *)s->b, (const T *)s->fu, s->lam, (T *)s->u, mu, im, s->st, 0, 0, 0.0}, done, st);
+        return;
+    }
+    bin_sum(p, (const T *)s->Q, BinStore<T>{(T *)s->P_row}, done, st);
+    k_row_combine<T, T, 1, 2><<<gc, kWG, 0, st>>>(s->m, (const T *)s->P_row, nullptr, (const T *)s->b, s->b64,
+                                                  (const T *)s->fu, s->lam, (T *)s->u, mu, im, s->part_row,
+                                                  s->nblk_row_fused, s->st);
+}
+
 template <typename T, int L, int E>
 struct RowLaunch {
     static void run(uv_solver *s, hipStream_t st, int mode)
     {
+        if (s->bin_row.on()) return row_bin_launch<T>(s, st, mode);
         if (s->S_row == 2) return row_slab_launch<T, L, E, 2>(s, st, mode);
         if (s->S_row == 4) return row_slab_launch<T, L, E, 4>(s, st, mode);
         if (s->S_row == 8) return row_slab_launch<T, L, E, 8>(s, st, mode);
@@ -1268,10 +1353,29 @@ void col_slab_launch(uv_solver *s, hipStream_t st)
     col_update_launch<T, 1, 1, S>(s, st);
 }
 
+// The column pass by the binned product: with orthant columns alone the
+// update is part of its second launch.
+template <typename T>
+void col_bin_launch(uv_solver *s, hipStream_t st)
+{
+    const BinPlan &p = s->bin_col;
+    const int *done = &s->st->done;
+    bin_mult<T, T, T>(p, (const T *)p.val, (const T *)s->u, (T *)s->Q, done, st);
+    if (s->n_soc == 0) {
+        bin_sum(p, (const T *)s->Q,
+                BinOrth<T>{(T *)s->x, (T *)s->z, s->delta, (const T *)s->c, s->o.mu, 1.0 / s->o.mu, 0, 0, 0, 0.0},
+                done, st);
+        return;
+    }
+    bin_sum(p, (const T *)s->Q, BinStore<T>{(T *)s->P_col}, done, st);
+    col_update_launch<T, 1, 1, 0>(s, st);
+}
+
 template <typename T, int L, int E>
 struct ColLaunch {
     static void run(uv_solver *s, hipStream_t st, int)
     {
+        if (s->bin_col.on()) return col_bin_launch<T>(s, st);
         if (s->S_col == 2) return col_slab_launch<T, L, E, 2>(s, st);
         if (s->S_col == 4) return col_slab_launch<T, L, E, 4>(s, st);
         if (s->S_col == 8) return col_slab_launch<T, L, E, 8>(s, st);
@@ -1358,12 +1462,12 @@ void launch_col(uv_solver *s, hipStream_t st) { dispatch<ColLaunch>(s, st, s->L_
 // product (else a separate residual pass follows).
 bool fused_row_check(const uv_solver *s)
 {
-    return s->o.precision == UV_FP64 || (s->S_row > 1 && s->chunked);
+    return s->o.precision == UV_FP64 || s->bin_row.on() || (s->S_row > 1 && s->chunked);
 }
 
 // Column residuals by the chunked slab product of A'lambda over the FP64
 // values of the column slab copy.
-bool slab_col_check(const uv_solver *s) { return s->S_col > 1 && s->chunked; }
+bool slab_col_check(const uv_solver *s) { return s->bin_col.on() || (s->S_col > 1 && s->chunked); }
 
 // mode: 0 iterate, 1 iterate + residual partials, 2 resume
 void launch_row(uv_solver *s, hipStream_t st, int mode)
@@ -1382,7 +1486,12 @@ void res_col_slab_launch(uv_solver *s, hipStream_t st)
     const unsigned g = blocks_for(s->n, kWG);
     const bool mixed = s->o.precision == UV_MIXED;
     double *P = mixed ? s->P_res : (double *)s->P_col;
-    seg_chunk_launch<double, S>(s, S * g, st, s->n, s->scp, s->sri, s->svc64, s->lam, P, s->res_skip);
+    if (s->bin_col.on()) {  // S == 1
+        bin_mult<double, double, double>(s->bin_col, s->bin_col.val64, s->lam, s->Q, s->res_skip, st);
+        bin_sum(s->bin_col, s->Q, BinStore<double>{P}, s->res_skip, st);
+    } else {
+        seg_chunk_launch<double, S>(s, S * g, st, s->n, s->scp, s->sri, s->svc64, s->lam, P, s->res_skip);
+    }
     if (mixed)
         k_res_col_slab<float, S><<<g, kWG, 0, st>>>(s->n, P, s->c64, s->delta, (const float *)s->z,
                                                     (const float *)s->x, s->part_col, (int)g, s->res_skip);
@@ -1407,7 +1516,8 @@ void launch_residuals(uv_solver *s, hipStream_t st, bool row_done, bool decide)
     // (FP64 values in both precisions), else the plain column residual pass
     const bool slab = slab_col_check(s);
     if (slab) {
-        if (s->S_col == 2) res_col_slab_launch<2>(s, st);
+        if (s->bin_col.on()) res_col_slab_launch<1>(s, st);
+        else if (s->S_col == 2) res_col_slab_launch<2>(s, st);
         else if (s->S_col == 4) res_col_slab_launch<4>(s, st);
         else res_col_slab_launch<8>(s, st);
     } else {
@@ -1571,6 +1681,15 @@ int validate(const uv_csr *A, const double *b, const double *c, const uv_cones *
     return UV_OK;
 }
 
+// Asks for the LDS of the binned kernels the solver launches.
+template <typename T>
+bool bins_ready()
+{
+    return bin_mult_ready<T, T, T>() && bin_mult_ready<double, double, T>() && bin_mult_ready<double, double, double>() &&
+           bin_sum_ready<T, BinRow<T>>() && bin_sum_ready<T, BinOrth<T>>() && bin_sum_ready<T, BinStore<T>>() &&
+           bin_sum_ready<double, BinStore<double>>();
+}
+
 int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const uv_cones *K)
 {
     const int m = s->m, n = s->n;
@@ -1698,10 +1817,34 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
     // Column-major copy of A.
     if (!build_csc(m, n, nnz, s->rp, s->ci, s->va64, s->cp, s->ri, s->vc64, cnt, bsum, st)) return UV_EHIP;
 
+    // Binned products in place of slabs where they pay and no launch shape is
+    // forced.
+    if (!s->forced) {
+        for (int pass = 0; pass < 2; ++pass) {
+            const int S = pass == 0 ? s->S_row : s->S_col;
+            if (S == 1 || !bins_pay(S, pass == 0 ? m : n, nnz)) continue;
+            auto get = [&](size_t bytes) { return (void *)dalloc<char>(s, bytes); };
+            const BinBuilt r = pass == 0 ? build_bins(m, n, nnz, s->rp, s->ci, s->va64, mixed, get, st, &s->bin_row)
+                                         : build_bins(n, m, nnz, s->cp, s->ri, s->vc64, mixed, get, st, &s->bin_col);
+            if (r == BIN_NOMEM) return UV_ENOMEM;
+            if (r == BIN_HIP) return UV_EHIP;
+            if (r == BIN_NO) continue;
+            void *&part = pass == 0 ? s->P_row : s->P_col;
+            part = dalloc<char>(s, ts * (size_t)(pass == 0 ? 2 * (size_t)m : (size_t)n));
+            if (!part) return UV_ENOMEM;
+        }
+        if (s->bin_row.on() || s->bin_col.on()) {
+            s->Q = dalloc<double>(s, nnz);
+            if (!s->Q) return UV_ENOMEM;
+            const bool ok = mixed ? bins_ready<float>() : bins_ready<double>();
+            if (!ok) return UV_EHIP;
+        }
+    }
+
     // XCD slab copies: row pass split by column ranges, column pass by row ranges.
     for (int pass = 0; pass < 2; ++pass) {
         const int S = pass == 0 ? s->S_row : s->S_col;
-        if (S == 1) continue;
+        if (S == 1 || (pass == 0 ? s->bin_row : s->bin_col).on()) continue;
         const int nr = pass == 0 ? m : n, width = pass == 0 ? n : m;
         int *off = dalloc<int>(s, (size_t)S * nr + 1);
         int *sidx = dalloc<int>(s, nnz);
@@ -1862,9 +2005,9 @@ int solver_create(const uv_csr *A, const double *b, const double *c, const uv_co
             return UV_EINVAL;
         }
         // automatic only when no launch shape of the sweep kernels is forced
-        const bool forced = o.lanes_row || o.lanes_col || o.unroll_row || o.unroll_col || o.slabs_row ||
-                            o.slabs_col || o.slab_kernel;
-        s->resident = fits && (o.resident == 2 || (o.resident == 0 && !forced));
+        s->forced = o.lanes_row || o.lanes_col || o.unroll_row || o.unroll_col || o.slabs_row || o.slabs_col ||
+                    o.slab_kernel;
+        s->resident = fits && (o.resident == 2 || (o.resident == 0 && !s->forced));
         s->res_lr = resident_lanes(A->m);
         s->res_lc = resident_lanes(A->n);
         if (s->resident) {

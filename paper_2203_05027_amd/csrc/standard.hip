@@ -35,6 +35,7 @@
 #include <vector>
 
 #include "../../include/uvadmm.h"
+#include "binned.hpp"
 #include "common.hpp"
 #include "setup.hpp"
 #include "spmv.hpp"
@@ -389,8 +390,13 @@ struct uv_standard {
     double *x1 = nullptr, *x2 = nullptr, *lam = nullptr, *delta = nullptr, *v = nullptr, *d = nullptr, *w = nullptr,
            *t = nullptr;
     double *nu = nullptr, *r = nullptr, *p = nullptr, *q = nullptr;
+    BinPlan bin_row, bin_col;  // binned products (in place of the slab copies where on)
+    double *Q = nullptr;       // products of a binned pass
     double *P_row = nullptr, *P_col = nullptr, *part = nullptr, *part_row = nullptr, *part_col = nullptr;
     StdStatus *st = nullptr, *st_host = nullptr;
+    // partials a product leaves for each row and column
+    int parts_row() const { return bin_row.on() ? 1 : S_row; }
+    int parts_col() const { return bin_col.on() ? 1 : S_col; }
 };
 
 namespace {
@@ -409,10 +415,16 @@ T *salloc(uv_standard *h, size_t count)
     return (T *)p;
 }
 
-// A'vec into P_col (S_col partials) and A vec into P_row (S_row partials).
+// A'vec into P_col (S_col partials) and A vec into P_row (S_row partials);
+// the binned products leave the whole sum (S == 1).
 template <int S>
-void prod_col(uv_standard *h, hipStream_t st, const double *vec, const int *skip)
+void prod_col(uv_standard *h, hipStream_t st, const double *vec, const int *skip, double *whole = nullptr)
 {
+    if (h->bin_col.on()) {
+        bin_mult<double, double, double>(h->bin_col, h->bin_col.val64, vec, h->Q, skip, st);
+        bin_sum(h->bin_col, h->Q, BinStore<double>{whole ? whole : h->P_col}, skip, st);
+        return;
+    }
     k_seg_chunk<double, double, S, 8><<<S * blocks_for(h->n, kWG), kWG, 0, st>>>(h->n, h->scp, h->sri, h->svc, vec,
                                                                             h->P_col, skip);
 }
@@ -420,6 +432,11 @@ void prod_col(uv_standard *h, hipStream_t st, const double *vec, const int *skip
 template <int S>
 void prod_row(uv_standard *h, hipStream_t st, const double *vec, const int *skip)
 {
+    if (h->bin_row.on()) {
+        bin_mult<double, double, double>(h->bin_row, h->bin_row.val64, vec, h->Q, skip, st);
+        bin_sum(h->bin_row, h->Q, BinStore<double>{h->P_row}, skip, st);
+        return;
+    }
     k_seg_chunk<double, double, S, 8><<<S * blocks_for(h->m, kWG), kWG, 0, st>>>(h->m, h->srp, h->sci, h->sva, vec,
                                                                             h->P_row, skip);
 }
@@ -441,8 +458,8 @@ void iteration(uv_standard *h, hipStream_t st, bool check)
     k_std_r0<SR><<<gm, kWG, 0, st>>>(m, h->P_row, h->b, h->r, h->p, h->part, h->st);
     k_std_cg_start<<<1, kWG, 0, st>>>((int)gm, h->part, h->st);
     for (int k = 0; k < h->cg_iters; ++k) {
-        prod_col<SC>(h, st, h->p, idle);
-        k_std_sum<SC><<<gn, kWG, 0, st>>>(n, h->P_col, h->t, h->st);
+        prod_col<SC>(h, st, h->p, idle, h->t);
+        if (!h->bin_col.on()) k_std_sum<SC><<<gn, kWG, 0, st>>>(n, h->P_col, h->t, h->st);
         prod_row<SR>(h, st, h->t, idle);
         k_std_q<SR><<<gm, kWG, 0, st>>>(m, h->P_row, h->p, h->q, h->part, h->st);
         k_std_alpha<<<1, kWG, 0, st>>>((int)gm, h->part, h->st);
@@ -464,15 +481,15 @@ void iteration(uv_standard *h, hipStream_t st, bool check)
 template <int SR>
 void iteration_sc(uv_standard *h, hipStream_t st, bool check)
 {
-    if (h->S_col == 2) iteration<SR, 2>(h, st, check);
-    else if (h->S_col == 4) iteration<SR, 4>(h, st, check);
+    if (h->parts_col() == 2) iteration<SR, 2>(h, st, check);
+    else if (h->parts_col() == 4) iteration<SR, 4>(h, st, check);
     else iteration<SR, 1>(h, st, check);
 }
 
 void launch_iteration(uv_standard *h, hipStream_t st, bool check)
 {
-    if (h->S_row == 2) iteration_sc<2>(h, st, check);
-    else if (h->S_row == 4) iteration_sc<4>(h, st, check);
+    if (h->parts_row() == 2) iteration_sc<2>(h, st, check);
+    else if (h->parts_row() == 4) iteration_sc<4>(h, st, check);
     else iteration_sc<1>(h, st, check);
 }
 
@@ -493,12 +510,12 @@ void launch_check(uv_standard *h, hipStream_t st)
 {
     auto sc = [&](auto sr) {
         constexpr int SR = decltype(sr)::value;
-        if (h->S_col == 2) check_only<SR, 2>(h, st);
-        else if (h->S_col == 4) check_only<SR, 4>(h, st);
+        if (h->parts_col() == 2) check_only<SR, 2>(h, st);
+        else if (h->parts_col() == 4) check_only<SR, 4>(h, st);
         else check_only<SR, 1>(h, st);
     };
-    if (h->S_row == 2) sc(std::integral_constant<int, 2>());
-    else if (h->S_row == 4) sc(std::integral_constant<int, 4>());
+    if (h->parts_row() == 2) sc(std::integral_constant<int, 2>());
+    else if (h->parts_row() == 4) sc(std::integral_constant<int, 4>());
     else sc(std::integral_constant<int, 1>());
 }
 
@@ -643,8 +660,23 @@ int standard_create(const uv_csr *A, const double *b, const double *c, const uv_
     h->srp = h->rp; h->sci = h->ci; h->sva = h->va;
     h->scp = h->cp; h->sri = h->ri; h->svc = h->vc;
     for (int pass = 0; pass < 2; ++pass) {
+        const int S = pass == 0 ? h->S_row : h->S_col, nr = pass == 0 ? m : n;
+        if (S == 1 || o.slabs_row || o.slabs_col || !bins_pay(S, nr, nnz)) continue;
+        auto get = [&](size_t bytes) { return (void *)salloc<char>(h, bytes); };
+        const BinBuilt r = pass == 0 ? build_bins(m, n, nnz, h->rp, h->ci, h->va, false, get, st, &h->bin_row)
+                                     : build_bins(n, m, nnz, h->cp, h->ri, h->vc, false, get, st, &h->bin_col);
+        if (r == BIN_NOMEM) return fail(UV_ENOMEM);
+        if (r == BIN_HIP) return fail(UV_EHIP);
+        if (r == BIN_OK && !h->Q) {
+            h->Q = salloc<double>(h, nnz);
+            if (!h->Q) return fail(UV_ENOMEM);
+            if (!bin_mult_ready<double, double, double>() || !bin_sum_ready<double, BinStore<double>>())
+                return fail(UV_EHIP);
+        }
+    }
+    for (int pass = 0; pass < 2; ++pass) {
         const int S = pass == 0 ? h->S_row : h->S_col;
-        if (S == 1) continue;
+        if (S == 1 || (pass == 0 ? h->bin_row : h->bin_col).on()) continue;
         const int nr = pass == 0 ? m : n, width = pass == 0 ? n : m;
         int *off = salloc<int>(h, (size_t)S * nr + 1);
         int *sidx = salloc<int>(h, nnz);
@@ -709,10 +741,10 @@ int standard_set_state(uv_standard *h, const double *x2, const double *lam, cons
     s->check_iter = -1;
     UV_TRY(hipMemcpyAsync(h->st, s, sizeof(StdStatus), hipMemcpyHostToDevice, st));
     const unsigned gn = blocks_for(h->n, kWG);
-    if (h->S_col == 2) {
+    if (h->parts_col() == 2) {
         prod_col<2>(h, st, h->nu, nullptr);
         k_std_sum<2><<<gn, kWG, 0, st>>>(h->n, h->P_col, h->w, h->st);
-    } else if (h->S_col == 4) {
+    } else if (h->parts_col() == 4) {
         prod_col<4>(h, st, h->nu, nullptr);
         k_std_sum<4><<<gn, kWG, 0, st>>>(h->n, h->P_col, h->w, h->st);
     } else {

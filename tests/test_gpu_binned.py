@@ -1,0 +1,109 @@
+"""The binned product (vectors above an XCD's L2, 4e6 entries and up) against
+the FP64 CPU oracles where its plan can go wrong: a last part and last group
+that are not full, empty rows and columns, rows of exactly half a group (the
+longest it takes) and one more (the slab product then), cones."""
+import sys
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import oracle
+from oracle import standard as std_oracle
+from paper_2203_05027_amd import instances as I
+from paper_2203_05027_amd.solver import Solver, Standard
+
+pytestmark = pytest.mark.gpu
+
+HALF_GROUP = 5120
+_insts = {}
+
+
+def rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-30))
+
+
+def _instance(kind):
+    if kind in _insts:
+        return _insts[kind]
+    if kind == "cones":
+        inst = I.conic_instance(330_001, 300_007, [3, 50, 1, 17, 64] * 2400, 7, seed=71)
+    else:
+        inst = I.lp_instance(310_001, 640_009, 7, seed=72)
+    if kind.startswith("long"):
+        A = sp.csr_matrix((inst["val"], inst["col_idx"], inst["row_ptr"]), shape=(inst["m"], inst["n"])).tolil()
+        rng = np.random.default_rng(73)
+        A = A.tocsr()
+        keep = np.ones(inst["m"])
+        keep[[0, 17, inst["m"] - 1]] = 0.0           # the dense rows, drawn below
+        keep[100:40_000] = 0.0                        # more empty rows than a group has threads
+        cols = np.ones(inst["n"])
+        cols[-9000:] = 0.0                            # and empty columns at the end
+        A = sp.diags(keep) @ A @ sp.diags(cols)
+        count = HALF_GROUP + (1 if kind == "long+1" else 0)
+        for r in (0, 17, inst["m"] - 1):
+            j = np.sort(rng.choice(inst["n"] - 9000, size=count, replace=False))
+            B = sp.csr_matrix((rng.standard_normal(count) * 0.02, (np.full(count, r), j)), shape=A.shape)
+            A = A + B
+        A = A.tocsr()
+        A.eliminate_zeros()
+        A.sort_indices()
+        inst = dict(inst, row_ptr=A.indptr.astype(np.int64), col_idx=A.indices.astype(np.int32), val=A.data,
+                    nnz=A.nnz, b=A @ inst["x0"], c=A.T @ inst["y0"] + inst["s0"])
+    _insts[kind] = inst
+    return inst
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", ["ragged", "long", "long+1", "cones"])
+def test_binned_product_matches_oracle(kind, precision):
+    """22 iterations, a check every seven, then a resume from that state: in
+    FP64 the oracle's iterates and residuals to 1e-9, in mixed precision to
+    1e-5 (FP32 rounding) with the residuals of its own iterate to 1e-11."""
+    inst = _instance(kind)
+    orc = oracle.Oracle.from_instance(inst)
+    orc.iterate(22)
+    o = orc.state()
+    with Solver.from_instance(inst, eps=0.0, check_every=7, precision=precision, full_checks=True) as s:
+        s.iterate(21)
+        g21, r21 = s.solution(), s.residuals()
+        s.iterate(1)
+        g = s.solution()
+        s.resume(g21["x"], g21["z"], g21["delta"], g21["lambda"])
+        s.iterate(1)
+        again = s.solution()
+    tol = 1e-9 if precision == "fp64" else 1e-5
+    errs = {k: rel(g[k], o[k]) for k in g}
+    sys.__stderr__.write(f"[gpu-test] binned {kind} {precision}: {errs}\n")
+    assert max(errs.values()) <= tol, errs
+    assert max(rel(again[k], o[k]) for k in g) <= tol
+    orc.set_state(x=g21["x"], z=g21["z"], delta=g21["delta"], lam=g21["lambda"])
+    ro = orc.residuals()
+    for k in ("r_prim", "r_dual", "r_gap", "pobj", "dobj", "res_ax_b", "prim_inf", "dual_inf", "scale_p", "scale_d"):
+        assert abs(r21[k] - ro[k]) <= 1e-11 * max(abs(ro[k]), 1e-3), (k, r21[k], ro[k])
+
+
+def test_binned_product_is_reproducible():
+    """The entries' places are handed out by atomics; the sums do not depend on them."""
+    inst = _instance("ragged")
+    outs = []
+    for _ in range(2):
+        with Solver.from_instance(inst, eps=0.0) as s:
+            s.iterate(30)
+            outs.append(s.solution())
+    for k in outs[0]:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("kind", ["long", "cones"])
+def test_standard_baseline_with_binned_products(kind):
+    inst = _instance(kind)
+    orc = std_oracle.StandardADMM.from_instance(inst, mu=1.0, cg_iters=2, cg_tol=0.0)
+    orc.iterate(6)
+    o = orc.state()
+    with Standard.from_instance(inst, cg_iters=2, eps=0.0, check_every=4) as s:
+        s.iterate(6)
+        g = s.solution()
+    errs = {k: rel(g[k], o[k]) for k in ("x1", "x2", "lam", "nu", "delta")}
+    sys.__stderr__.write(f"[gpu-test] standard binned {kind}: {errs}\n")
+    assert max(errs.values()) <= 1e-9, errs
