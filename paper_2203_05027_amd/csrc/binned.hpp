@@ -17,10 +17,10 @@
 // What bounds it: streaming, 28 bytes an entry in FP64 (8 + 2 read, 8
 // written, 8 + 2 read) and 16 in FP32, against 12 (8) bytes and one random
 // 64-byte L2 request an entry of the slab product.  On the 1e6 x 2e6 LP (2e7
-// entries, FP64; a copy of 1 GiB runs at 5.15 TB/s here): k_bin_mult 74 us =
-// 360 MB and 48 MB of staged parts at 5.5 TB/s, k_bin_sum with the update
-// fused 54 us (columns) and 44 us (rows); column pass 182 -> 129 us, row
-// pass 170 -> 121 us.  Flat optimum: parts of 8192 values, groups of 6656 to
+// entries, FP64; a copy of 1 GiB runs at 5.15 TB/s here): k_bin_mult 73 us =
+// 360 MB and 48 MB of staged parts at 5.6 TB/s, k_bin_sum with the update
+// fused 54 us (columns) and 44 us (rows); column pass 182 -> 127 us, row
+// pass 170 -> 119 us.  Flat optimum: parts of 8192 values, groups of 6656 to
 // 20000 products, batches of 256 or 1024 entries, runs aligned to 32 or 64
 // bytes and a second workgroup a CU are all 0-8 % slower; non-temporal
 // stores of the products 14-20 % slower (they then leave the Infinity Cache
@@ -217,7 +217,7 @@ k_bin_mult(int batches, int len, const BinBatch *__restrict__ batch, const int *
         const G *src = vec + (size_t)p * kPart;
         const int cnt = min(kPart, len - p * kPart);
         __syncthreads();  // the last part is no longer read
-        for (int i = threadIdx.x; i < cnt; i += kMultThreads) xs[i] = src[i];
+        uv::stage_lds<kMultThreads>(xs, src, cnt);
         __syncthreads();
         for (int q0 = b + w; q0 < be; q0 += kMultThreads / 64) {
             const int q = __builtin_amdgcn_readfirstlane(q0);
@@ -347,12 +347,12 @@ bool bin_sum_ready()
 // product would take S > 1 slabs.  Its two launches cost about 25 us before
 // the first byte (staging the parts), the slab product a random L2 request
 // an entry and S partials a segment.  Measured pass times, binned / slab, by
-// nnz + S nseg: 1.6e6 30.0 / 23.4 us, 3.3e6 36.1 / 34.0, 3.6e6 38.9 / 33.2,
-// 4.2e6 39.8 / 42.5, 4.4e6 37.9 / 54.2, 7.2e6 50.9 / 70.6, 2.4e7 129 / 182
-// (FP64); 1.6e6 25.9 / 20.4, 3.6e6 29.4 / 30.6, 4.4e6 31.7 / 39.4, 7.2e6
+// nnz + 2 S nseg: 2.2e6 30.0 / 23.4 us, 4.5e6 36.6 / 34.2, 5.3e6 40.0 / 38.3,
+// 5.9e6 41.2 / 43.6, 6.6e6 37.9 / 54.2, 9.6e6 50.9 / 70.6, 2.8e7 127 / 182
+// (FP64); 2.2e6 25.9 / 20.4, 4.3e6 30.9 / 30.0, 5.6e6 29.0 / 36.9, 9.6e6
 // 38.9 / 56.6 (mixed); at 6e7 entries and vectors of 15e6, whose runs are
 // only 11 entries long, still 724 / 1261 and 412 / 854.
-inline bool bins_pay(int S, int nseg, int nnz) { return (int64_t)nnz + (int64_t)S * nseg >= 4000000; }
+inline bool bins_pay(int S, int nseg, int nnz) { return (int64_t)nnz + (int64_t)2 * S * nseg >= 5600000; }
 
 enum BinBuilt { BIN_OK = 0, BIN_NO = 1, BIN_NOMEM = 2, BIN_HIP = 3 };  // BIN_NO: the matrix does not suit the plan
 

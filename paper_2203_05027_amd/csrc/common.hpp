@@ -183,4 +183,23 @@ __device__ __forceinline__ void block_sum_max(double (&vs)[KS], double (&vm)[KM]
     }
 }
 
+// Copies cnt values from src (16-byte aligned) to LDS with the NT threads of
+// a workgroup, 16 bytes a load and eight loads in flight per thread.
+template <int NT, typename G>
+__device__ __forceinline__ void stage_lds(G *__restrict__ dst, const G *__restrict__ src, int cnt)
+{
+    typedef unsigned V __attribute__((ext_vector_type(4)));
+    constexpr int PER = 16 / sizeof(G), U = 8;
+    const int whole = cnt / PER;
+    for (int t = threadIdx.x; t < whole; t += U * NT) {
+        V r[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) r[q] = ((const V *)src)[min(t + q * NT, whole - 1)];
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (t + q * NT < whole) ((V *)dst)[t + q * NT] = r[q];
+    }
+    if ((int)threadIdx.x < cnt - whole * PER) dst[whole * PER + threadIdx.x] = src[whole * PER + threadIdx.x];
+}
+
 }  // namespace uv

@@ -35,6 +35,7 @@
 #include "common.hpp"
 #include "setup.hpp"
 #include "spmv.hpp"
+#include "staged.hpp"
 
 using uv::kWG;
 
@@ -1147,6 +1148,7 @@ struct uv_solver {
     double *P_res = nullptr;    // FP64 slab partials of the mixed form's checks
     BinPlan bin_row, bin_col;   // binned products (in place of the slab copies where on)
     double *Q = nullptr;        // products of a binned pass (nnz FP64 values)
+    StagedPlan stg_row, stg_col;  // staged products (in place of the lane groups where on)
     int nblk_row_fused = 0;     // row-residual partial blocks written by the check row pass
     bool resident = false;      // iterate with k_resident (the whole problem in one workgroup's LDS)
     bool need_start = false;    // b changed (solver_set_rhs): no iteration before a new start
@@ -1293,11 +1295,48 @@ void row_bin_launch(uv_solver *s, hipStream_t st, int mode)
                                                   s->nblk_row_fused, s->st);
 }
 
+// The row pass by the staged product, S parts: with one part the update is
+// part of the product's launch (not in checks and the resume mapping).
+template <typename T, int S>
+void row_staged_launch(uv_solver *s, hipStream_t st, int mode)
+{
+    const StagedPlan &p = s->stg_row;
+    const unsigned gc = blocks_for(s->m, kWG);
+    const double mu = s->o.mu, im = 1.0 / s->o.mu;
+    const int *done = mode == 2 ? nullptr : &s->st->done;
+    if (mode == 1) {
+        double *px = check_px<T>(s), *pz = row_pz<T, S>(s);
+        staged<double, double, T>(p, p.val64, (const T *)s->z, BinStore<double>{pz}, done, st);
+        staged<double, double, T>(p, p.val64, (const T *)s->x, BinStore<double>{px}, done, st);
+        k_row_combine<T, double, S, 1><<<gc, kWG, 0, st>>>(s->m, px, pz, (const T *)s->b, s->b64, (const T *)s->fu,
+                                                           s->lam, (T *)s->u, mu, im, s->part_row, s->nblk_row_fused,
+                                                           s->st);
+        return;
+    }
+    if (S == 1 && mode == 0) {
+        staged<T, T, T>(p, (const T *)p.val, (const T *)s->x,
+                        BinRow<T>{(const T *)s->b, (const T *)s->fu, s->lam, (T *)s->u, mu, im, s->st, 0, 0, 0.0}, done,
+                        st);
+        return;
+    }
+    staged<T, T, T>(p, (const T *)p.val, (const T *)s->x, BinStore<T>{(T *)s->P_row}, done, st);
+#define UV_COMB_ARGS                                                                                      \
+    s->m, (const T *)s->P_row, nullptr, (const T *)s->b, s->b64, (const T *)s->fu, s->lam, (T *)s->u, mu, \
+        im, s->part_row, s->nblk_row_fused, s->st
+    if (mode == 2) k_row_combine<T, T, S, 2><<<gc, kWG, 0, st>>>(UV_COMB_ARGS);
+    else k_row_combine<T, T, S, 0><<<gc, kWG, 0, st>>>(UV_COMB_ARGS);
+#undef UV_COMB_ARGS
+}
+
 template <typename T, int L, int E>
 struct RowLaunch {
     static void run(uv_solver *s, hipStream_t st, int mode)
     {
         if (s->bin_row.on()) return row_bin_launch<T>(s, st, mode);
+        if (s->stg_row.S == 1) return row_staged_launch<T, 1>(s, st, mode);
+        if (s->stg_row.S == 2) return row_staged_launch<T, 2>(s, st, mode);
+        if (s->stg_row.S == 4) return row_staged_launch<T, 4>(s, st, mode);
+        if (s->stg_row.S == 8) return row_staged_launch<T, 8>(s, st, mode);
         if (s->S_row == 2) return row_slab_launch<T, L, E, 2>(s, st, mode);
         if (s->S_row == 4) return row_slab_launch<T, L, E, 4>(s, st, mode);
         if (s->S_row == 8) return row_slab_launch<T, L, E, 8>(s, st, mode);
@@ -1371,11 +1410,33 @@ void col_bin_launch(uv_solver *s, hipStream_t st)
     col_update_launch<T, 1, 1, 0>(s, st);
 }
 
+// The column pass by the staged product; with one part and orthant columns
+// alone the update is part of its launch.
+template <typename T>
+void col_staged_launch(uv_solver *s, hipStream_t st)
+{
+    const StagedPlan &p = s->stg_col;
+    const int *done = &s->st->done;
+    if (p.S == 1 && s->n_soc == 0) {
+        staged<T, T, T>(p, (const T *)p.val, (const T *)s->u,
+                        BinOrth<T>{(T *)s->x, (T *)s->z, s->delta, (const T *)s->c, s->o.mu, 1.0 / s->o.mu, 0, 0, 0,
+                                   0.0},
+                        done, st);
+        return;
+    }
+    staged<T, T, T>(p, (const T *)p.val, (const T *)s->u, BinStore<T>{(T *)s->P_col}, done, st);
+    if (p.S == 1) col_update_launch<T, 1, 1, 0>(s, st);
+    else if (p.S == 2) col_update_launch<T, 1, 1, 2>(s, st);
+    else if (p.S == 4) col_update_launch<T, 1, 1, 4>(s, st);
+    else col_update_launch<T, 1, 1, 8>(s, st);
+}
+
 template <typename T, int L, int E>
 struct ColLaunch {
     static void run(uv_solver *s, hipStream_t st, int)
     {
         if (s->bin_col.on()) return col_bin_launch<T>(s, st);
+        if (s->stg_col.on()) return col_staged_launch<T>(s, st);
         if (s->S_col == 2) return col_slab_launch<T, L, E, 2>(s, st);
         if (s->S_col == 4) return col_slab_launch<T, L, E, 4>(s, st);
         if (s->S_col == 8) return col_slab_launch<T, L, E, 8>(s, st);
@@ -1462,12 +1523,16 @@ void launch_col(uv_solver *s, hipStream_t st) { dispatch<ColLaunch>(s, st, s->L_
 // product (else a separate residual pass follows).
 bool fused_row_check(const uv_solver *s)
 {
-    return s->o.precision == UV_FP64 || s->bin_row.on() || (s->S_row > 1 && s->chunked);
+    return s->o.precision == UV_FP64 || s->bin_row.on() || s->stg_row.on() ||
+           (s->S_row > 1 && s->chunked);
 }
 
 // Column residuals by the chunked slab product of A'lambda over the FP64
 // values of the column slab copy.
-bool slab_col_check(const uv_solver *s) { return s->bin_col.on() || (s->S_col > 1 && s->chunked); }
+bool slab_col_check(const uv_solver *s)
+{
+    return s->bin_col.on() || s->stg_col.on() || (s->S_col > 1 && s->chunked);
+}
 
 // mode: 0 iterate, 1 iterate + residual partials, 2 resume
 void launch_row(uv_solver *s, hipStream_t st, int mode)
@@ -1489,6 +1554,8 @@ void res_col_slab_launch(uv_solver *s, hipStream_t st)
     if (s->bin_col.on()) {  // S == 1
         bin_mult<double, double, double>(s->bin_col, s->bin_col.val64, s->lam, s->Q, s->res_skip, st);
         bin_sum(s->bin_col, s->Q, BinStore<double>{P}, s->res_skip, st);
+    } else if (s->stg_col.on()) {
+        staged<double, double, double>(s->stg_col, s->stg_col.val64, s->lam, BinStore<double>{P}, s->res_skip, st);
     } else {
         seg_chunk_launch<double, S>(s, S * g, st, s->n, s->scp, s->sri, s->svc64, s->lam, P, s->res_skip);
     }
@@ -1516,9 +1583,10 @@ void launch_residuals(uv_solver *s, hipStream_t st, bool row_done, bool decide)
     // (FP64 values in both precisions), else the plain column residual pass
     const bool slab = slab_col_check(s);
     if (slab) {
-        if (s->bin_col.on()) res_col_slab_launch<1>(s, st);
-        else if (s->S_col == 2) res_col_slab_launch<2>(s, st);
-        else if (s->S_col == 4) res_col_slab_launch<4>(s, st);
+        const int S = s->bin_col.on() ? 1 : s->stg_col.on() ? s->stg_col.S : s->S_col;
+        if (S == 1) res_col_slab_launch<1>(s, st);
+        else if (S == 2) res_col_slab_launch<2>(s, st);
+        else if (S == 4) res_col_slab_launch<4>(s, st);
         else res_col_slab_launch<8>(s, st);
     } else {
         dispatch_le_res<ResColLaunch>(s, st, s->L_col);
@@ -1690,6 +1758,14 @@ bool bins_ready()
            bin_sum_ready<double, BinStore<double>>();
 }
 
+template <typename T>
+bool staged_all_ready()
+{
+    return staged_ready<T, T, T, BinRow<T>>() && staged_ready<T, T, T, BinOrth<T>>() &&
+           staged_ready<T, T, T, BinStore<T>>() && staged_ready<double, double, T, BinStore<double>>() &&
+           staged_ready<double, double, double, BinStore<double>>();
+}
+
 int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const uv_cones *K)
 {
     const int m = s->m, n = s->n;
@@ -1733,7 +1809,10 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
         s->c = s->c64;
     }
     s->nblk_row = (int)blocks_for(m, kWG / s->L_row);
-    s->nblk_row_fused = s->S_row > 1 ? (int)blocks_for(m, kWG) : s->nblk_row;
+    const int stg_r = s->resident || s->forced || s->S_row > 1 ? 0 : staged_parts(n, (int)ts);
+    const int stg_c = s->resident || s->forced || s->S_col > 1 ? 0 : staged_parts(m, 8);  // the check gathers FP64 lambda
+    const bool use_r = staged_pays(stg_r, m, nnz), use_c = staged_pays(stg_c, n, nnz);
+    s->nblk_row_fused = s->S_row > 1 || use_r ? (int)blocks_for(m, kWG) : s->nblk_row;
     s->nblk_rescol = (int)blocks_for(n, kWG / s->L_col);
     s->part_row = dalloc<double>(s, 5 * (size_t)std::max(s->nblk_row, s->nblk_row_fused));
     s->part_col = dalloc<double>(s, 5 * std::max((size_t)s->nblk_rescol, (size_t)blocks_for(n, kWG)));
@@ -1746,7 +1825,8 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
         UV_TRY(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
         s->clock_khz = khz;
     }
-    const size_t ncnt = std::max({(size_t)n, (size_t)s->S_row * m, (size_t)s->S_col * n});
+    const size_t ncnt = std::max({(size_t)n, (size_t)(use_r ? stg_r : s->S_row) * m,
+                                  (size_t)(use_c ? stg_c : s->S_col) * n});
     int *cnt = dalloc<int>(s, ncnt);
     int *bsum = dalloc<int>(s, blocks_for(ncnt, 4 * kWG));
     for (void *p : {(void *)s->rp, (void *)s->ci, (void *)s->va64, (void *)s->cp, (void *)s->ri,
@@ -1865,10 +1945,61 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
         if (pass == 0) { s->srp = off; s->sci = sidx; s->sva = sval; s->sva64 = sval64; s->P_row = part; }
         else { s->scp = off; s->sri = sidx; s->svc = sval; s->svc64 = sval64; s->P_col = part; }
     }
-    if (mixed && (s->S_row > 1 || s->S_col > 1)) {
+    // Staged products: the slab-major copy (with one part the matrix's own
+    // arrays) and each entry's place in its part.
+    for (int pass = 0; pass < 2; ++pass) {
+        if (!(pass == 0 ? use_r : use_c)) continue;
+        StagedPlan &p = pass == 0 ? s->stg_row : s->stg_col;
+        const int S = pass == 0 ? stg_r : stg_c, nr = pass == 0 ? m : n, len = pass == 0 ? n : m;
+        const int *ptr = pass == 0 ? s->rp : s->cp, *idx = pass == 0 ? s->ci : s->ri;
+        const double *v64 = pass == 0 ? s->va64 : s->vc64;
+        const void *v = pass == 0 ? s->va : s->vc;
+        p.width = staged_width(len, S);
+        if (S > 1) {
+            int *off = dalloc<int>(s, (size_t)S * nr + 1), *sidx = dalloc<int>(s, nnz);
+            double *sval = dalloc<double>(s, nnz);
+            if (!off || !sidx || !sval) return UV_ENOMEM;
+            if (!build_slabs(nr, nnz, ptr, idx, v64, S, p.width, off, sidx, sval, cnt, bsum, st)) return UV_EHIP;
+            ptr = off;
+            idx = sidx;
+            v64 = sval;
+            v = sval;
+        }
+        if (mixed) {  // the matrix's own FP32 values are only filled below
+            float *f = S > 1 ? dalloc<float>(s, nnz) : (float *)const_cast<void *>(v);
+            if (!f) return UV_ENOMEM;
+            if (S > 1) k_narrow<float><<<blocks_for(nnz, kWG), kWG, 0, st>>>(nnz, v64, f);
+            v = f;
+        }
+        p.nseg = nr;
+        p.len = len;
+        p.off = ptr;
+        p.val64 = v64;
+        p.val = v;
+        while (p.L < 64 && (int64_t)p.L * kStagedE * S * nr < nnz) p.L *= 2;
+        int dev = 0, cus = 0;
+        UV_TRY(hipGetDevice(&dev));
+        UV_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        p.per = std::max(1, cus / S);
+        p.wseg = dalloc<int>(s, (size_t)S * (p.per + 1));
+        p.place = dalloc<unsigned short>(s, nnz);
+        void *part = dalloc<char>(s, ts * (size_t)(pass == 0 ? 2 * S : S) * nr);
+        if (!p.wseg || !p.place || !part) return UV_ENOMEM;
+        (pass == 0 ? s->P_row : s->P_col) = part;
+        k_staged_split<<<blocks_for(S * (p.per + 1), kWG), kWG, 0, st>>>(nr, S, p.per, ptr, p.wseg);
+        k_staged_place<<<blocks_for(nnz, kWG), kWG, 0, st>>>(nnz, idx, S, p.width, p.place);
+        UV_TRY(hipGetLastError());
+        p.S = S;
+    }
+    if (use_r || use_c) {
+        const bool ok = mixed ? staged_all_ready<float>() : staged_all_ready<double>();
+        if (!ok) return UV_EHIP;
+    }
+    if (mixed && (s->S_row > 1 || s->S_col > 1 || use_r || use_c)) {
         // FP64 partials of the checks' A z and A'lambda
-        const size_t pr = s->S_row > 1 ? 2 * (size_t)s->S_row * m : 0;
-        const size_t pc = s->S_col > 1 ? (size_t)s->S_col * n : 0;
+        const int sr = use_r ? stg_r : s->S_row, sc = use_c ? stg_c : s->S_col;
+        const size_t pr = use_r || sr > 1 ? 2 * (size_t)sr * m : 0;
+        const size_t pc = use_c || sc > 1 ? (size_t)sc * n : 0;
         s->P_res = dalloc<double>(s, std::max(pr, pc));
         if (!s->P_res) return UV_ENOMEM;
     }

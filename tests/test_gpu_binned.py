@@ -1,4 +1,4 @@
-"""The binned product (vectors above an XCD's L2, 4e6 entries and up) against
+"""The binned product (vectors above an XCD's L2, some 5e6 entries and up) against
 the FP64 CPU oracles where its plan can go wrong: a last part and last group
 that are not full, empty rows and columns, rows of exactly half a group (the
 longest it takes) and one more (the slab product then), cones."""
@@ -27,9 +27,9 @@ def _instance(kind):
     if kind in _insts:
         return _insts[kind]
     if kind == "cones":
-        inst = I.conic_instance(330_001, 300_007, [3, 50, 1, 17, 64] * 2400, 7, seed=71)
+        inst = I.conic_instance(330_001, 300_007, [3, 50, 1, 17, 64] * 2400, 8, seed=71)
     else:
-        inst = I.lp_instance(310_001, 640_009, 7, seed=72)
+        inst = I.lp_instance(310_001, 640_009, 9, seed=72)
     if kind.startswith("long"):
         A = sp.csr_matrix((inst["val"], inst["col_idx"], inst["row_ptr"]), shape=(inst["m"], inst["n"])).tolil()
         rng = np.random.default_rng(73)
