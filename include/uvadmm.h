@@ -395,9 +395,9 @@ void batch_destroy(uv_batch *h);
 /* ------------------------------------------------------------------------
  * Parametric family: one A and c (orthant cone), B right-hand sides
  * b_1..b_B iterated together.  Per-instance vectors live instance-fastest on
- * the device (entry j of instance l at j * B + l), so every nonzero of A is
- * read once per 64 instances and its gather is one contiguous line.  Each
- * instance is checked every check_every iterations and frozen once it stops.
+ * the device in groups of 128 bytes, so every nonzero of A is read once per
+ * group and its gather is one cache line.  Each instance is checked every
+ * check_every iterations and frozen once it stops.
  * Host arrays below are instance-major: instance l's vector starts at
  * l * length.
  * ------------------------------------------------------------------------ */

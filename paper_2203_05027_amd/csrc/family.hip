@@ -1,13 +1,27 @@
 // family.hip -- one matrix A and cost c, B right-hand sides b_1..b_B (a
 // parametric family of LPs, orthant cone), iterated together.
 //
-// Every per-instance vector is stored instance-fastest: v[j * B + l] is
-// entry j of instance l.  A wavefront takes one row (or column) of A and 64
-// instances, so each nonzero of A is read once per 64 instances (a uniform,
-// scalar load) and its gather of x or u is one contiguous 64-entry line.
+// The instances are cut into groups of 128 bytes of the sweep type (32 in
+// FP32, 16 in FP64) and every per-instance vector is stored group by group,
+// instance-fastest within a group: entry j of instance l is
+// v[((l / G) * len + j) * G + l % G].  A gather of x or u is one cache line
+// for a whole group, and a group's gathered vector is 6.4 MB for u at m = 5e4.
+// G lanes take one row (or column) of A for a group; a workgroup takes a
+// block of them with the block's entries in LDS, and each XCD works through
+// its groups one after the other.
+// What bounds it: bytes and lines from beyond L2 (HBM streams of x, z, delta
+// and lambda, b, u; a quarter to a half of the gathered lines).  5e4 x 1e5,
+// 8e5 entries, 256 instances, mixed: column pass 220 -> 185 us, row pass 167
+// -> 146 us, the check's two passes 322 + 319 -> 314 + 225 us; an iteration,
+// checks included, 434 -> 373 us (FP64 661 -> 618) against groups of 64
+// instances, a wavefront each, with the entries in scalar registers.  Groups
+// of 64 bytes hit L2 more often but ask for twice the lines: 455 us; groups
+// of 256 bytes 420 us; reading a segment's operands and gathers ahead of the
+// last one's stores 405 us.
 // The iteration is the reduced form of Algorithm 1 used by the single
 // solver; each instance is checked every check_every iterations and frozen
-// (its stores are masked) once it stops.
+// (its stores are masked) once it stops; a group that has stopped whole is
+// passed over.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,266 +55,354 @@ struct FShared {
     double cnorm2;
 };
 
-// Work item of wave `wave` of workgroup `blk` in the sweep passes: segment
-// (column or row) `seg` for the 64-instance group `grp`.  Workgroups go to
-// the 8 XCDs in turn; when ng divides 8 the workgroup on XCD x always takes
-// group x % ng, so an XCD's L2 holds the gathered lines of its own groups
-// only (8 / ng workgroups of a round share a group, 4 segments each; 5-8 %
-// faster per iteration at B = 256 on the 5e4 x 1e5 family than spreading
-// every group over every XCD).  Otherwise a workgroup takes the ng groups of
-// consecutive segments in turn.  Either way every (segment, group) pair is
-// one wave's.
-__device__ __forceinline__ void fam_item(int blk, int wave, int ng, int &seg, int &grp)
-{
-    if ((8 % ng) == 0) {
-        const int x = blk & 7, per = 8 / ng;
-        grp = x % ng;
-        seg = ((blk >> 3) * per + x / ng) * 4 + wave;
-    } else {
-        const int gw = blk * 4 + wave;
-        seg = gw / ng;
-        grp = gw % ng;
-    }
-}
+constexpr int kFamThreads = 256;
 
-// Workgroups of a sweep pass over nseg segments (see fam_item).
-inline unsigned fam_blocks(int nseg, int ng)
-{
-    if ((8 % ng) == 0) {
-        const int per_round = 4 * (8 / ng);
-        return (unsigned)(((int64_t)nseg + per_round - 1) / per_round * 8);
-    }
-    return (unsigned)(((int64_t)nseg * ng + 3) / 4);
-}
-
-// column pass: wave = (column j, 64 instances)
+// Instances a group holds.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_fam_col(int n, int B, const int *__restrict__ cp, const int *__restrict__ ri, const T *__restrict__ vc,
-          const T *__restrict__ U, T *__restrict__ X, T *__restrict__ Z, double *__restrict__ D,
-          const T *__restrict__ c, const FInst *__restrict__ inst, double mu, double inv_mu,
+constexpr int fam_group() { return 128 / (int)sizeof(T); }
+
+// Place of entry j of instance l in a vector of len entries an instance.
+__device__ __forceinline__ size_t fam_at(int len, int G, int j, int l)
+{
+    return ((size_t)(l / G) * len + j) * G + l % G;
+}
+
+// Workgroup's unit of work: block `blk` (of nb) of group `grp` (of ng).
+// Workgroups go to the 8 XCDs in turn, and each XCD takes an eighth of the
+// units in order, so that it gathers from one group's vector at a time
+// (256 instances in FP32: one group an XCD).  False past the last unit.
+__device__ __forceinline__ bool fam_unit(int ng, int nb, int &grp, int &blk)
+{
+    const int units = ng * nb, per = (units + 7) >> 3, i = blockIdx.x >> 3, u = (blockIdx.x & 7) * per + i;
+    if (i >= per || u >= units) return false;
+    grp = u / nb;
+    blk = u % nb;
+    return true;
+}
+
+inline unsigned fam_grid(int ng, int nb) { return 8u * (unsigned)(((int64_t)ng * nb + 7) / 8); }
+
+// Blocks of 16, 24 and 64 segments measured 391, 382 and 398 us an iteration
+// at 256 instances in FP32 and 699, 682 and 627 in FP64; 32: 391 and 642.
+constexpr int kFamSegs = 32;   // segments a workgroup takes in a sweep pass, at most
+constexpr int kFamCap = 1024;  // entries it stages
+static_assert(kFamCap % kFamThreads == 0, "fam_stage reads whole rounds of the workgroup");
+
+// A load (store) that leaves the caches to the gathered vector, in families
+// too large for the Infinity Cache (256 instances above: 455 against 489 us
+// without; 128 of 2e4 x 3.6e4 in FP64, which fit: 128 against 100 us).
+template <bool NT, typename V>
+__device__ __forceinline__ V fam_ld(const V *p)
+{
+    return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
+template <bool NT, typename V>
+__device__ __forceinline__ void fam_st(V v, V *p)
+{
+    if (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+// Segments a workgroup of a sweep pass takes: kFamSegs, fewer while that
+// leaves under 4096 workgroups.
+inline int fam_segs(int nseg, int ng, int G)
+{
+    int w = kFamSegs;
+    while (w > kFamThreads / G && (int64_t)nseg * ng / w < 4096) w /= 2;
+    return w;
+}
+
+inline int fam_blocks(int nseg, int segs) { return (nseg + segs - 1) / segs; }
+
+// Stages a block's segment bounds and, when they fit, its entries in LDS.
+// True if the entries are there (the bounds are then relative to the first).
+template <typename T>
+__device__ __forceinline__ bool fam_stage(int s0, int w, const int *__restrict__ ptr, const int *__restrict__ idx,
+                                          const T *__restrict__ val, int *__restrict__ sp, int *__restrict__ si,
+                                          T *__restrict__ sv)
+{
+    const int k0 = ptr[s0], cnt = ptr[s0 + w] - k0;
+    const bool fits = cnt <= kFamCap;
+    for (int t = threadIdx.x; t <= w; t += kFamThreads) sp[t] = ptr[s0 + t] - (fits ? k0 : 0);
+    if (fits) {
+        constexpr int U = kFamCap / kFamThreads;
+        int i[U];
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = threadIdx.x + u * kFamThreads;
+            if (k < cnt) {
+                i[u] = idx[k0 + k];
+                v[u] = val[k0 + k];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = threadIdx.x + u * kFamThreads;
+            if (k < cnt) {
+                si[k] = i[u];
+                sv[k] = v[u];
+            }
+        }
+    }
+    __syncthreads();
+    return fits;
+}
+
+typedef int i4u __attribute__((ext_vector_type(4), aligned(4)));
+template <typename T>
+struct V4 {
+    typedef T type __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+};
+
+// Sum over the entries beg..end-1 of val[k] * vec[idx[k] * G]: four running
+// sums, entry k - beg mod 4 in each (the tail in the first), added as
+// (a0 + a1) + (a2 + a3).  Eight entries' gathers are in flight.
+template <int G, typename T, typename TV, typename S>
+__device__ __forceinline__ T fam_dot(int beg, int end, const int *__restrict__ idx, const TV *__restrict__ val,
+                                     const S *__restrict__ vec)
+{
+    T a[4] = {0, 0, 0, 0};
+    int k = beg;
+    for (; k + 7 < end; k += 8) {
+        const i4u j0 = *(const i4u *)(idx + k), j1 = *(const i4u *)(idx + k + 4);
+        const typename V4<TV>::type v0 = *(const typename V4<TV>::type *)(val + k),
+                                    v1 = *(const typename V4<TV>::type *)(val + k + 4);
+        S g[8];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = vec[(size_t)j0[q] * G];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[4 + q] = vec[(size_t)j1[q] * G];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] += (T)v0[q] * (T)g[q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] += (T)v1[q] * (T)g[4 + q];
+    }
+    if (k + 3 < end) {
+        const i4u j0 = *(const i4u *)(idx + k);
+        const typename V4<TV>::type v0 = *(const typename V4<TV>::type *)(val + k);
+        S g[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = vec[(size_t)j0[q] * G];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] += (T)v0[q] * (T)g[q];
+        k += 4;
+    }
+    for (; k < end; ++k) a[0] += (T)val[k] * (T)vec[(size_t)idx[k] * G];
+    return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// fam_dot over two vectors at once (A z and A x of a check row), one read of
+// the entries, in FP64.
+template <int G, typename S>
+__device__ __forceinline__ void fam_dot2(int beg, int end, const int *__restrict__ idx,
+                                         const double *__restrict__ val, const S *__restrict__ vz,
+                                         const S *__restrict__ vx, double &qz, double &qx)
+{
+    double z[4] = {0.0, 0.0, 0.0, 0.0}, x[4] = {0.0, 0.0, 0.0, 0.0};
+    int k = beg;
+    for (; k + 3 < end; k += 4) {
+        S gz[4], gx[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const size_t o = (size_t)idx[k + q] * G;
+            gz[q] = vz[o];
+            gx[q] = vx[o];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            z[q] += val[k + q] * (double)gz[q];
+            x[q] += val[k + q] * (double)gx[q];
+        }
+    }
+    for (; k < end; ++k) {
+        const size_t o = (size_t)idx[k] * G;
+        z[0] += val[k] * (double)vz[o];
+        x[0] += val[k] * (double)vx[o];
+    }
+    qz = (z[0] + z[1]) + (z[2] + z[3]);
+    qx = (x[0] + x[1]) + (x[2] + x[3]);
+}
+
+// column pass: G lanes = (column j, one group)
+template <typename T, bool NT>
+__global__ void __launch_bounds__(kFamThreads)
+k_fam_col(int n, int m, int ng, int nb, int segs, const int *__restrict__ cp, const int *__restrict__ ri,
+          const T *__restrict__ vc, const T *__restrict__ U, T *__restrict__ X, T *__restrict__ Z,
+          double *__restrict__ D, const T *__restrict__ c, const int *__restrict__ run, double mu, double inv_mu,
           const FShared *__restrict__ sh)
 {
-    if (sh->active == 0) return;
-    const int lane = threadIdx.x & 63;
-    int js, g;
-    fam_item(blockIdx.x, threadIdx.x >> 6, B >> 6, js, g);
-    const int j = __builtin_amdgcn_readfirstlane(js), l = __builtin_amdgcn_readfirstlane(g) * 64 + lane;
-    if (j >= n) return;
-    const int beg = cp[j], end = cp[j + 1];
-    const size_t o = (size_t)j * B + l;
-    const T xo = X[o], zo = Z[o], cj = c[j];
-    const double d = D[o];
-    T a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    int k = beg;
-    for (; k + 3 < end; k += 4) {
-        const int r0 = ri[k], r1 = ri[k + 1], r2 = ri[k + 2], r3 = ri[k + 3];
-        const T v0 = vc[k], v1 = vc[k + 1], v2 = vc[k + 2], v3 = vc[k + 3];
-        a0 += v0 * U[(size_t)r0 * B + l];
-        a1 += v1 * U[(size_t)r1 * B + l];
-        a2 += v2 * U[(size_t)r2 * B + l];
-        a3 += v3 * U[(size_t)r3 * B + l];
+    constexpr int G = fam_group<T>();
+    int g, blk;
+    if (sh->active == 0 || !fam_unit(ng, nb, g, blk)) return;
+    const int lane = threadIdx.x % G;
+    const int running = run[g * G + lane];
+    if (!__any(running)) return;  // the whole workgroup: it has one group
+    __shared__ int sp[kFamSegs + 1], si[kFamCap];
+    __shared__ T sv[kFamCap];
+    const int j0 = blk * segs, w = min(segs, n - j0);
+    const bool staged = fam_stage(j0, w, cp, ri, vc, sp, si, sv);
+    const T *Ug = U + (size_t)g * m * G + lane;
+    for (int t = threadIdx.x / G; t < w; t += kFamThreads / G) {
+        const int beg = sp[t], end = sp[t + 1], j = j0 + t;
+        const size_t o = ((size_t)g * n + j) * G + lane;
+        const T xo = fam_ld<NT>(X + o), zo = fam_ld<NT>(Z + o), cj = c[j];
+        const double d = fam_ld<NT>(D + o);
+        const T atu = staged ? fam_dot<G, T>(beg, end, si, sv, Ug) : fam_dot<G, T>(beg, end, ri, vc, Ug);
+        if (running) {
+            const int cnt = end - beg;
+            const T dm = (T)(d * inv_mu);
+            const T p = (T)cnt * xo + atu;
+            const T xn = (p + zo + dm - cj * (T)inv_mu) / (T)(1 + cnt);
+            const T v = xn - dm;
+            const T zn = v > (T)0 ? v : (T)0;
+            fam_st<NT>(xn, X + o);
+            fam_st<NT>(zn, Z + o);
+            fam_st<NT>(d + mu * ((double)zn - (double)xn), D + o);
+        }
     }
-    for (; k < end; ++k) a0 += vc[k] * U[(size_t)ri[k] * B + l];
-    const T atu = (a0 + a1) + (a2 + a3);
-    if (inst[l].status != UV_STATUS_RUNNING) return;
-    const int cnt = end - beg;
-    const T dm = (T)(d * inv_mu);
-    const T p = (T)cnt * xo + atu;
-    const T xn = (p + zo + dm - cj * (T)inv_mu) / (T)(1 + cnt);
-    const T v = xn - dm;
-    const T zn = v > (T)0 ? v : (T)0;
-    X[o] = xn;
-    Z[o] = zn;
-    D[o] = d + mu * ((double)zn - (double)xn);
 }
 
-// row pass: wave = (row i, 64 instances)
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_fam_row(int m, int B, const int *__restrict__ rp, const int *__restrict__ ci, const T *__restrict__ va,
-          const T *__restrict__ X, const T *__restrict__ BV, const T *__restrict__ fu, double *__restrict__ LAM,
-          T *__restrict__ U, const FInst *__restrict__ inst, double mu, double inv_mu, FShared *sh)
+// row pass: G lanes = (row i, one group)
+template <typename T, bool NT>
+__global__ void __launch_bounds__(kFamThreads)
+k_fam_row(int m, int n, int ng, int nb, int segs, const int *__restrict__ rp, const int *__restrict__ ci,
+          const T *__restrict__ va, const T *__restrict__ X, const T *__restrict__ BV, const T *__restrict__ fu,
+          double *__restrict__ LAM, T *__restrict__ U, const int *__restrict__ run, double mu, double inv_mu,
+          FShared *sh)
 {
-    if (sh->active == 0) return;
-    const int lane = threadIdx.x & 63;
-    int is, g;
-    fam_item(blockIdx.x, threadIdx.x >> 6, B >> 6, is, g);
-    const int i = __builtin_amdgcn_readfirstlane(is), l = __builtin_amdgcn_readfirstlane(g) * 64 + lane;
+    constexpr int G = fam_group<T>();
+    int g, blk;
+    if (sh->active == 0 || !fam_unit(ng, nb, g, blk)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) sh->iter += 1;
-    if (i >= m) return;
-    const int beg = rp[i], end = rp[i + 1];
-    const size_t o = (size_t)i * B + l;
-    const T bi = BV[o], fi = fu[i];
-    const double l0 = LAM[o];
-    T a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    int k = beg;
-    for (; k + 3 < end; k += 4) {
-        const int j0 = ci[k], j1 = ci[k + 1], j2 = ci[k + 2], j3 = ci[k + 3];
-        const T v0 = va[k], v1 = va[k + 1], v2 = va[k + 2], v3 = va[k + 3];
-        a0 += v0 * X[(size_t)j0 * B + l];
-        a1 += v1 * X[(size_t)j1 * B + l];
-        a2 += v2 * X[(size_t)j2 * B + l];
-        a3 += v3 * X[(size_t)j3 * B + l];
+    const int lane = threadIdx.x % G;
+    const int running = run[g * G + lane];
+    if (!__any(running)) return;
+    __shared__ int sp[kFamSegs + 1], si[kFamCap];
+    __shared__ T sv[kFamCap];
+    const int i0 = blk * segs, w = min(segs, m - i0);
+    const bool staged = fam_stage(i0, w, rp, ci, va, sp, si, sv);
+    const T *Xg = X + (size_t)g * n * G + lane;
+    for (int t = threadIdx.x / G; t < w; t += kFamThreads / G) {
+        const int beg = sp[t], end = sp[t + 1], i = i0 + t;
+        const size_t o = ((size_t)g * m + i) * G + lane;
+        const T bi = fam_ld<NT>(BV + o), fi = fu[i];
+        const double l0 = fam_ld<NT>(LAM + o);
+        const T q = staged ? fam_dot<G, T>(beg, end, si, sv, Xg) : fam_dot<G, T>(beg, end, ci, va, Xg);
+        if (running) {
+            const T e = fi * (bi - q);
+            const double li = l0 - mu * (double)e;
+            fam_st<NT>(li, LAM + o);
+            fam_st<NT>((T)((double)e - li * inv_mu), U + o);
+        }
     }
-    for (; k < end; ++k) a0 += va[k] * X[(size_t)ci[k] * B + l];
-    const T q = (a0 + a1) + (a2 + a3);
-    if (inst[l].status != UV_STATUS_RUNNING) return;
-    const T e = fi * (bi - q);
-    const double li = l0 - mu * (double)e;
-    LAM[o] = li;
-    U[o] = (T)((double)e - li * inv_mu);
 }
 
-// Residual partials over rows: per instance ||A z - b||^2, b'lambda,
-// ||A x - b||^2 (FP64 values of A).  part[(blk * 3 + k) * B + l].  The grid
-// is kResBlocks * (B / 64): workgroup w takes the 64-instance group
-// w / kResBlocks and the row chunk blk = w % kResBlocks (rows blk * 4 + wave,
-// then every kResBlocks * 4-th); each wavefront sums a row's entries four at
-// a time with their gathers in flight together.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_fam_res_row(int m, int B, const int *__restrict__ rp, const int *__restrict__ ci, const double *__restrict__ va,
-              const T *__restrict__ X, const T *__restrict__ Z, const double *__restrict__ BV,
-              const double *__restrict__ LAM, double *__restrict__ part)
+// Workgroup sums of K values per instance of a group over the workgroup's
+// kFamThreads / G segments, in order: part[(blk * K + k) * B + instance].
+template <int K, int G>
+__device__ __forceinline__ void fam_partials(const double (&a)[K], int blk, int B, int grp, double *__restrict__ part)
 {
-    __shared__ double s[3][4][64];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int blk = blockIdx.x % kResBlocks, l = (blockIdx.x / kResBlocks) * 64 + lane;
-    double a[3] = {0.0, 0.0, 0.0};
-    for (int i = blk * 4 + w; i < m; i += kResBlocks * 4) {
-        const int beg = rp[i], end = rp[i + 1];
-        double z0 = 0.0, z1 = 0.0, z2 = 0.0, z3 = 0.0, x0 = 0.0, x1 = 0.0, x2 = 0.0, x3 = 0.0;
-        int k = beg;
-        for (; k + 3 < end; k += 4) {
-            const size_t o0 = (size_t)ci[k] * B + l, o1 = (size_t)ci[k + 1] * B + l;
-            const size_t o2 = (size_t)ci[k + 2] * B + l, o3 = (size_t)ci[k + 3] * B + l;
-            const double v0 = va[k], v1 = va[k + 1], v2 = va[k + 2], v3 = va[k + 3];
-            z0 += v0 * (double)Z[o0];
-            z1 += v1 * (double)Z[o1];
-            z2 += v2 * (double)Z[o2];
-            z3 += v3 * (double)Z[o3];
-            x0 += v0 * (double)X[o0];
-            x1 += v1 * (double)X[o1];
-            x2 += v2 * (double)X[o2];
-            x3 += v3 * (double)X[o3];
-        }
-        for (; k < end; ++k) {
-            const size_t o = (size_t)ci[k] * B + l;
-            z0 += va[k] * (double)Z[o];
-            x0 += va[k] * (double)X[o];
-        }
-        const double qz = (z0 + z1) + (z2 + z3), qx = (x0 + x1) + (x2 + x3);
-        const double bi = BV[(size_t)i * B + l];
-        a[0] += (qz - bi) * (qz - bi);
-        a[1] += bi * LAM[(size_t)i * B + l];
-        a[2] += (qx - bi) * (qx - bi);
-    }
-    for (int k = 0; k < 3; ++k) s[k][w][lane] = a[k];
+    constexpr int SEG = kFamThreads / G;
+    __shared__ double s[K][SEG][G];
+    const int lane = threadIdx.x % G, seg = threadIdx.x / G;
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k][seg][lane] = a[k];
     __syncthreads();
-    if (w == 0)
-        for (int k = 0; k < 3; ++k)
-            part[((size_t)blk * 3 + k) * B + l] = ((s[k][0][lane] + s[k][1][lane]) + s[k][2][lane]) + s[k][3][lane];
+    if (threadIdx.x >= K * G) return;
+    const int k = threadIdx.x / G;
+    double t = s[k][0][lane];
+    for (int q = 1; q < SEG; ++q) t += s[k][q][lane];
+    part[((size_t)blk * K + k) * B + grp * G + lane] = t;
 }
 
-// The row pass of a check iteration, on the grid of k_fam_res_row: each
-// row's A z and A x in FP64 (FP64 values of A, the same sums in the same
-// order as k_fam_res_row), the iteration's lambda and u updates from that
-// A x (rounded to the sweep type), and the row partials of the check with
-// the updated lambda -- one pass where the row pass and k_fam_res_row took
-// two.
+// The row pass of a check iteration (kResBlocks blocks a group): each row's
+// A z and A x in FP64 (FP64 values of A), the iteration's lambda and u
+// updates from that A x (rounded to the sweep type), and the row partials of
+// the check with the updated lambda: per instance ||A z - b||^2, b'lambda,
+// ||A x - b||^2.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_fam_row_check(int m, int B, const int *__restrict__ rp, const int *__restrict__ ci,
+__global__ void __launch_bounds__(kFamThreads)
+k_fam_row_check(int m, int n, int B, const int *__restrict__ rp, const int *__restrict__ ci,
                 const double *__restrict__ va, const T *__restrict__ X, const T *__restrict__ Z,
                 const T *__restrict__ BV, const double *__restrict__ BV64, const T *__restrict__ fu,
-                double *__restrict__ LAM, T *__restrict__ U, const FInst *__restrict__ inst, double mu,
+                double *__restrict__ LAM, T *__restrict__ U, const int *__restrict__ run, double mu,
                 double inv_mu, FShared *sh, double *__restrict__ part)
 {
-    if (sh->active == 0) return;
-    __shared__ double s[3][4][64];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int blk = blockIdx.x % kResBlocks, l = (blockIdx.x / kResBlocks) * 64 + lane;
+    constexpr int G = fam_group<T>(), SEG = kFamThreads / G;
+    int g, blk;
+    if (sh->active == 0 || !fam_unit(B / G, kResBlocks, g, blk)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) sh->iter += 1;
-    const bool run = inst[l].status == UV_STATUS_RUNNING;
+    const int lane = threadIdx.x % G;
+    const int running = run[g * G + lane];
+    if (!__any(running)) return;  // the group has stopped: every wavefront leaves, its partials are not read
+    const T *Xg = X + (size_t)g * n * G + lane, *Zg = Z + (size_t)g * n * G + lane;
+    __shared__ int sp[kFamSegs + 1], si[kFamCap];
+    __shared__ double sv[kFamCap];
     double a[3] = {0.0, 0.0, 0.0};
-    for (int i = blk * 4 + w; i < m; i += kResBlocks * 4) {
-        const int beg = rp[i], end = rp[i + 1];
-        double z0 = 0.0, z1 = 0.0, z2 = 0.0, z3 = 0.0, x0 = 0.0, x1 = 0.0, x2 = 0.0, x3 = 0.0;
-        int k = beg;
-        for (; k + 3 < end; k += 4) {
-            const size_t o0 = (size_t)ci[k] * B + l, o1 = (size_t)ci[k + 1] * B + l;
-            const size_t o2 = (size_t)ci[k + 2] * B + l, o3 = (size_t)ci[k + 3] * B + l;
-            const double v0 = va[k], v1 = va[k + 1], v2 = va[k + 2], v3 = va[k + 3];
-            z0 += v0 * (double)Z[o0];
-            z1 += v1 * (double)Z[o1];
-            z2 += v2 * (double)Z[o2];
-            z3 += v3 * (double)Z[o3];
-            x0 += v0 * (double)X[o0];
-            x1 += v1 * (double)X[o1];
-            x2 += v2 * (double)X[o2];
-            x3 += v3 * (double)X[o3];
+    const int per = (m + kResBlocks - 1) / kResBlocks, i1 = min((blk + 1) * per, m);  // per * kResBlocks fits: m + 512
+    for (int i0 = blk * per; i0 < i1; i0 += kFamSegs) {
+        const int w = min(kFamSegs, i1 - i0);
+        __syncthreads();  // the last rows' entries are no longer read
+        const bool staged = fam_stage(i0, w, rp, ci, va, sp, si, sv);
+        for (int t = threadIdx.x / G; t < w; t += SEG) {
+            const int i = i0 + t;
+            const size_t o = ((size_t)g * m + i) * G + lane;
+            double li = LAM[o], qz, qx;
+            const double bi = BV64[o];
+            const T bt = BV[o], fi = fu[i];
+            if (staged) fam_dot2<G>(sp[t], sp[t + 1], si, sv, Zg, Xg, qz, qx);
+            else fam_dot2<G>(sp[t], sp[t + 1], ci, va, Zg, Xg, qz, qx);
+            if (running) {
+                const T e = fi * (bt - (T)qx);
+                li = li - mu * (double)e;
+                LAM[o] = li;
+                U[o] = (T)((double)e - li * inv_mu);
+            }
+            a[0] += (qz - bi) * (qz - bi);
+            a[1] += bi * li;
+            a[2] += (qx - bi) * (qx - bi);
         }
-        for (; k < end; ++k) {
-            const size_t o = (size_t)ci[k] * B + l;
-            z0 += va[k] * (double)Z[o];
-            x0 += va[k] * (double)X[o];
-        }
-        const double qz = (z0 + z1) + (z2 + z3), qx = (x0 + x1) + (x2 + x3);
-        const size_t o = (size_t)i * B + l;
-        double li = LAM[o];
-        if (run) {
-            const T e = fu[i] * (BV[o] - (T)qx);
-            li = li - mu * (double)e;
-            LAM[o] = li;
-            U[o] = (T)((double)e - li * inv_mu);
-        }
-        const double bi = BV64[o];
-        a[0] += (qz - bi) * (qz - bi);
-        a[1] += bi * li;
-        a[2] += (qx - bi) * (qx - bi);
     }
-    for (int k = 0; k < 3; ++k) s[k][w][lane] = a[k];
-    __syncthreads();
-    if (w == 0)
-        for (int k = 0; k < 3; ++k)
-            part[((size_t)blk * 3 + k) * B + l] = ((s[k][0][lane] + s[k][1][lane]) + s[k][2][lane]) + s[k][3][lane];
+    fam_partials<3, G>(a, blk, B, g, part);
 }
 
 // Residual partials over columns: ||A'lambda + c - delta||^2, c'z (same
-// grid and order as the row partials).
+// blocks as the row partials).
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_fam_res_col(int n, int B, const int *__restrict__ cp, const int *__restrict__ ri, const double *__restrict__ vc,
-              const double *__restrict__ LAM, const double *__restrict__ c, const double *__restrict__ D,
-              const T *__restrict__ Z, double *__restrict__ part)
+__global__ void __launch_bounds__(kFamThreads)
+k_fam_res_col(int n, int m, int B, const int *__restrict__ cp, const int *__restrict__ ri,
+              const double *__restrict__ vc, const double *__restrict__ LAM, const double *__restrict__ c,
+              const double *__restrict__ D, const T *__restrict__ Z, const int *__restrict__ run,
+              const FShared *__restrict__ sh, double *__restrict__ part)
 {
-    __shared__ double s[2][4][64];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int blk = blockIdx.x % kResBlocks, l = (blockIdx.x / kResBlocks) * 64 + lane;
+    constexpr int G = fam_group<T>(), SEG = kFamThreads / G;
+    int g, blk;
+    if (sh->active == 0 || !fam_unit(B / G, kResBlocks, g, blk)) return;
+    const int lane = threadIdx.x % G;
+    if (!__any(run[g * G + lane])) return;
+    const double *L = LAM + (size_t)g * m * G + lane;
+    __shared__ int sp[kFamSegs + 1], si[kFamCap];
+    __shared__ double sv[kFamCap];
     double a[2] = {0.0, 0.0};
-    for (int j = blk * 4 + w; j < n; j += kResBlocks * 4) {
-        const int beg = cp[j], end = cp[j + 1];
-        double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
-        int k = beg;
-        for (; k + 3 < end; k += 4) {
-            t0 += vc[k] * LAM[(size_t)ri[k] * B + l];
-            t1 += vc[k + 1] * LAM[(size_t)ri[k + 1] * B + l];
-            t2 += vc[k + 2] * LAM[(size_t)ri[k + 2] * B + l];
-            t3 += vc[k + 3] * LAM[(size_t)ri[k + 3] * B + l];
+    const int per = (n + kResBlocks - 1) / kResBlocks, j1 = min((blk + 1) * per, n);
+    for (int j0 = blk * per; j0 < j1; j0 += kFamSegs) {
+        const int w = min(kFamSegs, j1 - j0);
+        __syncthreads();
+        const bool staged = fam_stage(j0, w, cp, ri, vc, sp, si, sv);
+        for (int s = threadIdx.x / G; s < w; s += SEG) {
+            const int j = j0 + s;
+            const size_t o = ((size_t)g * n + j) * G + lane;
+            const double d = D[o], zj = (double)Z[o], cj = c[j];
+            const double t = staged ? fam_dot<G, double>(sp[s], sp[s + 1], si, sv, L)
+                                    : fam_dot<G, double>(sp[s], sp[s + 1], ri, vc, L);
+            const double r = t + cj - d;
+            a[0] += r * r;
+            a[1] += cj * zj;
         }
-        for (; k < end; ++k) t0 += vc[k] * LAM[(size_t)ri[k] * B + l];
-        const double t = (t0 + t1) + (t2 + t3);
-        const size_t o = (size_t)j * B + l;
-        const double r = t + c[j] - D[o];
-        a[0] += r * r;
-        a[1] += c[j] * (double)Z[o];
     }
-    for (int k = 0; k < 2; ++k) s[k][w][lane] = a[k];
-    __syncthreads();
-    if (w == 0)
-        for (int k = 0; k < 2; ++k)
-            part[((size_t)blk * 2 + k) * B + l] = ((s[k][0][lane] + s[k][1][lane]) + s[k][2][lane]) + s[k][3][lane];
+    fam_partials<2, G>(a, blk, B, g, part);
 }
 
 constexpr int kFold = 16;  // partial blocks added per thread in the first stage of the check's sum
@@ -333,7 +435,7 @@ k_fam_fold(int B, int nblk, const double *__restrict__ prow, const double *__res
 // One thread per instance: add the group sums of k_fam_fold in order, decide.
 __global__ void __launch_bounds__(1024)
 k_fam_finalize(int B, int nblk, const double *__restrict__ red, double eps, long long max_iter, FInst *inst,
-               FShared *sh)
+               int *__restrict__ run, FShared *sh)
 {
     __shared__ int s_active[1024];
     const int l = threadIdx.x;
@@ -371,6 +473,7 @@ k_fam_finalize(int B, int nblk, const double *__restrict__ red, double eps, long
             else if (kkt <= eps) I.status = UV_STATUS_CONVERGED;
             else if (max_iter > 0 && I.iter >= max_iter) I.status = UV_STATUS_MAX_ITER;
             running = I.status == UV_STATUS_RUNNING;
+            run[l] = running;
         }
     }
     s_active[l] = running;
@@ -382,36 +485,55 @@ k_fam_finalize(int B, int nblk, const double *__restrict__ red, double eps, long
     }
 }
 
-// Instance-major host layout <-> instance-fastest device layout.
+// Instance-major rows <-> the group layout, a workgroup for kTile entries
+// of one group: both sides are read and written in whole lines, the
+// transposition goes through LDS.
+constexpr int kTile = 64;
+constexpr int kMaxGroup = 32;
+
 template <typename S, typename T>
 __global__ void __launch_bounds__(256)
-k_fam_to_dev(int len, int B, int nb, const S *__restrict__ src, T *__restrict__ dst)
+k_fam_to_dev(int len, int G, int nb, const S *__restrict__ src, T *__restrict__ dst)
 {
-    // src[l * len + j] (l < nb) -> dst[j * B + l]; instances >= nb get 0
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (size_t)len * B) return;
-    const int j = (int)(t / B), l = (int)(t % B);
-    dst[t] = l < nb ? (T)src[(size_t)l * len + j] : (T)0;
+    // src[l * len + j] (l < nb) -> entry j of instance l; instances >= nb get 0
+    __shared__ T t[kMaxGroup][kTile + 1];
+    const int tiles = (len + kTile - 1) / kTile, g = blockIdx.x / tiles, j0 = (blockIdx.x % tiles) * kTile;
+    const int w = min(kTile, len - j0);
+    for (int q = threadIdx.x; q < G * kTile; q += 256) {
+        const int l = q / kTile, j = q % kTile;
+        if (j < w) t[l][j] = g * G + l < nb ? (T)src[(size_t)(g * G + l) * len + j0 + j] : (T)0;
+    }
+    __syncthreads();
+    T *out = dst + ((size_t)g * len + j0) * G;
+    for (int q = threadIdx.x; q < G * w; q += 256) out[q] = t[q % G][q / G];
 }
 
 template <typename S, typename T>
 __global__ void __launch_bounds__(256)
-k_fam_from_dev(int len, int B, int nb, const S *__restrict__ src, T *__restrict__ dst, size_t ld, int off)
+k_fam_from_dev(int len, int G, int nb, const S *__restrict__ src, T *__restrict__ dst, size_t ld, int off)
 {
-    // src[j * B + l] -> dst[l * ld + off + j] for l < nb
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (size_t)len * nb) return;
-    const int l = (int)(t / len), j = (int)(t % len);
-    dst[(size_t)l * ld + off + j] = (T)src[(size_t)j * B + l];
+    // entry j of instance l -> dst[l * ld + off + j] for l < nb
+    __shared__ S t[kMaxGroup][kTile + 1];
+    const int tiles = (len + kTile - 1) / kTile, g = blockIdx.x / tiles, j0 = (blockIdx.x % tiles) * kTile;
+    const int w = min(kTile, len - j0);
+    const S *in = src + ((size_t)g * len + j0) * G;
+    for (int q = threadIdx.x; q < G * w; q += 256) t[q % G][q / G] = in[q];
+    __syncthreads();
+    for (int q = threadIdx.x; q < G * kTile; q += 256) {
+        const int l = q / kTile, j = q % kTile;
+        if (j < w && g * G + l < nb) dst[(size_t)(g * G + l) * ld + off + j0 + j] = (T)t[l][j];
+    }
 }
 
-// One instance's column: src[j * B + slot] -> dst[j] (FP64).
+inline unsigned fam_tiles(int len, int groups) { return (unsigned)((len + kTile - 1) / kTile) * (unsigned)groups; }
+
+// One instance's entries -> dst[j] (FP64).
 template <typename S>
 __global__ void __launch_bounds__(256)
-k_fam_slot_from_dev(int len, int B, int slot, const S *__restrict__ src, double *__restrict__ dst)
+k_fam_slot_from_dev(int len, int G, int slot, const S *__restrict__ src, double *__restrict__ dst)
 {
     const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j < len) dst[j] = (double)src[(size_t)j * B + slot];
+    if (j < len) dst[j] = (double)src[fam_at(len, G, j, slot)];
 }
 
 // u = -lambda/mu for all instances, and per-instance reset.
@@ -427,18 +549,21 @@ k_fam_start(size_t len, const double *__restrict__ LAM, T *__restrict__ U, doubl
 // delta = max(c + A'lambda, 0) (the dual-feasible part of the stationarity
 // condition c + A'lambda - delta = 0), u = -lambda/mu.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_fam_dual_start(int n, int B, const int *__restrict__ cp, const int *__restrict__ ri,
+__global__ void __launch_bounds__(kFamThreads)
+k_fam_dual_start(int n, int m, int ng, int nb, const int *__restrict__ cp, const int *__restrict__ ri,
                  const double *__restrict__ vc, const double *__restrict__ LAM, const double *__restrict__ c,
                  const T *__restrict__ X, T *__restrict__ Z, double *__restrict__ D)
 {
-    const int gw = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int ng = B >> 6;
-    const int j = gw / ng, l = (gw % ng) * 64 + lane;
+    constexpr int G = fam_group<T>();
+    int g, blk;
+    if (!fam_unit(ng, nb, g, blk)) return;
+    const int lane = threadIdx.x % G, j = blk * (kFamThreads / G) + threadIdx.x / G;
     if (j >= n) return;
+    const double *L = LAM + (size_t)g * m * G + lane;
     double t = 0.0;
-    for (int k = cp[j]; k < cp[j + 1]; ++k) t += vc[k] * LAM[(size_t)ri[k] * B + l];
-    const size_t o = (size_t)j * B + l;
+#pragma unroll 4
+    for (int k = cp[j]; k < cp[j + 1]; ++k) t += vc[k] * L[(size_t)ri[k] * G];
+    const size_t o = ((size_t)g * n + j) * G + lane;
     const double s = c[j] + t;
     D[o] = s > 0.0 ? s : 0.0;
     const T xo = X[o];
@@ -446,11 +571,11 @@ k_fam_dual_start(int n, int B, const int *__restrict__ cp, const int *__restrict
 }
 
 __global__ void __launch_bounds__(1024)
-k_fam_reset(int B, int nb, FInst *inst, FShared *sh, const double *__restrict__ BV64)
+k_fam_reset(int B, int nb, FInst *inst, int *__restrict__ run, FShared *sh)
 {
-    (void)BV64;
     const int l = threadIdx.x;
     if (l < B) {
+        run[l] = l < nb;
         inst[l].status = l < nb ? UV_STATUS_RUNNING : UV_STATUS_CONVERGED;  // padding lanes never run
         inst[l].iter = 0;
         inst[l].iter0 = 0;
@@ -468,7 +593,7 @@ constexpr int kBChunks = 256;
 static_assert(kBChunks % 8 == 0 && kBChunks <= 3 * kResBlocks, "partials fit the check's row scratch");
 
 __global__ void __launch_bounds__(256)
-k_fam_bnorm_part(int m, int B, const double *__restrict__ BV64, double *__restrict__ part)
+k_fam_bnorm_part(int m, int B, int G, const double *__restrict__ BV64, double *__restrict__ part)
 {
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (size_t)kBChunks * B) return;
@@ -479,7 +604,7 @@ k_fam_bnorm_part(int m, int B, const double *__restrict__ BV64, double *__restri
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int i = i0 + r * kBChunks;
-            v[r] = i < m ? BV64[(size_t)i * B + l] : 0.0;
+            v[r] = i < m ? BV64[fam_at(m, G, i, l)] : 0.0;
         }
 #pragma unroll
         for (int r = 0; r < 8; ++r) s += v[r] * v[r];
@@ -506,13 +631,13 @@ __global__ void __launch_bounds__(1024) k_fam_bnorm(int B, const double *__restr
 // from the FP64 rows b[q * m + i] staged on the device.
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_fam_slot_rhs(int m, int B, int count, const int *__restrict__ slots, const double *__restrict__ b,
+k_fam_slot_rhs(int m, int G, int count, const int *__restrict__ slots, const double *__restrict__ b,
                T *__restrict__ BV, double *__restrict__ BV64)
 {
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (size_t)count * m) return;
     const int q = (int)(t / m), i = (int)(t % m);
-    const size_t o = (size_t)i * B + slots[q];
+    const size_t o = fam_at(m, G, i, slots[q]);
     BV[o] = (T)b[t];
     BV64[o] = b[t];
 }
@@ -522,7 +647,7 @@ k_fam_slot_rhs(int m, int B, int count, const int *__restrict__ slots, const dou
 // family_set_start_predicted), or zero when xl is null.
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_fam_slot_xl(int n, int m, int B, int count, const int *__restrict__ slots, const float *__restrict__ xl,
+k_fam_slot_xl(int n, int m, int G, int count, const int *__restrict__ slots, const float *__restrict__ xl,
               long long ld, int parts, T *__restrict__ X, double *__restrict__ LAM)
 {
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -532,15 +657,15 @@ k_fam_slot_xl(int n, int m, int B, int count, const int *__restrict__ slots, con
     const int sl = slots[q];
     const bool use = xl && (j < n ? (parts & 1) : (parts & 2));
     const float v = use ? xl[(size_t)q * ld + j] : 0.0f;
-    if (j < n) X[(size_t)j * B + sl] = (T)v;
-    else LAM[(size_t)(j - n) * B + sl] = (double)v;
+    if (j < n) X[fam_at(n, G, j, sl)] = (T)v;
+    else LAM[fam_at(m, G, j - n, sl)] = (double)v;
 }
 
 // Refill: z = max(x, 0) and delta = max(c + A'lambda, 0) of the entering
 // members (the arithmetic of k_fam_dual_start; zero for a zero start).
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_fam_slot_zd(int n, int B, int count, const int *__restrict__ slots, const int *__restrict__ cp,
+k_fam_slot_zd(int n, int m, int G, int count, const int *__restrict__ slots, const int *__restrict__ cp,
               const int *__restrict__ ri, const double *__restrict__ vc, const double *__restrict__ LAM,
               const double *__restrict__ c, const T *__restrict__ X, T *__restrict__ Z, double *__restrict__ D,
               int zero)
@@ -549,14 +674,14 @@ k_fam_slot_zd(int n, int B, int count, const int *__restrict__ slots, const int 
     if (t >= (size_t)count * n) return;
     const int q = (int)(t / n), j = (int)(t % n);
     const int sl = slots[q];
-    const size_t o = (size_t)j * B + sl;
+    const size_t o = fam_at(n, G, j, sl);
     if (zero) {
         Z[o] = (T)0;
         D[o] = 0.0;
         return;
     }
     double a = 0.0;
-    for (int k = cp[j]; k < cp[j + 1]; ++k) a += vc[k] * LAM[(size_t)ri[k] * B + sl];
+    for (int k = cp[j]; k < cp[j + 1]; ++k) a += vc[k] * LAM[fam_at(m, G, ri[k], sl)];
     const double v = c[j] + a;
     D[o] = v > 0.0 ? v : 0.0;
     const T xo = X[o];
@@ -566,26 +691,27 @@ k_fam_slot_zd(int n, int B, int count, const int *__restrict__ slots, const int 
 // Refill: u = -lambda/mu of the entering members.
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_fam_slot_u(int m, int B, int count, const int *__restrict__ slots, const double *__restrict__ LAM,
+k_fam_slot_u(int m, int G, int count, const int *__restrict__ slots, const double *__restrict__ LAM,
              T *__restrict__ U, double inv_mu)
 {
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (size_t)count * m) return;
     const int q = (int)(t / m), i = (int)(t % m);
-    const size_t o = (size_t)i * B + slots[q];
+    const size_t o = fam_at(m, G, i, slots[q]);
     U[o] = (T)(-LAM[o] * inv_mu);
 }
 
 // Refill: the entering members run from the family's current iteration;
 // the running count is taken again.
 __global__ void __launch_bounds__(1024)
-k_fam_slot_reset(int B, int count, const int *__restrict__ slots, FInst *inst, FShared *sh)
+k_fam_slot_reset(int B, int count, const int *__restrict__ slots, FInst *inst, int *__restrict__ run, FShared *sh)
 {
     __shared__ int s_run[1024];
     const int l = threadIdx.x;
     if (l < count) {
         FInst &I = inst[slots[l]];
         I.status = UV_STATUS_RUNNING;
+        run[slots[l]] = 1;
         I.iter = 0;
         I.iter0 = sh->iter;
     }
@@ -603,6 +729,8 @@ k_fam_slot_reset(int B, int count, const int *__restrict__ slots, FInst *inst, F
 
 struct uv_family {
     int m = 0, n = 0, nnz = 0, B = 0, nb = 0;
+    int G = 32;               // instances a group (fam_group)
+    bool big = false;         // the iterates exceed the Infinity Cache
     uv_opts o{};
     hipStream_t stream = nullptr, cap = nullptr;
     bool own_stream = false;
@@ -616,6 +744,7 @@ struct uv_family {
     double *stage = nullptr;  // B * max(m, n) doubles of staging
     FInst *inst = nullptr, *inst_host = nullptr;
     FShared *sh = nullptr, *sh_host = nullptr;
+    int *run = nullptr;       // 1 for a running instance (as inst[].status says)
     int *slots = nullptr;     // slot list of a refill (B entries)
     bool refilled = false;    // a member entered after the last set_rhs / set_start
     hipGraph_t graph = nullptr;
@@ -643,25 +772,30 @@ template <typename T>
 void fam_iteration_t(uv_family *h, hipStream_t st, bool check)
 {
     const double mu = h->o.mu, im = 1.0 / h->o.mu;
-    const int ng = h->B / 64;
-    k_fam_col<T><<<fam_blocks(h->n, ng), 256, 0, st>>>(
-        h->n, h->B, h->cp, h->ri, (const T *)h->vc, (const T *)h->U, (T *)h->X, (T *)h->Z, h->D, (const T *)h->c,
-        h->inst, mu, im, h->sh);
+    const int ng = h->B / h->G, wc = fam_segs(h->n, ng, h->G), wr = fam_segs(h->m, ng, h->G);
+    const int bc = fam_blocks(h->n, wc), br = fam_blocks(h->m, wr);
+#define UV_COL_ARGS                                                                                               \
+    h->n, h->m, ng, bc, wc, h->cp, h->ri, (const T *)h->vc, (const T *)h->U, (T *)h->X, (T *)h->Z, h->D,          \
+        (const T *)h->c, h->run, mu, im, h->sh
+#define UV_ROW_ARGS                                                                                               \
+    h->m, h->n, ng, br, wr, h->rp, h->ci, (const T *)h->va, (const T *)h->X, (const T *)h->BV, (const T *)h->fu, \
+        h->LAM, (T *)h->U, h->run, mu, im, h->sh
+    if (h->big) k_fam_col<T, true><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(UV_COL_ARGS);
+    else k_fam_col<T, false><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(UV_COL_ARGS);
     if (!check) {
-        k_fam_row<T><<<fam_blocks(h->m, ng), 256, 0, st>>>(
-            h->m, h->B, h->rp, h->ci, (const T *)h->va, (const T *)h->X, (const T *)h->BV, (const T *)h->fu, h->LAM,
-            (T *)h->U, h->inst, mu, im, h->sh);
+        if (h->big) k_fam_row<T, true><<<fam_grid(ng, br), kFamThreads, 0, st>>>(UV_ROW_ARGS);
+        else k_fam_row<T, false><<<fam_grid(ng, br), kFamThreads, 0, st>>>(UV_ROW_ARGS);
     } else {
-        k_fam_row_check<T><<<kResBlocks * ng, 256, 0, st>>>(
-            h->m, h->B, h->rp, h->ci, h->va64, (const T *)h->X, (const T *)h->Z, (const T *)h->BV, h->BV64,
-            (const T *)h->fu, h->LAM, (T *)h->U, h->inst, mu, im, h->sh, h->prow);
-        k_fam_res_col<T><<<kResBlocks * (h->B / 64), 256, 0, st>>>(h->n, h->B, h->cp, h->ri, h->vc64, h->LAM, h->c64, h->D,
-                                                     (const T *)h->Z, h->pcol);
-        const int ng = kResBlocks / kFold;
-        k_fam_fold<<<blocks_for((int64_t)ng * 5 * h->B, 256), 256, 0, st>>>(h->B, kResBlocks, h->prow, h->pcol,
+        k_fam_row_check<T><<<fam_grid(ng, kResBlocks), kFamThreads, 0, st>>>(
+            h->m, h->n, h->B, h->rp, h->ci, h->va64, (const T *)h->X, (const T *)h->Z, (const T *)h->BV, h->BV64,
+            (const T *)h->fu, h->LAM, (T *)h->U, h->run, mu, im, h->sh, h->prow);
+        k_fam_res_col<T><<<fam_grid(ng, kResBlocks), kFamThreads, 0, st>>>(
+            h->n, h->m, h->B, h->cp, h->ri, h->vc64, h->LAM, h->c64, h->D, (const T *)h->Z, h->run, h->sh, h->pcol);
+        const int nf = kResBlocks / kFold;
+        k_fam_fold<<<blocks_for((int64_t)nf * 5 * h->B, 256), 256, 0, st>>>(h->B, kResBlocks, h->prow, h->pcol,
                                                                            h->pred);
-        k_fam_finalize<<<1, 1024, 0, st>>>(h->B, ng, h->pred, h->o.eps_kkt, (long long)h->o.max_iter, h->inst,
-                                           h->sh);
+        k_fam_finalize<<<1, 1024, 0, st>>>(h->B, nf, h->pred, h->o.eps_kkt, (long long)h->o.max_iter, h->inst,
+                                           h->run, h->sh);
     }
 }
 
@@ -687,11 +821,11 @@ int upload_cols(uv_family *h, const S *src, int len, void *dst, bool to_f64)
     hipStream_t st = h->stream;
     const size_t bytes = sizeof(S) * (size_t)h->nb * len;
     UV_FTRY(hipMemcpyAsync(h->stage, src, bytes, hipMemcpyHostToDevice, st));
-    const unsigned g = blocks_for((int64_t)len * h->B, 256);
-    if (to_f64) k_fam_to_dev<S, double><<<g, 256, 0, st>>>(len, h->B, h->nb, (const S *)h->stage, (double *)dst);
+    const unsigned g = fam_tiles(len, h->B / h->G);
+    if (to_f64) k_fam_to_dev<S, double><<<g, 256, 0, st>>>(len, h->G, h->nb, (const S *)h->stage, (double *)dst);
     else if (h->o.precision == UV_MIXED)
-        k_fam_to_dev<S, float><<<g, 256, 0, st>>>(len, h->B, h->nb, (const S *)h->stage, (float *)dst);
-    else k_fam_to_dev<S, double><<<g, 256, 0, st>>>(len, h->B, h->nb, (const S *)h->stage, (double *)dst);
+        k_fam_to_dev<S, float><<<g, 256, 0, st>>>(len, h->G, h->nb, (const S *)h->stage, (float *)dst);
+    else k_fam_to_dev<S, double><<<g, 256, 0, st>>>(len, h->G, h->nb, (const S *)h->stage, (double *)dst);
     UV_FTRY(hipGetLastError());
     UV_FTRY(hipStreamSynchronize(st));  // the staging buffer is reused
     return UV_OK;
@@ -768,6 +902,8 @@ int family_create(const uv_csr *A, const double *c, int32_t B, const uv_opts *op
     const int m = h->m, n = h->n, nnz = h->nnz;
     const bool mixed = o.precision == UV_MIXED;
     const size_t ts = mixed ? 4 : 8;
+    h->G = mixed ? fam_group<float>() : fam_group<double>();
+    h->big = (size_t)B * ((2 * ts + 8) * n + (2 * ts + 8) * m) > ((size_t)256 << 20);
     if (o.hip_stream) h->stream = (hipStream_t)o.hip_stream;
     else {
         if (hipStreamCreateWithFlags(&h->stream, hipStreamNonBlocking) != hipSuccess) return fail(UV_EHIP);
@@ -807,12 +943,13 @@ int family_create(const uv_csr *A, const double *c, int32_t B, const uv_opts *op
     h->inst = falloc<FInst>(h, B);
     h->sh = falloc<FShared>(h, 1);
     h->slots = falloc<int>(h, B);
+    h->run = falloc<int>(h, B);
     int *cnt = falloc<int>(h, n);
     int *bsum = falloc<int>(h, blocks_for(n, 4 * kWG));
     for (void *p : {(void *)h->rp, (void *)h->ci, (void *)h->va64, (void *)h->cp, (void *)h->ri, (void *)h->vc64,
                     (void *)h->c64, h->fu, h->va, h->vc, h->c, h->X, h->Z, h->U, h->BV, (void *)h->LAM,
                     (void *)h->D, (void *)h->BV64, (void *)h->prow, (void *)h->pcol, (void *)h->pred, (void *)h->stage,
-                    (void *)h->inst, (void *)h->sh, (void *)h->slots, (void *)cnt, (void *)bsum})
+                    (void *)h->inst, (void *)h->sh, (void *)h->slots, (void *)h->run, (void *)cnt, (void *)bsum})
         if (!p) return fail(UV_ENOMEM);
     if (uv::host_malloc(&h->inst_host, sizeof(FInst) * B, hipHostMallocDefault) != hipSuccess) {
         h->inst_host = nullptr;
@@ -853,6 +990,8 @@ int family_create(const uv_csr *A, const double *c, int32_t B, const uv_opts *op
         std::memset(i0.data(), 0, sizeof(FInst) * B);
         for (auto &x : i0) x.status = UV_STATUS_CONVERGED;  // nothing runs before a right-hand side is set
         if (hipMemcpy(h->inst, i0.data(), sizeof(FInst) * B, hipMemcpyHostToDevice) != hipSuccess) return fail(UV_EHIP);
+        const std::vector<int> none(B, 0);
+        if (hipMemcpy(h->run, none.data(), sizeof(int) * B, hipMemcpyHostToDevice) != hipSuccess) return fail(UV_EHIP);
     }
     if (hipStreamSynchronize(st) != hipSuccess) return fail(UV_EHIP);
     int rc = fam_rebuild_graph(h);
@@ -870,7 +1009,8 @@ int family_set_rhs(uv_family *h, int32_t nb, const double *b)
     if ((rc = upload_cols<double>(h, b, h->m, h->BV, false)) != UV_OK) return rc;
     if ((rc = upload_cols<double>(h, b, h->m, h->BV64, true)) != UV_OK) return rc;
     // the check's row partials serve as scratch (kResBlocks * 3 * B >= kBChunks * B doubles)
-    k_fam_bnorm_part<<<blocks_for((int64_t)kBChunks * h->B, 256), 256, 0, h->stream>>>(h->m, h->B, h->BV64, h->prow);
+    k_fam_bnorm_part<<<blocks_for((int64_t)kBChunks * h->B, 256), 256, 0, h->stream>>>(h->m, h->B, h->G, h->BV64,
+                                                                                               h->prow);
     k_fam_bnorm<<<1, 1024, 0, h->stream>>>(h->B, h->prow, h->inst);
     UV_FTRY(hipGetLastError());
     return family_set_start(h, nullptr, nullptr, nullptr, nullptr);
@@ -894,7 +1034,7 @@ int family_set_start(uv_family *h, const double *x, const double *z, const doubl
     const double im = 1.0 / h->o.mu;
     if (h->o.precision == UV_MIXED) k_fam_start<float><<<blocks_for(Bm, 256), 256, 0, st>>>(Bm, h->LAM, (float *)h->U, im);
     else k_fam_start<double><<<blocks_for(Bm, 256), 256, 0, st>>>(Bm, h->LAM, (double *)h->U, im);
-    k_fam_reset<<<1, 1024, 0, st>>>(h->B, h->nb, h->inst, h->sh, h->BV64);
+    k_fam_reset<<<1, 1024, 0, st>>>(h->B, h->nb, h->inst, h->run, h->sh);
     h->refilled = false;
     UV_FTRY(hipGetLastError());
     return fam_sync(h);
@@ -921,28 +1061,28 @@ int family_set_start_predicted(uv_family *h, const float *xl_dev, int64_t ld, in
         float *stg = (float *)h->stage;
         UV_FTRY(hipMemcpy2DAsync(stg, sizeof(float) * len, xl_dev + off, sizeof(float) * ld, sizeof(float) * len, nb,
                                  hipMemcpyDeviceToDevice, st));
-        const unsigned g = blocks_for((int64_t)len * B, 256);
+        const unsigned g = fam_tiles(len, B / h->G);
         if (part == 0) {
-            if (h->o.precision == UV_MIXED) k_fam_to_dev<float, float><<<g, 256, 0, st>>>(len, B, nb, stg, (float *)h->X);
-            else k_fam_to_dev<float, double><<<g, 256, 0, st>>>(len, B, nb, stg, (double *)h->X);
+            if (h->o.precision == UV_MIXED) k_fam_to_dev<float, float><<<g, 256, 0, st>>>(len, h->G, nb, stg, (float *)h->X);
+            else k_fam_to_dev<float, double><<<g, 256, 0, st>>>(len, h->G, nb, stg, (double *)h->X);
         } else {
-            k_fam_to_dev<float, double><<<g, 256, 0, st>>>(len, B, nb, stg, h->LAM);
+            k_fam_to_dev<float, double><<<g, 256, 0, st>>>(len, h->G, nb, stg, h->LAM);
         }
         UV_FTRY(hipGetLastError());
         UV_FTRY(hipStreamSynchronize(st));
     }
-    const int ng = B / 64;
+    const int ng = B / h->G, bc = (h->n + kFamThreads / h->G - 1) / (kFamThreads / h->G);
     const double im = 1.0 / h->o.mu;
     if (h->o.precision == UV_MIXED) {
-        k_fam_dual_start<float><<<blocks_for((int64_t)h->n * ng, 4), 256, 0, st>>>(
-            h->n, B, h->cp, h->ri, h->vc64, h->LAM, h->c64, (const float *)h->X, (float *)h->Z, h->D);
+        k_fam_dual_start<float><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(
+            h->n, h->m, ng, bc, h->cp, h->ri, h->vc64, h->LAM, h->c64, (const float *)h->X, (float *)h->Z, h->D);
         k_fam_start<float><<<blocks_for(Bm, 256), 256, 0, st>>>(Bm, h->LAM, (float *)h->U, im);
     } else {
-        k_fam_dual_start<double><<<blocks_for((int64_t)h->n * ng, 4), 256, 0, st>>>(
-            h->n, B, h->cp, h->ri, h->vc64, h->LAM, h->c64, (const double *)h->X, (double *)h->Z, h->D);
+        k_fam_dual_start<double><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(
+            h->n, h->m, ng, bc, h->cp, h->ri, h->vc64, h->LAM, h->c64, (const double *)h->X, (double *)h->Z, h->D);
         k_fam_start<double><<<blocks_for(Bm, 256), 256, 0, st>>>(Bm, h->LAM, (double *)h->U, im);
     }
-    k_fam_reset<<<1, 1024, 0, st>>>(h->B, h->nb, h->inst, h->sh, h->BV64);
+    k_fam_reset<<<1, 1024, 0, st>>>(h->B, h->nb, h->inst, h->run, h->sh);
     h->refilled = false;
     UV_FTRY(hipGetLastError());
     return fam_sync(h);
@@ -970,24 +1110,24 @@ int family_refill(uv_family *h, int32_t count, const int32_t *slots, const doubl
     const unsigned gm = blocks_for((int64_t)count * m, 256), gn = blocks_for((int64_t)count * n, 256);
     const unsigned gx = blocks_for((int64_t)count * (n + m), 256);
     if (mixed) {
-        k_fam_slot_rhs<float><<<gm, 256, 0, st>>>(m, B, count, h->slots, h->stage, (float *)h->BV, h->BV64);
-        k_fam_slot_xl<float><<<gx, 256, 0, st>>>(n, m, B, count, h->slots, xl_dev, ld, parts, (float *)h->X, h->LAM);
-        k_fam_slot_zd<float><<<gn, 256, 0, st>>>(n, B, count, h->slots, h->cp, h->ri, h->vc64, h->LAM, h->c64,
+        k_fam_slot_rhs<float><<<gm, 256, 0, st>>>(m, h->G, count, h->slots, h->stage, (float *)h->BV, h->BV64);
+        k_fam_slot_xl<float><<<gx, 256, 0, st>>>(n, m, h->G, count, h->slots, xl_dev, ld, parts, (float *)h->X, h->LAM);
+        k_fam_slot_zd<float><<<gn, 256, 0, st>>>(n, m, h->G, count, h->slots, h->cp, h->ri, h->vc64, h->LAM, h->c64,
                                                  (const float *)h->X, (float *)h->Z, h->D, xl_dev ? 0 : 1);
-        k_fam_slot_u<float><<<gm, 256, 0, st>>>(m, B, count, h->slots, h->LAM, (float *)h->U, im);
+        k_fam_slot_u<float><<<gm, 256, 0, st>>>(m, h->G, count, h->slots, h->LAM, (float *)h->U, im);
     } else {
-        k_fam_slot_rhs<double><<<gm, 256, 0, st>>>(m, B, count, h->slots, h->stage, (double *)h->BV, h->BV64);
-        k_fam_slot_xl<double><<<gx, 256, 0, st>>>(n, m, B, count, h->slots, xl_dev, ld, parts, (double *)h->X,
+        k_fam_slot_rhs<double><<<gm, 256, 0, st>>>(m, h->G, count, h->slots, h->stage, (double *)h->BV, h->BV64);
+        k_fam_slot_xl<double><<<gx, 256, 0, st>>>(n, m, h->G, count, h->slots, xl_dev, ld, parts, (double *)h->X,
                                                   h->LAM);
-        k_fam_slot_zd<double><<<gn, 256, 0, st>>>(n, B, count, h->slots, h->cp, h->ri, h->vc64, h->LAM, h->c64,
+        k_fam_slot_zd<double><<<gn, 256, 0, st>>>(n, m, h->G, count, h->slots, h->cp, h->ri, h->vc64, h->LAM, h->c64,
                                                   (const double *)h->X, (double *)h->Z, h->D, xl_dev ? 0 : 1);
-        k_fam_slot_u<double><<<gm, 256, 0, st>>>(m, B, count, h->slots, h->LAM, (double *)h->U, im);
+        k_fam_slot_u<double><<<gm, 256, 0, st>>>(m, h->G, count, h->slots, h->LAM, (double *)h->U, im);
     }
     // ||b||^2 of every slot again (same fixed order as at set_rhs; the
     // check's row partials serve as scratch)
-    k_fam_bnorm_part<<<blocks_for((int64_t)kBChunks * B, 256), 256, 0, st>>>(m, B, h->BV64, h->prow);
+    k_fam_bnorm_part<<<blocks_for((int64_t)kBChunks * B, 256), 256, 0, st>>>(m, B, h->G, h->BV64, h->prow);
     k_fam_bnorm<<<1, 1024, 0, st>>>(B, h->prow, h->inst);
-    k_fam_slot_reset<<<1, 1024, 0, st>>>(B, count, h->slots, h->inst, h->sh);
+    k_fam_slot_reset<<<1, 1024, 0, st>>>(B, count, h->slots, h->inst, h->run, h->sh);
     UV_FTRY(hipGetLastError());
     h->refilled = true;
     return fam_sync(h);
@@ -1064,11 +1204,11 @@ int family_solution(uv_family *h, double *x, double *z, double *lambda, double *
     const bool mixed = h->o.precision == UV_MIXED;
     auto get = [&](double *dst, const void *src, int len, bool f64) -> int {
         if (!dst) return UV_OK;
-        const unsigned g = blocks_for((int64_t)len * nb, 256);
+        const unsigned g = fam_tiles(len, B / h->G);
         if (f64 || !mixed)
-            k_fam_from_dev<double, double><<<g, 256, 0, st>>>(len, B, nb, (const double *)src, h->stage, (size_t)len, 0);
+            k_fam_from_dev<double, double><<<g, 256, 0, st>>>(len, h->G, nb, (const double *)src, h->stage, (size_t)len, 0);
         else
-            k_fam_from_dev<float, double><<<g, 256, 0, st>>>(len, B, nb, (const float *)src, h->stage, (size_t)len, 0);
+            k_fam_from_dev<float, double><<<g, 256, 0, st>>>(len, h->G, nb, (const float *)src, h->stage, (size_t)len, 0);
         if (hipMemcpyAsync(dst, h->stage, 8 * (size_t)len * nb, hipMemcpyDeviceToHost, st) != hipSuccess) return UV_EHIP;
         return hipStreamSynchronize(st) == hipSuccess ? UV_OK : UV_EHIP;
     };
@@ -1089,9 +1229,9 @@ int family_member_state(uv_family *h, int32_t slot, double *x, double *z, double
         if (!dst) return UV_OK;
         const unsigned g = blocks_for(len, 256);
         if (f64 || !mixed)
-            k_fam_slot_from_dev<double><<<g, 256, 0, st>>>(len, h->B, slot, (const double *)src, h->stage);
+            k_fam_slot_from_dev<double><<<g, 256, 0, st>>>(len, h->G, slot, (const double *)src, h->stage);
         else
-            k_fam_slot_from_dev<float><<<g, 256, 0, st>>>(len, h->B, slot, (const float *)src, h->stage);
+            k_fam_slot_from_dev<float><<<g, 256, 0, st>>>(len, h->G, slot, (const float *)src, h->stage);
         if (hipMemcpyAsync(dst, h->stage, 8 * (size_t)len, hipMemcpyDeviceToHost, st) != hipSuccess) return UV_EHIP;
         return hipStreamSynchronize(st) == hipSuccess ? UV_OK : UV_EHIP;
     };
@@ -1109,13 +1249,13 @@ int family_solution_device(uv_family *h, float *dst_dev, int64_t ld)
     if (!h || !dst_dev || h->nb < 1 || ld < (int64_t)h->n + h->m) return UV_EINVAL;
     hipStream_t st = h->stream;
     const int B = h->B, nb = h->nb;
-    unsigned g = blocks_for((int64_t)h->n * nb, 256);
+    unsigned g = fam_tiles(h->n, B / h->G);
     if (h->o.precision == UV_MIXED)
-        k_fam_from_dev<float, float><<<g, 256, 0, st>>>(h->n, B, nb, (const float *)h->Z, dst_dev, (size_t)ld, 0);
+        k_fam_from_dev<float, float><<<g, 256, 0, st>>>(h->n, h->G, nb, (const float *)h->Z, dst_dev, (size_t)ld, 0);
     else
-        k_fam_from_dev<double, float><<<g, 256, 0, st>>>(h->n, B, nb, (const double *)h->Z, dst_dev, (size_t)ld, 0);
-    g = blocks_for((int64_t)h->m * nb, 256);
-    k_fam_from_dev<double, float><<<g, 256, 0, st>>>(h->m, B, nb, h->LAM, dst_dev, (size_t)ld, h->n);
+        k_fam_from_dev<double, float><<<g, 256, 0, st>>>(h->n, h->G, nb, (const double *)h->Z, dst_dev, (size_t)ld, 0);
+    g = fam_tiles(h->m, B / h->G);
+    k_fam_from_dev<double, float><<<g, 256, 0, st>>>(h->m, h->G, nb, h->LAM, dst_dev, (size_t)ld, h->n);
     UV_FTRY(hipGetLastError());
     UV_FTRY(hipStreamSynchronize(st));
     return UV_OK;
