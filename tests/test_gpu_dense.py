@@ -1,0 +1,56 @@
+"""The FP32 matrix-core GEMM at the sizes where it can go wrong: edges of the
+64 x 64 x 32 tiles, k split within workgroups and not, every operand order,
+strides that are not one."""
+import ctypes
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+U32 = 2.0 ** -24
+
+
+def _bound(A, B, K):
+    """Any order of FP32 products and sums: (K + 2) u sum_k |a_ik| |b_kj|."""
+    return (K + 2) * U32 * (A.abs().double() @ B.abs().double()) + 1e-30
+
+
+@pytest.mark.parametrize("tA,tB", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (63, 65, 31), (64, 64, 32), (65, 130, 33), (200, 3, 4096),
+                                   (17, 70, 2053), (513, 1025, 100)])
+def test_gemm_tile_edges(M, N, K, tA, tB):
+    import torch
+    from paper_2203_05027_amd import learn
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * 7 + N * 3 + K)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    B = torch.randn(K, N, generator=g, device="cuda")
+    C0 = torch.randn(M, N, generator=g, device="cuda")
+    As, Bs = (A.t().contiguous() if tA else A), (B.t().contiguous() if tB else B)
+    C = C0.clone()
+    learn.gemm(As, Bs, C, alpha=0.5, beta=-2.0, transA=tA, transB=tB)
+    ref = 0.5 * (A.double() @ B.double()) - 2.0 * C0.double()
+    err = (C.double() - ref).abs()
+    assert bool((err <= _bound(A, B, K) + 4 * U32 * C0.abs().double()).all()), float(err.max())
+
+
+def test_gemm_general_strides_and_unaligned_operands():
+    import torch
+    from paper_2203_05027_amd import learn
+    from paper_2203_05027_amd.solver import lib
+    M, N, K = 77, 90, 150
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    bufA = torch.randn(M * K * 2 + 1, generator=g, device="cuda")
+    bufB = torch.randn(K * N * 3 + 3, generator=g, device="cuda")
+    learn._bind()
+    for a_off, a_rs, a_cs, b_off, b_rs, b_cs in [(0, 2 * K, 2, 0, 3 * N, 3), (1, K, 1, 3, N, 1), (1, 1, M, 1, 1, K),
+                                                 (0, 2, 2 * M, 1, N + 1, 1)]:
+        A = torch.as_strided(bufA, (M, K), (a_rs, a_cs), a_off)
+        B = torch.as_strided(bufB, (K, N), (b_rs, b_cs), b_off)
+        C = torch.full((M, N + 5), 7.0, device="cuda")  # ldc > N: the margin is left alone
+        p = lambda t, o=0: ctypes.c_void_p(t.data_ptr() + 4 * o)
+        rc = lib().gemm_f32(M, N, K, p(bufA, a_off), a_rs, a_cs, p(bufB, b_off), b_rs, b_cs, p(C), N + 5, 1.0, 0.0, None)
+        assert rc == 0
+        err = (C[:, :N].double() - A.double() @ B.double()).abs()
+        assert bool((err <= _bound(A, B, K)).all()), float(err.max())
+        assert bool((C[:, N:] == 7.0).all())
