@@ -110,7 +110,7 @@ struct Tile {
 // reading A from HBM, which the split shares among the compute units.
 // Against the vector units' 16-deep slices and no split: 4096^3 2.36 -> 1.35
 // ms (102 TFLOP/s), 2000 x 30000 x 96 253 -> 187 us, 2000 x 96 x 30000 4.86
-// -> 0.58 ms without a workspace and 0.10 ms with one; the products of a PCA
+// -> 0.58 ms without a workspace and under 0.25 ms with one; the products of a PCA
 // fit of 2000 x 30000 samples (l = 128) 51 -> 2.5 ms.
 template <int AM, int BM, int KS>
 __global__ void __launch_bounds__(256 * KS)
@@ -414,17 +414,19 @@ int gemm(hipStream_t st, int M, int N, int K, const float *A, int64_t a_rs, int6
 
 // ---- host-side small dense factorizations (l x l, row-major) ----
 
-// Lower Cholesky G = L L'.  A non-positive pivot (rank loss) is replaced by
-// a tiny positive one so the factor stays finite.
+// Lower Cholesky G = L L' of FP32 products.  A pivot at their rounding level
+// (rank loss) is replaced by the largest diagonal entry: the dependent column
+// then fades by that much instead of being scaled up to overflow.
 void chol_lower(std::vector<double> &G, int l)
 {
     double scale = 0.0;
     for (int i = 0; i < l; ++i) scale = std::max(scale, G[(size_t)i * l + i]);
-    const double floor_ = std::max(scale, 1e-300) * 1e-14;
+    if (!(scale > 0.0)) scale = 1.0;
+    const double floor_ = scale * 2.4e-7;  // 4 u of FP32
     for (int j = 0; j < l; ++j) {
         double d = G[(size_t)j * l + j];
         for (int k = 0; k < j; ++k) d -= G[(size_t)j * l + k] * G[(size_t)j * l + k];
-        d = std::sqrt(std::max(d, floor_));
+        d = std::sqrt(d > floor_ ? d : scale);
         G[(size_t)j * l + j] = d;
         for (int i = j + 1; i < l; ++i) {
             double s = G[(size_t)i * l + j];

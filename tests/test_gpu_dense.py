@@ -1,8 +1,10 @@
-"""The FP32 matrix-core GEMM at the sizes where it can go wrong: edges of the
-64 x 64 x 32 tiles, k split within workgroups and not, every operand order,
-strides that are not one."""
+"""The FP32 matrix-core GEMM and the PCA fit at the sizes where they can go
+wrong: edges of the 64 x 64 x 32 tiles, k split within workgroups and not,
+every operand order, strides that are not one; odd, smallest and rank-deficient
+eigenproblems."""
 import ctypes
 
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -54,3 +56,27 @@ def test_gemm_general_strides_and_unaligned_operands():
         err = (C[:, :N].double() - A.double() @ B.double()).abs()
         assert bool((err <= _bound(A, B, K)).all()), float(err.max())
         assert bool((C[:, N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("N,D,k,over", [(37, 50, 20, 32), (2, 5, 1, 0), (1, 7, 1, 3), (70, 41, 41, 32), (300, 200, 8, 9)])
+def test_pca_spans_and_odd_sizes(N, D, k, over):
+    """Samples of rank k plus noise 1e-3 of its smallest direction: mean,
+    singular values and the reconstruction of an FP64 decomposition (FP32
+    data and products through five of them: 1e-4); rank-k inputs that fill
+    the whole space come back whole."""
+    import torch
+    from paper_2203_05027_amd import learn
+    rng = np.random.default_rng(N + D)
+    r = min(k, N, D)
+    Y = (rng.standard_normal((N, r)) @ rng.standard_normal((r, D)) + rng.standard_normal(D)).astype(np.float32)
+    Y += (1e-3 * rng.standard_normal((N, D))).astype(np.float32)
+    mean, basis, sv = learn.pca_fit(torch.from_numpy(Y).cuda(), k, oversample=over)
+    m = Y.astype(np.float64).mean(0)
+    Uo, so, Vo = np.linalg.svd(Y - m, full_matrices=False)
+    assert np.abs(mean.cpu().numpy() - m).max() <= 1e-5 * max(np.abs(m).max(), 1.0)
+    top = max(so[0], 1e-30)
+    assert np.abs(sv[: min(k, so.size)] - so[:k]).max() <= 1e-4 * top + 1e-4
+    B = basis.cpu().numpy().astype(np.float64)
+    back = (Y - m) @ B.T @ B
+    want = (Uo[:, :k] * so[:k]) @ Vo[:k]
+    assert np.linalg.norm(back - want) <= 2e-3 * np.linalg.norm(want) + 1e-3
