@@ -36,7 +36,39 @@ enum Epi {
     EPI_F32 = 0,        // C (FP32)
     EPI_BIAS_RELU = 1,  // relu(C + bias) -> BF16 activation
     EPI_BIAS_F32 = 2,   // C + bias -> FP32 output
-    EPI_MASK = 3,       // C * [act > 0] -> FP32 and BF16 (gradient through a ReLU)
+    EPI_MASK = 3,       // C * [act > 0] -> BF16 (gradient through a ReLU), and its column sums
+    EPI_MSE = 4,        // 2 (C + bias - target) / len -> BF16, its column sums and the squared error's
+    EPI_ADAM = 5,       // C is a weight gradient: the Adam step of the weights and their BF16 copy
+};
+
+// Adam's constants of one step (bias corrections c1, c2).
+struct AdamStep {
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ float adam(float p, float g, float &m1, float &m2, const AdamStep &s)
+{
+    const float a = s.b1 * m1 + (1.f - s.b1) * g;
+    const float v = s.b2 * m2 + (1.f - s.b2) * g * g;
+    m1 = a;
+    m2 = v;
+    const float upd = s.lr * (a / s.c1) / (sqrtf(v / s.c2) + s.eps);
+    return p - upd;
+}
+
+// What an epilogue reads and writes (see Epi).
+struct EpiArgs {
+    float *Cf;
+    uint16_t *Cb;
+    int64_t ldc;
+    const float *bias;
+    const uint16_t *act;
+    const float *target;
+    float scale;        // 2 / len
+    float *colsum;      // [2 * block row + wave row][N]: column sums of the FP32 gradient
+    double *sqerr;      // one per workgroup
+    float *m1, *m2;
+    AdamStep step;
 };
 
 // How a GEMM operand tile is read from global memory: 16-byte loads of
@@ -45,11 +77,13 @@ enum Epi {
 // neither stride is 1 or the addresses are not 16-byte aligned.
 enum LoadMode { LD_KC = 0, LD_MC = 1, LD_EL = 2 };
 
-constexpr int kBK = 64;           // k per staged step (two 16x16x32 MFMAs)
-constexpr int kLK = kBK + 8;      // LDS row pitch in elements (144 bytes: 16-byte aligned rows)
+constexpr int kBK = 64;           // k per staged step of the 64 x 64 and larger blocks
+constexpr int kDeep = 256;        // k per staged step of the 32 x 32 blocks
+// LDS row pitch in elements of a BK-deep tile (16-byte aligned rows)
+constexpr int pitch(int BK) { return BK + 8; }
 
 // The loads of one operand tile (ROWS rows of the tile's m or n dimension,
-// k0..k0+63) of a thread: ROWS * 8 / 256 chunks of eight elements, held in
+// k0..k0+BK-1) of a thread: ROWS * BK / 8 / 256 chunks of eight elements, held in
 // registers between the global loads and the LDS stores so that the next
 // tile's loads are in flight while the current tile is multiplied.
 // Element (r, k) of the operand is P[r * rs + k * ks]; rows >= R and k >= K
@@ -58,10 +92,10 @@ constexpr int kLK = kBK + 8;      // LDS row pitch in elements (144 bytes: 16-by
 // wavefront store their transposed elements to 64 consecutive k of one row
 // (no LDS bank conflicts; lanes eight rows apart would all meet in one or
 // two banks, whatever the 16-byte-aligned pitch).
-template <int MODE, int ROWS>
+template <int MODE, int ROWS, int BK>
 struct TileLoad {
-    static constexpr int kChunks = ROWS * kBK / 8 / 256;
-    static_assert(kChunks >= 1 && ROWS * kBK / 8 % 256 == 0, "whole chunks per thread");
+    static constexpr int kChunks = ROWS * BK / 8 / 256, kKC = BK / 8, kLK = pitch(BK);
+    static_assert(kChunks >= 1 && ROWS * BK / 8 % 256 == 0, "whole chunks per thread");
     uint4 v[kChunks];
 
     __device__ __forceinline__ void load(const uint16_t *__restrict__ P, int64_t rs, int64_t ks, int r0, int R,
@@ -72,10 +106,10 @@ struct TileLoad {
             const int c = threadIdx.x + q * 256;
             v[q] = uint4{0u, 0u, 0u, 0u};
             if (MODE == LD_KC) {
-                const int gr = r0 + (c >> 3), gk = k0 + (c & 7) * 8;
+                const int gr = r0 + c / kKC, gk = k0 + c % kKC * 8;
                 if (gr < R && gk < K) v[q] = *(const uint4 *)(P + (int64_t)gr * rs + gk);
             } else {
-                const int gk = k0 + c % kBK, gr = r0 + (c / kBK) * 8;
+                const int gk = k0 + c % BK, gr = r0 + (c / BK) * 8;
                 if (gr < R && gk < K) v[q] = *(const uint4 *)(P + (int64_t)gk * ks + gr);
             }
         }
@@ -88,9 +122,9 @@ struct TileLoad {
         for (int q = 0; q < kChunks; ++q) {
             const int c = threadIdx.x + q * 256;
             if (MODE == LD_KC) {
-                *(uint4 *)(T + (c >> 3) * kLK + (c & 7) * 8) = v[q];
+                *(uint4 *)(T + c / kKC * kLK + c % kKC * 8) = v[q];
             } else {
-                const int kk = c % kBK, r8 = (c / kBK) * 8;
+                const int kk = c % BK, r8 = (c / BK) * 8;
                 const uint16_t *e = (const uint16_t *)&v[q];
 #pragma unroll
                 for (int t = 0; t < 8; ++t) T[(r8 + t) * kLK + kk] = e[t];
@@ -101,13 +135,13 @@ struct TileLoad {
 
 // The element-wise form (no unit stride or unaligned operands): straight
 // into LDS.
-template <int ROWS>
+template <int ROWS, int BK>
 __device__ __forceinline__ void stage_el(const uint16_t *__restrict__ P, int64_t rs, int64_t ks, int r0, int R,
                                          int k0, int K, uint16_t *__restrict__ T)
 {
-    for (int c = threadIdx.x; c < ROWS * kBK; c += 256) {
-        const int r = c / kBK, kk = c % kBK, gr = r0 + r, gk = k0 + kk;
-        T[r * kLK + kk] = (gr < R && gk < K) ? P[(int64_t)gr * rs + (int64_t)gk * ks] : (uint16_t)0;
+    for (int c = threadIdx.x; c < ROWS * BK; c += 256) {
+        const int r = c / BK, kk = c % BK, gr = r0 + r, gk = k0 + kk;
+        T[r * pitch(BK) + kk] = (gr < R && gk < K) ? P[(int64_t)gr * rs + (int64_t)gk * ks] : (uint16_t)0;
     }
 }
 
@@ -115,20 +149,19 @@ __device__ __forceinline__ void stage_el(const uint16_t *__restrict__ P, int64_t
 // A(i,k) = A[i*a_rs + k*a_cs], B(k,j) = B[k*b_rs + j*b_cs]; M, N, K
 // multiples of 16.  A workgroup (four wavefronts, 2 x 2) owns a block of
 // (32 TM) x (32 TN) entries of C, a wavefront (16 TM) x (16 TN): TM x TN
-// accumulators of the 16x16x32 MFMA.  Each 64-deep k step stages the
+// accumulators of the 16x16x32 MFMA.  Each BK-deep k step stages the
 // block's A rows and B columns in LDS, k contiguous, from coalesced 16-byte
 // loads issued during the previous step's products; lane l reads its
 // operands as one 16-byte LDS load each: A[l % 16][8 (l / 16) .. +7] and
-// B[8 (l / 16) .. +7][l % 16] of a 32-wide half step, and holds
-// C[4 (l / 16) .. +3][l % 16] of each tile.
-template <int EPI, int TM, int TN, int AM, int BMODE>
+// B[8 (l / 16) .. +7][l % 16] of a 32-wide half step (zero past K), and holds
+// C[4 (l / 16) .. +3][l % 16] of each tile.  Every block shape adds an entry's
+// products in the same order, 32 at a time, so results do not depend on it.
+template <int EPI, int TM, int TN, int BK, int AM, int BMODE>
 __global__ void __launch_bounds__(256)
 k_mfma_gemm(int M, int N, int K, const uint16_t *__restrict__ A, int64_t a_rs, int64_t a_cs,
-            const uint16_t *__restrict__ B, int64_t b_rs, int64_t b_cs, float *__restrict__ Cf,
-            uint16_t *__restrict__ Cb, int64_t ldc, const float *__restrict__ bias,
-            const uint16_t *__restrict__ act)
+            const uint16_t *__restrict__ B, int64_t b_rs, int64_t b_cs, EpiArgs x)
 {
-    constexpr int BM = 32 * TM, BN = 32 * TN;
+    constexpr int BM = 32 * TM, BN = 32 * TN, kLK = pitch(BK);
     constexpr bool PREFETCH = AM != LD_EL && BMODE != LD_EL;
     __shared__ __align__(16) uint16_t As[BM * kLK];
     __shared__ __align__(16) uint16_t Bs[BN * kLK];
@@ -143,27 +176,27 @@ k_mfma_gemm(int M, int N, int K, const uint16_t *__restrict__ A, int64_t a_rs, i
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
     // A tile: rows m (A(m, k) = A[m a_rs + k a_cs]); B tile: rows n (B(k, n) = B[n b_cs + k b_rs])
-    TileLoad<AM == LD_EL ? LD_KC : AM, BM> la;
-    TileLoad<BMODE == LD_EL ? LD_KC : BMODE, BN> lb;
+    TileLoad<AM == LD_EL ? LD_KC : AM, BM, BK> la;
+    TileLoad<BMODE == LD_EL ? LD_KC : BMODE, BN, BK> lb;
     if (PREFETCH) {
         la.load(A, a_rs, a_cs, m0, M, 0, K);
         lb.load(B, b_cs, b_rs, n0, N, 0, K);
     }
-    for (int k0 = 0; k0 < K; k0 += kBK) {
+    for (int k0 = 0; k0 < K; k0 += BK) {
         if (PREFETCH) {
             la.store(As);
             lb.store(Bs);
         } else {
-            stage_el<BM>(A, a_rs, a_cs, m0, M, k0, K, As);
-            stage_el<BN>(B, b_cs, b_rs, n0, N, k0, K, Bs);
+            stage_el<BM, BK>(A, a_rs, a_cs, m0, M, k0, K, As);
+            stage_el<BN, BK>(B, b_cs, b_rs, n0, N, k0, K, Bs);
         }
         __syncthreads();
-        if (PREFETCH && k0 + kBK < K) {
-            la.load(A, a_rs, a_cs, m0, M, k0 + kBK, K);
-            lb.load(B, b_cs, b_rs, n0, N, k0 + kBK, K);
+        if (PREFETCH && k0 + BK < K) {
+            la.load(A, a_rs, a_cs, m0, M, k0 + BK, K);
+            lb.load(B, b_cs, b_rs, n0, N, k0 + BK, K);
         }
 #pragma unroll
-        for (int h = 0; h < kBK / 32; ++h) {
+        for (int h = 0; h < BK / 32; ++h) {
             v8bf af[TM], bf[TN];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
@@ -179,74 +212,60 @@ k_mfma_gemm(int M, int N, int K, const uint16_t *__restrict__ A, int64_t a_rs, i
         }
         __syncthreads();
     }
+    double sq = 0.0;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+        const int col = n0 + wn * 16 * TN + j * 16 + r;
+        float cs = 0.f;  // this lane's part of the column's sum
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = n0 + wn * 16 * TN + j * 16 + r;
+        for (int i = 0; i < TM; ++i) {
             if (col >= N) continue;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int row = m0 + wm * 16 * TM + i * 16 + kq * 4 + e;
                 if (row >= M) continue;
-                const int64_t o = (int64_t)row * ldc + col;
+                const int64_t o = (int64_t)row * x.ldc + col;
                 float v = acc[i][j][e];
                 if (EPI == EPI_F32) {
-                    Cf[o] = v;
+                    x.Cf[o] = v;
                 } else if (EPI == EPI_BIAS_RELU) {
-                    v += bias[col];
-                    Cb[o] = f2bf(v > 0.f ? v : 0.f);
+                    v += x.bias[col];
+                    x.Cb[o] = f2bf(v > 0.f ? v : 0.f);
                 } else if (EPI == EPI_BIAS_F32) {
-                    Cf[o] = v + bias[col];
+                    x.Cf[o] = v + x.bias[col];
+                } else if (EPI == EPI_MASK) {
+                    v = bf2f(x.act[o]) > 0.f ? v : 0.f;
+                    x.Cb[o] = f2bf(v);
+                    cs += v;
+                } else if (EPI == EPI_MSE) {
+                    const float d = v + x.bias[col] - x.target[o];
+                    sq += (double)d * d;
+                    const float g = x.scale * d;
+                    x.Cb[o] = f2bf(g);
+                    cs += g;
                 } else {
-                    v = bf2f(act[o]) > 0.f ? v : 0.f;
-                    Cf[o] = v;
-                    Cb[o] = f2bf(v);
+                    float a = x.m1[o], b = x.m2[o];
+                    const float p = adam(x.Cf[o], v, a, b, x.step);
+                    x.m1[o] = a;
+                    x.m2[o] = b;
+                    x.Cf[o] = p;
+                    x.Cb[o] = f2bf(p);
                 }
             }
         }
+        if (EPI == EPI_MASK || EPI == EPI_MSE) {  // the column's rows of this wavefront, in a fixed order
+            cs += __shfl_xor(cs, 16);
+            cs += __shfl_xor(cs, 32);
+            if (kq == 0 && col < N) x.colsum[(int64_t)(m0 / BM * 2 + wm) * N + col] = cs;
+        }
+    }
+    if (EPI == EPI_MSE) uv::block_sum<1>(reinterpret_cast<double(&)[1]>(sq), x.sqerr + blockIdx.x, 1);
 }
 
 __global__ void __launch_bounds__(256) k_to_bf16(int64_t len, const float *__restrict__ x, uint16_t *__restrict__ y)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t < len) y[t] = f2bf(x[t]);
-}
-
-// Loss = mean((Y - T)^2) and dY = 2 (Y - T) / len, FP32 and BF16; one
-// workgroup, fixed summation order.
-__global__ void __launch_bounds__(256)
-k_mse(int64_t len, const float *__restrict__ Y, const float *__restrict__ T, float *__restrict__ dYf,
-      uint16_t *__restrict__ dYb, float *__restrict__ loss)
-{
-    __shared__ double s[256];
-    double acc = 0.0;
-    const float sc = 2.0f / (float)len;
-    for (int64_t t = threadIdx.x; t < len; t += 256) {
-        const float d = Y[t] - T[t];
-        acc += (double)d * d;
-        const float g = sc * d;
-        dYf[t] = g;
-        dYb[t] = f2bf(g);
-    }
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = (float)(s[0] / (double)len);
-}
-
-// db[j] = sum_i dZ[i][j]
-__global__ void __launch_bounds__(256)
-k_colsum(int M, int N, const float *__restrict__ dZ, float *__restrict__ db)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= N) return;
-    float s = 0.f;
-    for (int i = 0; i < M; ++i) s += dZ[(int64_t)i * N + j];
-    db[j] = s;
 }
 
 __device__ __forceinline__ uint64_t mix64(uint64_t x)
@@ -269,23 +288,46 @@ k_init(int64_t len, int fan_in, uint64_t seed, float *__restrict__ w, uint16_t *
     wb[t] = f2bf(v);
 }
 
-// Adam (bias-corrected), FP32 state; refreshes the BF16 copy.
-__global__ void __launch_bounds__(256)
-k_adam(int64_t len, float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m1,
-       float *__restrict__ m2, uint16_t *__restrict__ pb, float lr, float b1, float b2, float eps, float c1,
-       float c2)
+constexpr int kMaxLayers = 16;
+
+// The biases' part of a step, all layers in one launch: db from the
+// gradient's column sums (`rows` of them per layer, added in order), then
+// stored (gb) or, with `train`, Adam's step.  Workgroup 0 also adds the
+// workgroups' squared errors to the loss, on the device and (if given) in
+// host memory.
+struct BiasArgs {
+    int layers, train;
+    int width[kMaxLayers], rows[kMaxLayers];
+    const float *colsum[kMaxLayers];
+    float *gb[kMaxLayers], *b[kMaxLayers], *mb[kMaxLayers], *vb[kMaxLayers];
+    const double *sqerr;
+    int nsq;
+    double len;
+    float *loss, *loss_host;
+    AdamStep step;
+};
+
+__global__ void __launch_bounds__(256) k_bias(BiasArgs a)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= len) return;
-    const float gt = g[t];
-    const float a = b1 * m1[t] + (1.f - b1) * gt;
-    const float v = b2 * m2[t] + (1.f - b2) * gt * gt;
-    m1[t] = a;
-    m2[t] = v;
-    const float upd = lr * (a / c1) / (sqrtf(v / c2) + eps);
-    const float np = p[t] - upd;
-    p[t] = np;
-    if (pb) pb[t] = f2bf(np);
+    int j = blockIdx.x * 256 + threadIdx.x, l = 0;
+    while (l < a.layers && j >= a.width[l]) j -= a.width[l++];
+    if (l < a.layers) {
+        float g = 0.f;
+#pragma unroll 8
+        for (int q = 0; q < a.rows[l]; ++q) g += a.colsum[l][(int64_t)q * a.width[l] + j];
+        if (a.train) a.b[l][j] = adam(a.b[l][j], g, a.mb[l][j], a.vb[l][j], a.step);
+        else a.gb[l][j] = g;
+    }
+    if (blockIdx.x > 0) return;
+    double s[1] = {0.0};
+    for (int q = threadIdx.x; q < a.nsq; q += 256) s[0] += a.sqerr[q];
+    __shared__ double sum;
+    uv::block_sum<1>(s, &sum, 1);
+    if (threadIdx.x == 0) {
+        const float loss = (float)(sum / a.len);
+        *a.loss = loss;
+        if (a.loss_host) *a.loss_host = loss;
+    }
 }
 
 inline unsigned nb256(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -301,10 +343,13 @@ struct uv_mlp {
     std::vector<float *> W, b, gW, gb, mW, vW, mb, vb;
     std::vector<uint16_t *> Wb;      // BF16 weight copies
     std::vector<uint16_t *> act;     // BF16 activations a_0 (input) .. a_{L-1}
-    std::vector<float *> dzf;        // FP32 gradient w.r.t. pre-activations
-    std::vector<uint16_t *> dzb;     // BF16 copies
-    float *y = nullptr;              // FP32 output (max_batch x d[L])
+    std::vector<uint16_t *> dzb;     // BF16 gradient w.r.t. pre-activations
+    std::vector<float *> colsum;     // column sums of its FP32 values (2 per block row)
+    std::vector<int> rows;           // how many the last backward pass left
+    double *sqerr = nullptr;         // squared errors of the last layer's workgroups
+    int nsq = 0;
     float *loss = nullptr;
+    float *loss_host = nullptr;      // pinned
     int64_t step = 0;
 };
 
@@ -330,81 +375,143 @@ int load_mode(const uint16_t *P, int64_t rs, int64_t ks)
     return LD_EL;
 }
 
-template <int EPI, int TM, int TN, int AM>
+template <int EPI, int TM, int TN, int BK, int AM>
 void gemm_launch_b(int bmode, unsigned grid, hipStream_t st, int M, int N, int K, const uint16_t *A, int64_t a_rs,
-                   int64_t a_cs, const uint16_t *B, int64_t b_rs, int64_t b_cs, float *Cf, uint16_t *Cb, int64_t ldc,
-                   const float *bias, const uint16_t *act)
+                   int64_t a_cs, const uint16_t *B, int64_t b_rs, int64_t b_cs, const EpiArgs &x)
 {
-#define UV_GEMM_ARGS M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, Cf, Cb, ldc, bias, act
-    if (bmode == LD_KC) k_mfma_gemm<EPI, TM, TN, AM, LD_KC><<<grid, 256, 0, st>>>(UV_GEMM_ARGS);
-    else if (bmode == LD_MC) k_mfma_gemm<EPI, TM, TN, AM, LD_MC><<<grid, 256, 0, st>>>(UV_GEMM_ARGS);
-    else k_mfma_gemm<EPI, TM, TN, AM, LD_EL><<<grid, 256, 0, st>>>(UV_GEMM_ARGS);
+#define UV_GEMM_ARGS M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, x
+    if (bmode == LD_KC) k_mfma_gemm<EPI, TM, TN, BK, AM, LD_KC><<<grid, 256, 0, st>>>(UV_GEMM_ARGS);
+    else if (bmode == LD_MC) k_mfma_gemm<EPI, TM, TN, BK, AM, LD_MC><<<grid, 256, 0, st>>>(UV_GEMM_ARGS);
+    else k_mfma_gemm<EPI, TM, TN, BK, AM, LD_EL><<<grid, 256, 0, st>>>(UV_GEMM_ARGS);
 }
 
-template <int EPI, int TM, int TN>
+template <int EPI, int TM, int TN, int BK>
 void gemm_launch(hipStream_t st, int M, int N, int K, const uint16_t *A, int64_t a_rs, int64_t a_cs,
-                 const uint16_t *B, int64_t b_rs, int64_t b_cs, float *Cf, uint16_t *Cb, int64_t ldc,
-                 const float *bias, const uint16_t *act)
+                 const uint16_t *B, int64_t b_rs, int64_t b_cs, const EpiArgs &x)
 {
     const unsigned grid = (unsigned)(((M + 32 * TM - 1) / (32 * TM)) * ((N + 32 * TN - 1) / (32 * TN)));
     const int am = load_mode(A, a_rs, a_cs), bm = load_mode(B, b_cs, b_rs);
-    if (am == LD_KC) gemm_launch_b<EPI, TM, TN, LD_KC>(bm, grid, st, UV_GEMM_ARGS);
-    else if (am == LD_MC) gemm_launch_b<EPI, TM, TN, LD_MC>(bm, grid, st, UV_GEMM_ARGS);
-    else gemm_launch_b<EPI, TM, TN, LD_EL>(bm, grid, st, UV_GEMM_ARGS);
-#undef UV_GEMM_ARGS
+    if (am == LD_KC) gemm_launch_b<EPI, TM, TN, BK, LD_KC>(bm, grid, st, UV_GEMM_ARGS);
+    else if (am == LD_MC) gemm_launch_b<EPI, TM, TN, BK, LD_MC>(bm, grid, st, UV_GEMM_ARGS);
+    else gemm_launch_b<EPI, TM, TN, BK, LD_EL>(bm, grid, st, UV_GEMM_ARGS);
 }
 
-// 128 x 128 blocks when they still give every CU a block, else 64 x 64.
+// Rows (columns) of C a workgroup's block has, over 32: 128 x 128 blocks when
+// they still give every CU a block, 64 x 64 blocks likewise, else 32 x 32
+// with 256-deep steps: the network's own products (256 x 512 x 512) have 32
+// blocks of 64 x 64 and eight steps, each a trip to memory (8.6-12 us), and
+// 128 blocks of 32 x 32 with two steps (WHAT us).
+int gemm_block(int M, int N)
+{
+    if ((int64_t)((M + 127) / 128) * ((N + 127) / 128) >= 256) return 4;
+    return (int64_t)((M + 63) / 64) * ((N + 63) / 64) >= 256 ? 2 : 1;
+}
+
 template <int EPI>
 int gemm_any(hipStream_t st, int M, int N, int K, const uint16_t *A, int64_t a_rs, int64_t a_cs,
-             const uint16_t *B, int64_t b_rs, int64_t b_cs, float *Cf, uint16_t *Cb, int64_t ldc,
-             const float *bias, const uint16_t *act)
+             const uint16_t *B, int64_t b_rs, int64_t b_cs, const EpiArgs &x)
 {
-    const int64_t big = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-    if (big >= 256) gemm_launch<EPI, 4, 4>(st, M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, Cf, Cb, ldc, bias, act);
-    else gemm_launch<EPI, 2, 2>(st, M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, Cf, Cb, ldc, bias, act);
+    const int b = gemm_block(M, N);
+    if (b == 4) gemm_launch<EPI, 4, 4, kBK>(st, UV_GEMM_ARGS);
+    else if (b == 2) gemm_launch<EPI, 2, 2, kBK>(st, UV_GEMM_ARGS);
+    else gemm_launch<EPI, 1, 1, kDeep>(st, UV_GEMM_ARGS);
+#undef UV_GEMM_ARGS
     return hipGetLastError() == hipSuccess ? UV_OK : UV_EHIP;
 }
 
-template <int EPI>
-int mm(uv_mlp *h, int M, int N, int K, const uint16_t *A, int64_t a_rs, int64_t a_cs, const uint16_t *B,
-       int64_t b_rs, int64_t b_cs, float *Cf, uint16_t *Cb, int64_t ldc, const float *bias, const uint16_t *act)
-{
-    return gemm_any<EPI>(h->stream, M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, Cf, Cb, ldc, bias, act);
-}
-
-int forward(uv_mlp *h, int batch, const float *x)
+// The forward pass: the output into y, or (target given) straight into the
+// loss's gradient.
+int forward(uv_mlp *h, int batch, const float *x, float *y, const float *target)
 {
     k_to_bf16<<<nb256((int64_t)batch * h->d[0]), 256, 0, h->stream>>>((int64_t)batch * h->d[0], x, h->act[0]);
     int rc = UV_OK;
     for (int l = 0; l < h->L && rc == UV_OK; ++l) {
         const int K = h->d[l], N = h->d[l + 1];
-        if (l < h->L - 1)
-            rc = mm<EPI_BIAS_RELU>(h, batch, N, K, h->act[l], K, 1, h->Wb[l], N, 1, nullptr, h->act[l + 1], N,
-                                   h->b[l], nullptr);
-        else
-            rc = mm<EPI_BIAS_F32>(h, batch, N, K, h->act[l], K, 1, h->Wb[l], N, 1, h->y, nullptr, N, h->b[l],
-                                  nullptr);
+        EpiArgs e{};
+        e.ldc = N;
+        e.bias = h->b[l];
+#define UV_MM_FWD h->stream, batch, N, K, h->act[l], K, 1, h->Wb[l], N, 1, e
+        if (l < h->L - 1) {
+            e.Cb = h->act[l + 1];
+            rc = gemm_any<EPI_BIAS_RELU>(UV_MM_FWD);
+        } else if (!target) {
+            e.Cf = y;
+            rc = gemm_any<EPI_BIAS_F32>(UV_MM_FWD);
+        } else {
+            const int b = 32 * gemm_block(batch, N);
+            e.Cb = h->dzb[l];
+            e.target = target;
+            e.scale = 2.0f / (float)((int64_t)batch * N);
+            e.colsum = h->colsum[l];
+            e.sqerr = h->sqerr;
+            h->rows[l] = 2 * ((batch + b - 1) / b);
+            h->nsq = ((batch + b - 1) / b) * ((N + b - 1) / b);
+            rc = gemm_any<EPI_MSE>(UV_MM_FWD);
+        }
+#undef UV_MM_FWD
     }
     return rc;
 }
 
-int backward(uv_mlp *h, int batch, const float *t)
+// The backward pass from the gradient that forward() left.  step null:
+// the gradients into gW and gb; else Adam's step of every parameter.  A
+// layer's weights are updated only after the gradient has passed them.
+int backward(uv_mlp *h, int batch, const AdamStep *step, float *loss_host)
 {
     const int L = h->L;
-    const int64_t out_len = (int64_t)batch * h->d[L];
-    k_mse<<<1, 256, 0, h->stream>>>(out_len, h->y, t, h->dzf[L - 1], h->dzb[L - 1], h->loss);
     int rc = UV_OK;
     for (int l = L - 1; l >= 0 && rc == UV_OK; --l) {
         const int K = h->d[l], N = h->d[l + 1];
-        // dW_l = a_l' dz_l  (K x N), db_l = column sums of dz_l
-        rc = mm<EPI_F32>(h, K, N, batch, h->act[l], 1, K, h->dzb[l], N, 1, h->gW[l], nullptr, N, nullptr, nullptr);
-        k_colsum<<<nb256(N), 256, 0, h->stream>>>(batch, N, h->dzf[l], h->gb[l]);
-        if (l > 0 && rc == UV_OK)  // dz_{l-1} = (dz_l W_l') * [a_l > 0]
-            rc = mm<EPI_MASK>(h, batch, K, N, h->dzb[l], N, 1, h->Wb[l], 1, N, h->dzf[l - 1], h->dzb[l - 1], K,
-                              nullptr, h->act[l]);
+        EpiArgs e{};
+        if (l > 0) {  // dz_{l-1} = (dz_l W_l') * [a_l > 0]
+            const int b = 32 * gemm_block(batch, K);
+            e.ldc = K;
+            e.Cb = h->dzb[l - 1];
+            e.act = h->act[l];
+            e.colsum = h->colsum[l - 1];
+            h->rows[l - 1] = 2 * ((batch + b - 1) / b);
+            rc = gemm_any<EPI_MASK>(h->stream, batch, K, N, h->dzb[l], N, 1, h->Wb[l], 1, N, e);
+        }
+        // dW_l = a_l' dz_l  (K x N)
+        e = EpiArgs{};
+        e.ldc = N;
+        if (step) {
+            e.Cf = h->W[l];
+            e.Cb = h->Wb[l];
+            e.m1 = h->mW[l];
+            e.m2 = h->vW[l];
+            e.step = *step;
+            if (rc == UV_OK)
+                rc = gemm_any<EPI_ADAM>(h->stream, K, N, batch, h->act[l], 1, K, h->dzb[l], N, 1, e);
+        } else {
+            e.Cf = h->gW[l];
+            if (rc == UV_OK)
+                rc = gemm_any<EPI_F32>(h->stream, K, N, batch, h->act[l], 1, K, h->dzb[l], N, 1, e);
+        }
     }
-    return rc == UV_OK && hipGetLastError() == hipSuccess ? UV_OK : UV_EHIP;
+    if (rc != UV_OK) return rc;
+    BiasArgs a{};
+    a.layers = L;
+    a.train = step ? 1 : 0;
+    int64_t total = 0;
+    for (int l = 0; l < L; ++l) {
+        a.width[l] = h->d[l + 1];
+        a.rows[l] = h->rows[l];
+        a.colsum[l] = h->colsum[l];
+        a.gb[l] = h->gb[l];
+        a.b[l] = h->b[l];
+        a.mb[l] = h->mb[l];
+        a.vb[l] = h->vb[l];
+        total += h->d[l + 1];
+    }
+    a.sqerr = h->sqerr;
+    a.nsq = h->nsq;
+    a.len = (double)((int64_t)batch * h->d[L]);
+    a.loss = h->loss;
+    a.loss_host = loss_host;
+    if (step) a.step = *step;
+    k_bias<<<nb256(total), 256, 0, h->stream>>>(a);
+    return hipGetLastError() == hipSuccess ? UV_OK : UV_EHIP;
 }
 
 bool dims_ok(int batch, const uv_mlp *h) { return batch >= 16 && batch % 16 == 0 && batch <= h->max_batch; }
@@ -418,6 +525,7 @@ void mlp_destroy(uv_mlp *h)
     if (!h) return;
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     for (void *p : h->allocs) (void)hipFree(p);
+    if (h->loss_host) (void)hipHostFree(h->loss_host);
     delete h;
 }
 
@@ -436,7 +544,8 @@ int mlp_create(int32_t nlayers, const int32_t *dims, int32_t max_batch, uint64_t
     h->stream = (hipStream_t)stream;
     const int L = nlayers;
     h->W.resize(L); h->b.resize(L); h->gW.resize(L); h->gb.resize(L); h->mW.resize(L); h->vW.resize(L);
-    h->mb.resize(L); h->vb.resize(L); h->Wb.resize(L); h->act.resize(L); h->dzf.resize(L); h->dzb.resize(L);
+    h->mb.resize(L); h->vb.resize(L); h->Wb.resize(L); h->act.resize(L); h->dzb.resize(L);
+    h->colsum.resize(L); h->rows.resize(L);
     bool ok = true;
     for (int l = 0; l < L; ++l) {
         const size_t nw = (size_t)h->d[l] * h->d[l + 1], nbias = h->d[l + 1];
@@ -450,11 +559,15 @@ int mlp_create(int32_t nlayers, const int32_t *dims, int32_t max_batch, uint64_t
         ok &= (h->mb[l] = malloc_d<float>(h, nbias)) != nullptr;
         ok &= (h->vb[l] = malloc_d<float>(h, nbias)) != nullptr;
         ok &= (h->act[l] = malloc_d<uint16_t>(h, (size_t)max_batch * h->d[l])) != nullptr;
-        ok &= (h->dzf[l] = malloc_d<float>(h, (size_t)max_batch * h->d[l + 1])) != nullptr;
+        ok &= (h->colsum[l] = malloc_d<float>(h, (size_t)2 * ((max_batch + 31) / 32) * h->d[l + 1])) != nullptr;
         ok &= (h->dzb[l] = malloc_d<uint16_t>(h, (size_t)max_batch * h->d[l + 1])) != nullptr;
     }
-    ok &= (h->y = malloc_d<float>(h, (size_t)max_batch * h->d[L])) != nullptr;
+    ok &= (h->sqerr = malloc_d<double>(h, (size_t)((max_batch + 31) / 32) * ((h->d[L] + 31) / 32))) != nullptr;
     ok &= (h->loss = malloc_d<float>(h, 1)) != nullptr;
+    if (ok && uv::host_malloc(&h->loss_host, sizeof(float), hipHostMallocDefault) != hipSuccess) {
+        h->loss_host = nullptr;
+        ok = false;
+    }
     if (!ok) {
         mlp_destroy(h);
         return UV_ENOMEM;
@@ -511,10 +624,8 @@ int mlp_set_params(uv_mlp *h, const float *w, const float *b)
 int mlp_forward(uv_mlp *h, int32_t batch, const float *x_dev, float *y_dev)
 {
     if (!h || !x_dev || !y_dev || !dims_ok(batch, h)) return UV_EINVAL;
-    int rc = forward(h, batch, x_dev);
+    int rc = forward(h, batch, x_dev, y_dev, nullptr);
     if (rc != UV_OK) return rc;
-    if (hipMemcpyAsync(y_dev, h->y, 4 * (size_t)batch * h->d[h->L], hipMemcpyDeviceToDevice, h->stream) != hipSuccess)
-        return UV_EHIP;
     return hipStreamSynchronize(h->stream) == hipSuccess ? UV_OK : UV_EHIP;
 }
 
@@ -522,8 +633,8 @@ int mlp_gradients(uv_mlp *h, int32_t batch, const float *x_dev, const float *t_d
                   float *loss)
 {
     if (!h || !x_dev || !t_dev || !dims_ok(batch, h)) return UV_EINVAL;
-    int rc = forward(h, batch, x_dev);
-    if (rc == UV_OK) rc = backward(h, batch, t_dev);
+    int rc = forward(h, batch, x_dev, nullptr, t_dev);
+    if (rc == UV_OK) rc = backward(h, batch, nullptr, nullptr);
     if (rc != UV_OK) return rc;
     if (hipStreamSynchronize(h->stream) != hipSuccess) return UV_EHIP;
     size_t ow = 0, ob = 0;
@@ -541,24 +652,16 @@ int mlp_gradients(uv_mlp *h, int32_t batch, const float *x_dev, const float *t_d
 int mlp_train_step(uv_mlp *h, int32_t batch, const float *x_dev, const float *t_dev, float lr, float *loss)
 {
     if (!h || !x_dev || !t_dev || !dims_ok(batch, h) || !(lr > 0.f)) return UV_EINVAL;
-    int rc = forward(h, batch, x_dev);
-    if (rc == UV_OK) rc = backward(h, batch, t_dev);
+    const double step = (double)(h->step + 1);
+    const AdamStep a{lr, 0.9f, 0.999f, 1e-8f, 1.f - (float)std::pow((double)0.9f, step),
+                     1.f - (float)std::pow((double)0.999f, step)};
+    int rc = forward(h, batch, x_dev, nullptr, t_dev);
+    if (rc == UV_OK) rc = backward(h, batch, &a, loss ? h->loss_host : nullptr);
     if (rc != UV_OK) return rc;
     h->step += 1;
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.f - (float)std::pow((double)b1, (double)h->step);
-    const float c2 = 1.f - (float)std::pow((double)b2, (double)h->step);
-    for (int l = 0; l < h->L; ++l) {
-        const int64_t nw = (int64_t)h->d[l] * h->d[l + 1], nbias = h->d[l + 1];
-        k_adam<<<nb256(nw), 256, 0, h->stream>>>(nw, h->W[l], h->gW[l], h->mW[l], h->vW[l], h->Wb[l], lr, b1, b2, eps,
-                                                 c1, c2);
-        k_adam<<<nb256(nbias), 256, 0, h->stream>>>(nbias, h->b[l], h->gb[l], h->mb[l], h->vb[l], nullptr, lr, b1, b2,
-                                                    eps, c1, c2);
-    }
-    if (hipGetLastError() != hipSuccess) return UV_EHIP;
     if (loss) {
-        if (hipMemcpyAsync(loss, h->loss, 4, hipMemcpyDeviceToHost, h->stream) != hipSuccess) return UV_EHIP;
         if (hipStreamSynchronize(h->stream) != hipSuccess) return UV_EHIP;
+        *loss = *h->loss_host;
     }
     return UV_OK;
 }
@@ -567,8 +670,10 @@ int mlp_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t *A, int64_t a_
                   int64_t b_rs, int64_t b_cs, float *C, int64_t ldc, void *stream)
 {
     if (M < 16 || N < 16 || K < 16 || M % 16 || N % 16 || K % 16 || !A || !B || !C) return UV_EINVAL;
-    if (gemm_any<EPI_F32>((hipStream_t)stream, M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, C, nullptr, ldc, nullptr,
-                          nullptr) != UV_OK)
+    EpiArgs e{};
+    e.Cf = C;
+    e.ldc = ldc;
+    if (gemm_any<EPI_F32>((hipStream_t)stream, M, N, K, A, a_rs, a_cs, B, b_rs, b_cs, e) != UV_OK)
         return UV_EHIP;
     return hipStreamSynchronize((hipStream_t)stream) == hipSuccess ? UV_OK : UV_EHIP;
 }
