@@ -11,6 +11,11 @@
 // barrier -- for up to `budget` iterations, checking the FP64 residuals every
 // check_every iterations.  A finished instance (converged, max_iter or
 // numeric failure) is masked out of later launches.
+//
+// Within an instance rows and columns are renumbered by falling entry count
+// (row r of the device is row rmap[r] of the caller), so that the 64 segments
+// of a slice are about equally long; b, c and starts are permuted on the way
+// in, solutions on the way out.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,13 +34,15 @@ namespace {
 
 constexpr int kMaxThreads = 1024;
 constexpr int kLdsMax = 160 * 1024 - 1024;  // LDS of one gfx950 CU less the kernel's static LDS
+constexpr int kLdsFree = 160 * 1024 - 1040; // what a launch is really left with
 
 struct BInst {
     int m, n;
     int row_off, col_off;  // first global row / column of the instance
     int Lr, Lc;            // lanes per row / per column
     int status;
-    int ch_off;            // first 64-column slice of the instance (sliced column copy)
+    int ch_off;            // first 64-column slice of the instance
+    int rh_off;            // first 64-row slice
     long long iter, check_iter;
     double r_prim, r_dual, r_gap, kkt, pobj, dobj, res_ax_b;
     double bnorm2, cnorm2;
@@ -136,55 +143,222 @@ __device__ __forceinline__ void seg_sum2(int beg, int end, int lane, int L, cons
     s2 = a2;
 }
 
-// Sliced column copy (lanes per column 0): the columns of an instance are
-// cut into slices of 64; slice h stores entry t of its column l at
-// s0 + 64 t + l, so lane l's t-th load is one coalesced 64-wide access.  The
-// slice is as wide as its longest column; lane l reads only its cnt
-// entries, in column order, so the sum is that of one lane per column.
-template <int U, typename T, typename TV, typename TS>
-__device__ __forceinline__ T sell_sum(int s0, int w, int cnt, int lane, const lidx_t *__restrict__ idx,
-                                      const TV *__restrict__ val, const TS *vs)
+// Sliced copies (lanes per row 1, lanes per column 0 or 1): the segments of
+// an instance are cut into slices of 64, a lane each; entry t of the slice's
+// lane l is stored at s0 + 128 (t / 2) + 2 l + t % 2 (s0 the slice's first
+// slot), so a wavefront reads two entries a lane with one 4-byte load of their
+// 16-bit numbers and one 8- or 16-byte load of their values.  A slice is as
+// wide as its longest segment (rounded up to two); the slots past a segment's
+// end hold the value 0 and the number `pad` (the gathered vector's length:
+// the sweep's vectors in LDS have a zero there).  A lane adds its entries in
+// order: the sums of one lane walking its segment.
+struct Slices {
+    const int *ptr;               // first slot of every slice, all instances
+    const unsigned *idx;          // pairs of numbers
+    const void *val;              // pairs of sweep values
+    const double *val64;          // pairs of FP64 values
+};
+
+constexpr int kPairs = 4;  // pairs in flight per lane
+
+template <typename T>
+struct Two {
+    typedef T type __attribute__((ext_vector_type(2)));
+};
+
+// One pass over an instance's slices by wavefronts, the next four pairs (of
+// this slice or the wavefront's next one) and the next slice's operands in
+// flight while four are multiplied.  Op: load(segment) reads what the update
+// needs besides the sum, put(segment, sum) makes it.
+// What bounds it: instructions (a wavefront's takes four cycles of its SIMD):
+// lanes walking their segments spent dozens an entry on bounds, clamps and
+// 64-bit addresses, here an entry costs half of two loads, two to unpack and
+// scale its number, an LDS read and a multiply-add.  An iteration of a 5000 x
+// 10000 LP with 6e4 entries alone, mixed (FP64), checks included: 44 (52) ->
+// 21 (28) us; streaming the entries 64 wide through LDS instead measured 46
+// (56) us.
+template <typename T, typename Op>
+__device__ __forceinline__ void sell_pass(int wv, int nwv, int lane, int nseg, const int *__restrict__ sp,
+                                          const unsigned *__restrict__ idx,
+                                          const typename Two<T>::type *__restrict__ val, const T *vs, Op op)
 {
-    T acc = 0;
-    for (int t0 = 0; t0 < w; t0 += U) {
-        int j[U];
-        TV v[U];
+    const int nch = (nseg + 63) >> 6;
+    int h = wv;
+    if (h >= nch) return;
+    unsigned j[kPairs], jn[kPairs];
+    typename Two<T>::type v[kPairs], vn[kPairs];
+    int base = sp[h] >> 1, np = (sp[h + 1] >> 1) - base;  // in pairs, 64 lanes each
+    np >>= 6;
+    op.load(min(h * 64 + lane, nseg - 1));
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = s0 + (t0 + u) * 64 + lane;
-            j[u] = 0;
-            v[u] = (TV)0;
-            if (t0 + u < cnt) {
-                j[u] = idx[k];
-                v[u] = val[k];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (t0 + u < cnt) acc += (T)v[u] * (T)vs[j[u]];
+    for (int q = 0; q < kPairs; ++q) {
+        const int o = base + (q << 6) + lane;
+        j[q] = idx[o];
+        v[q] = val[o];
     }
-    return acc;
+    for (;;) {
+        const int hn = h + nwv, hh = min(hn, nch - 1);
+        const int nbase = sp[hh] >> 1, nnp = ((sp[hh + 1] >> 1) - nbase) >> 6;
+        Op nop = op;
+        nop.load(min(hh * 64 + lane, nseg - 1));
+        T acc = 0;
+        for (int p = 0;; p += kPairs) {
+            const bool more = p + kPairs < np;
+            const int from = more ? base + ((p + kPairs) << 6) : nbase;
+#pragma unroll
+            for (int q = 0; q < kPairs; ++q) {
+                const int o = from + (q << 6) + lane;
+                jn[q] = idx[o];
+                vn[q] = val[o];
+            }
+#pragma unroll
+            for (int q = 0; q < kPairs; ++q)
+                if (p + q < np) {
+                    acc += v[q].x * vs[j[q] & 0xffffu];
+                    acc += v[q].y * vs[j[q] >> 16];
+                }
+#pragma unroll
+            for (int q = 0; q < kPairs; ++q) {
+                j[q] = jn[q];
+                v[q] = vn[q];
+            }
+            if (!more) break;
+        }
+        if (h * 64 + lane < nseg) op.put(h * 64 + lane, acc);
+        if (hn >= nch) return;
+        h = hn;
+        op = nop;
+        base = nbase;
+        np = nnp;
+    }
 }
 
-// Fills the sliced column copy from the compressed columns, one workgroup
-// per instance (slots past a column's end hold zeros).
+// FP64 sums of one slice's segments over one or two vectors (a check's
+// products), lane l reading only its cnt entries.
+template <int V, typename S>
+__device__ __forceinline__ void sell_check(int s0, int cnt, int w, int lane, const unsigned *__restrict__ idx,
+                                           const double *__restrict__ val64, const S *v1, const S *v2, double &q1,
+                                           double &q2)
+{
+    double a1 = 0.0, a2 = 0.0;
+#pragma unroll 4
+    for (int t = 0; t < w; t += 2) {
+        const int o = ((s0 + 64 * t) >> 1) + lane;
+        const unsigned j = idx[o];
+        const typename Two<double>::type v = ((const typename Two<double>::type *)val64)[o];
+        if (t < cnt) {
+            a1 += v.x * (double)v1[j & 0xffffu];
+            if (V == 2) a2 += v.x * (double)v2[j & 0xffffu];
+        }
+        if (t + 1 < cnt) {
+            a1 += v.y * (double)v1[j >> 16];
+            if (V == 2) a2 += v.y * (double)v2[j >> 16];
+        }
+    }
+    q1 = a1;
+    q2 = a2;
+}
+
+// The updates of a sliced sweep pass; pointers are the instance's own.
+template <typename T>
+struct SellCol {
+    T *xs, *zi;
+    const T *ci;
+    double *__restrict__ delta;
+    const lidx_t *__restrict__ cnt;
+    double mu, inv_mu;
+    double d;
+    T zj, cj;
+    int k;
+    __device__ __forceinline__ void load(int j)
+    {
+        d = delta[j];
+        zj = zi[j];
+        cj = ci[j];
+        k = cnt[j];
+    }
+    __device__ __forceinline__ void put(int j, T atu)
+    {
+        const T dm = (T)(d * inv_mu);
+        const T p = (T)k * xs[j] + atu;
+        const T xn = (p + zj + dm - cj * (T)inv_mu) / (T)(1 + k);
+        const T v = xn - dm;
+        const T zn = v > (T)0 ? v : (T)0;
+        xs[j] = xn;
+        zi[j] = zn;
+        delta[j] = d + mu * ((double)zn - (double)xn);
+    }
+};
+
+template <typename T>
+struct SellRow {
+    T *us;
+    const T *__restrict__ fu, *__restrict__ b;
+    double *__restrict__ lam;
+    double mu, inv_mu;
+    double l0;
+    T fi, bi;
+    __device__ __forceinline__ void load(int i)
+    {
+        fi = fu[i];
+        bi = b[i];
+        l0 = lam[i];
+    }
+    __device__ __forceinline__ void put(int i, T q)
+    {
+        const T e = fi * (bi - q);
+        const double li = l0 - mu * (double)e;
+        lam[i] = li;
+        us[i] = (T)((double)e - li * inv_mu);
+    }
+};
+
+// Fills a sliced copy from the compressed segments (rows or columns), one
+// workgroup per instance.
 __global__ void __launch_bounds__(256)
-k_sell_fill(const BInst *__restrict__ inst, const int *__restrict__ cp, const int *__restrict__ ri,
-            const double *__restrict__ vc, const int *__restrict__ sptr, lidx_t *__restrict__ sidx,
+k_sell_fill(const BInst *__restrict__ inst, int rows, const int *__restrict__ ptr, const int *__restrict__ idx,
+            const double *__restrict__ val, const int *__restrict__ sptr, lidx_t *__restrict__ sidx,
             double *__restrict__ sval)
 {
     const BInst &I = inst[blockIdx.x];
-    const int nch = (I.n + 63) >> 6;
+    const int nseg = rows ? I.m : I.n, off = rows ? I.row_off : I.col_off, sub = rows ? I.col_off : I.row_off;
+    const int pad = rows ? I.n : I.m, h0 = rows ? I.rh_off : I.ch_off;
+    const int nch = (nseg + 63) >> 6;
     for (int p = threadIdx.x; p < nch * 64; p += 256) {
-        const int h = p >> 6, l = p & 63, j = p;  // local column j = 64 h + l
-        const int s0 = sptr[I.ch_off + h], w = (sptr[I.ch_off + h + 1] - s0) >> 6;
-        const int beg = j < I.n ? cp[I.col_off + j] : 0;
-        const int len = j < I.n ? cp[I.col_off + j + 1] - beg : 0;
+        const int h = p >> 6, l = p & 63;
+        const int s0 = sptr[h0 + h], w = (sptr[h0 + h + 1] - s0) >> 6;
+        const int beg = p < nseg ? ptr[off + p] : 0, len = p < nseg ? ptr[off + p + 1] - beg : 0;
         for (int t = 0; t < w; ++t) {
-            const int k = s0 + t * 64 + l;
-            sidx[k] = t < len ? (lidx_t)(ri[beg + t] - I.row_off) : (lidx_t)0;
-            sval[k] = t < len ? vc[beg + t] : 0.0;
+            const int k = s0 + 128 * (t >> 1) + 2 * l + (t & 1);
+            sidx[k] = t < len ? (lidx_t)(idx[beg + t] - sub) : (lidx_t)pad;
+            sval[k] = t < len ? val[beg + t] : 0.0;
         }
+    }
+}
+
+// Entries of each column.
+__global__ void __launch_bounds__(256) k_col_entries(int n, const int *__restrict__ cp, lidx_t *__restrict__ cnt)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j < n) cnt[j] = (lidx_t)(cp[j + 1] - cp[j]);
+}
+
+// One instance's vectors in the caller's numbering as FP64, straight into
+// (pinned host) memory: x, z, delta (n each), lambda (m).
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_batch_out(int c0, int n, int r0, int m, const T *__restrict__ x, const T *__restrict__ z,
+            const double *__restrict__ delta, const double *__restrict__ lam, const int *__restrict__ cmap,
+            const int *__restrict__ rmap, double *__restrict__ out)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t < n) {
+        const int j = cmap[c0 + t];
+        out[j] = (double)x[c0 + t];
+        out[n + j] = (double)z[c0 + t];
+        out[2 * n + j] = delta[c0 + t];
+    } else if (t < n + m) {
+        out[3 * n + rmap[r0 + t - n]] = lam[r0 + t - n];
     }
 }
 
@@ -234,8 +408,8 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
         const T *__restrict__ b, const double *__restrict__ b64, const T *__restrict__ fu,
         const T *__restrict__ c, const double *__restrict__ c64, T *__restrict__ x, T *__restrict__ z,
         T *__restrict__ u, double *__restrict__ lam, double *__restrict__ delta, double mu, double inv_mu,
-        double eps, int check_every, long long max_iter, const int *__restrict__ sptr,
-        const lidx_t *__restrict__ sidx, const T *__restrict__ sval, const double *__restrict__ sval64, int gated)
+        double eps, int check_every, long long max_iter, Slices srow, Slices scol,
+        const lidx_t *__restrict__ ccnt, int sliced, int gated)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     T *xs = reinterpret_cast<T *>(lds_raw);
@@ -253,23 +427,29 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
         const int m = I->m, n = I->n, r0 = I->row_off, c0 = I->col_off;
         const int Lr = I->Lr, Lc = I->Lc;
         long long it = I->iter;
-        T *us = xs + n;
+        T *us = xs + n + sliced;  // the sliced copies' padding reads a zero after each vector
         // ZC: z and c of the instance in LDS as well (after u), so the column
         // pass streams only delta and the entries
-        T *zi = ZC ? us + m : z + c0;
-        const T *ci_ = ZC ? us + m + n : c + c0;
+        T *zi = ZC ? us + m + sliced : z + c0;
+        const T *ci_ = ZC ? zi + n : c + c0;
         for (int j = tid; j < n; j += nthr) xs[j] = x[c0 + j];
         for (int i = tid; i < m; i += nthr) us[i] = u[r0 + i];
         if (ZC)
             for (int j = tid; j < n; j += nthr) {
                 zi[j] = z[c0 + j];
-                us[m + n + j] = c[c0 + j];
+                zi[n + j] = c[c0 + j];
             }
+        if (sliced && tid == 0) {
+            xs[n] = (T)0;
+            us[m] = (T)0;
+        }
         __syncthreads();
-        // lane groups per column (Lc > 0) or the sliced copy (Lc == 0: a wavefront per 64 columns)
+        // lane groups per segment, or the sliced copies (a wavefront per 64)
+        const bool sc = sliced && Lc <= 1, sr = sliced && Lr == 1;
         const int Lc1 = Lc > 0 ? Lc : 1;
         const int gc = tid / Lc1, lc = tid % Lc1, Gc = nthr / Lc1;
-        const int wv = tid >> 6, lane64 = tid & 63, nwv = nthr >> 6, nch = (n + 63) >> 6, ch0 = I->ch_off;
+        const int wv = tid >> 6, lane64 = tid & 63, nwv = nthr >> 6, nch = (n + 63) >> 6;
+        const int *sp_c = scol.ptr + I->ch_off, *sp_r = srow.ptr + I->rh_off;
         const int gr = tid / Lr, lr = tid % Lr, Gr = nthr / Lr;
         int stop = 0;
         for (int k = 0; k < budget && !stop; ++k) {
@@ -284,22 +464,9 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                 zi[j] = zn;
                 delta[c0 + j] = d + mu * ((double)zn - (double)xn);
             };
-            if (Lc == 0) {
-                for (int h = wv; h < nch; h += nwv) {
-                    const int j = (h << 6) + lane64;
-                    T zj = 0, cj = 0;
-                    double d = 0.0;
-                    int cnt = 0;
-                    if (j < n) {  // the update's own loads, in flight with the sum's
-                        d = delta[c0 + j];
-                        zj = zi[j];
-                        cj = ci_[j];
-                        cnt = cp[c0 + j + 1] - cp[c0 + j];
-                    }
-                    const int s0 = sptr[ch0 + h], w = (sptr[ch0 + h + 1] - s0) >> 6;
-                    const T atu = sell_sum<4, T>(s0, w, cnt, lane64, sidx, sval, us);
-                    if (j < n) col_update(j, cnt, atu, d, zj, cj);
-                }
+            if (sc) {
+                sell_pass<T>(wv, nwv, lane64, n, sp_c, scol.idx, (const typename Two<T>::type *)scol.val, us,
+                             SellCol<T>{xs, zi, ci_, delta + c0, ccnt + c0, mu, inv_mu, 0.0, 0, 0, 0});
             } else
             for (int jb = 0; jb < n; jb += Gc) {
                 const int j = jb + gc;
@@ -326,6 +493,30 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
             // A x, so the check adds no second row product.
             const bool chk = (it + 1) % check_every == 0 || (max_iter > 0 && it + 1 >= max_iter);
             double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+            auto row_check = [&](int i, double qz, double qx, double li) {
+                const double bd = b64[r0 + i];
+                a[0] += (qz - bd) * (qz - bd);
+                a[1] += bd * li;
+                a[2] += (qx - bd) * (qx - bd);
+            };
+            if (sr && !chk) {
+                sell_pass<T>(wv, nwv, lane64, m, sp_r, srow.idx, (const typename Two<T>::type *)srow.val, xs,
+                             SellRow<T>{us, fu + r0, b + r0, lam + r0, mu, inv_mu, 0.0, 0, 0});
+            } else if (sr) {
+                for (int h = wv; h < (m + 63) >> 6; h += nwv) {
+                    const int i = (h << 6) + lane64, s0 = sp_r[h], w = (sp_r[h + 1] - s0) >> 6;
+                    const int cnt = i < m ? rp[r0 + i + 1] - rp[r0 + i] : 0;
+                    double qz, qx;
+                    sell_check<2>(s0, cnt, w, lane64, srow.idx, srow.val64, (const T *)zi, (const T *)xs, qz, qx);
+                    if (i < m) {
+                        const T e = fu[r0 + i] * (b[r0 + i] - (T)qx);
+                        const double li = lam[r0 + i] - mu * (double)e;
+                        lam[r0 + i] = li;
+                        us[i] = (T)((double)e - li * inv_mu);
+                        row_check(i, qz, qx, li);
+                    }
+                }
+            } else
             for (int ib = 0; ib < m; ib += Gr) {
                 const int i = ib + gr;
                 T q = 0, fi = 0, bi = 0;
@@ -352,12 +543,7 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                     const double li = l0 - mu * (double)e;
                     lam[r0 + i] = li;
                     us[i] = (T)((double)e - li * inv_mu);
-                    if (chk) {
-                        const double bd = b64[r0 + i];
-                        a[0] += (qz - bd) * (qz - bd);
-                        a[1] += bd * li;
-                        a[2] += (qx - bd) * (qx - bd);
-                    }
+                    if (chk) row_check(i, qz, qx, li);
                 }
             }
             __syncthreads();
@@ -382,12 +568,13 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                     a[3] += r * r;
                     a[4] += c64[c0 + j] * (double)zi[j];
                 };
-                if (Lc == 0) {
+                if (sc) {
                     for (int h = wv; h < nch; h += nwv) {
-                        const int j = (h << 6) + lane64;
-                        const int cnt = j < n ? cp[c0 + j + 1] - cp[c0 + j] : 0;
-                        const int s0 = sptr[ch0 + h], w = (sptr[ch0 + h + 1] - s0) >> 6;
-                        const double atl = sell_sum<4, double>(s0, w, cnt, lane64, sidx, sval64, lam + r0);
+                        const int j = (h << 6) + lane64, s0 = sp_c[h], w = (sp_c[h + 1] - s0) >> 6;
+                        const int cnt = j < n ? ccnt[c0 + j] : 0;
+                        double atl, none;
+                        sell_check<1>(s0, cnt, w, lane64, scol.idx, scol.val64, (const double *)lam + r0,
+                                      (const double *)lam + r0, atl, none);
                         if (j < n) col_res(j, atl);
                     }
                 } else
@@ -447,11 +634,12 @@ struct uv_batch {
     std::vector<void *> allocs;
     int *rp = nullptr, *ci = nullptr, *cp = nullptr, *ri = nullptr;
     lidx_t *cl = nullptr, *rl = nullptr;  // instance-local column (CSR) and row (CSC) numbers
-    // sliced column copy: slice offsets (64 slots per unit of width), local rows, values
-    int *sptr = nullptr;
-    lidx_t *sidx = nullptr;
-    double *sval64 = nullptr;
-    void *sval = nullptr;
+    Slices srow{}, scol{};       // sliced copies of the rows and columns
+    lidx_t *ccnt = nullptr;      // entries of each column
+    bool sliced = false;         // their padding's zeros fit LDS with x and u
+    std::vector<int> rmap, cmap; // instance-local numbers of the caller for the device's rows and columns
+    int *rmap_d = nullptr, *cmap_d = nullptr;
+    double *out = nullptr;       // pinned: one instance's solution
     double *va64 = nullptr, *vc64 = nullptr, *b64 = nullptr, *c64 = nullptr;
     void *va = nullptr, *vc = nullptr, *b = nullptr, *c = nullptr, *fu = nullptr;
     void *x = nullptr, *z = nullptr, *u = nullptr;
@@ -461,13 +649,16 @@ struct uv_batch {
     int *order = nullptr, *queue = nullptr, *budget = nullptr;
     int *budget_host = nullptr;  // pinned
     std::vector<int> order_host;
-    int threads = 256;
-    int xu_bytes = 0;   // x and u of the largest instance (16-byte aligned)
-    int zc_bytes = 0;   // x, u, z and c of the largest instance
+    int threads = 1024;
+    int xu_bytes = 0;   // x and u of the largest instance with the sliced copies' zeros (16-byte aligned)
+    int zc_bytes = 0;   // x, u, z and c likewise
     bool zc = false;    // z and c staged in LDS too
     int lds_bytes = 0;  // dynamic LDS per workgroup of the launch
     int grid = 0;
-    int tiles[2 * 4] = {2, 1, 2, 1, 2, 1, 2, 1};  // (Lr, Lc) per size bucket
+    // (Lr, Lc) per size bucket: the sliced copies, but four lanes a row while
+    // an instance has fewer rows than the workgroup a quarter of its threads
+    // (m < 128: 3.6 against 4.2 us an iteration, m < 512: 6.9 against 8.1)
+    int tiles[2 * 4] = {4, 1, 4, 1, 1, 1, 1, 1};
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
@@ -497,7 +688,7 @@ int batch_launch(uv_batch *h, hipStream_t st, const int *order, int nq)
     h->inst, order, nq, h->queue, h->budget, h->rp, h->cl, (const T *)h->va, h->va64, h->cp, h->rl,          \
         (const T *)h->vc, h->vc64, (const T *)h->b, h->b64, (const T *)h->fu, (const T *)h->c, h->c64,      \
         (T *)h->x, (T *)h->z, (T *)h->u, h->lam, h->delta, mu, im, o.eps_kkt, o.check_every, (long long)o.max_iter, \
-        h->sptr, h->sidx, (const T *)h->sval, h->sval64, o.full_checks == 0 ? 1 : 0
+        h->srow, h->scol, h->ccnt, h->sliced ? 1 : 0, o.full_checks == 0 ? 1 : 0
     const int grid = std::max(1, std::min(h->grid, nq));
     if (o.precision == UV_MIXED)
         h->zc ? k_batch<float, true><<<grid, h->threads, h->lds_bytes, st>>>(UV_BATCH_ARGS(float))
@@ -509,42 +700,41 @@ int batch_launch(uv_batch *h, hipStream_t st, const int *order, int nq)
     return hipGetLastError() == hipSuccess ? UV_OK : UV_EHIP;
 }
 
-// The sliced column copy (lanes per column 0): slices of 64 columns, each as
-// wide as its longest column, filled on the device from the compressed
-// columns.  Needs the instances' col_off / n on the host and cp on the
-// device; sets every instance's ch_off.
-int build_slices(uv_batch *h)
+// A sliced copy of the rows or columns: slices of 64 segments, each as wide
+// as its longest (counts: the segments' entries), filled on the device from
+// the compressed form.  Sets every instance's rh_off or ch_off on the host.
+int build_slices(uv_batch *h, bool rows, const std::vector<int> &counts)
 {
     const bool mixed = h->o.precision == UV_MIXED;
-    std::vector<int> cph((size_t)h->N + 1);
-    UV_BTRY(hipMemcpy(cph.data(), h->cp, sizeof(int) * cph.size(), hipMemcpyDeviceToHost));
     std::vector<int> sptr(1, 0);
     int64_t slots = 0;
     for (int i = 0; i < h->count; ++i) {
         BInst &I = h->inst_host[i];
-        I.ch_off = (int)sptr.size() - 1;
-        for (int j0 = 0; j0 < I.n; j0 += 64) {
+        const int off = rows ? I.row_off : I.col_off, nseg = rows ? I.m : I.n;
+        (rows ? I.rh_off : I.ch_off) = (int)sptr.size() - 1;
+        for (int j0 = 0; j0 < nseg; j0 += 64) {
             int w = 0;
-            for (int j = j0; j < std::min(j0 + 64, I.n); ++j)
-                w = std::max(w, cph[(size_t)I.col_off + j + 1] - cph[(size_t)I.col_off + j]);
-            slots += 64 * (int64_t)w;
-            if (slots >= ((int64_t)1 << 31)) return UV_ETOOBIG;
+            for (int j = j0; j < std::min(j0 + 64, nseg); ++j) w = std::max(w, counts[(size_t)off + j]);
+            slots += 64 * (int64_t)((w + 1) / 2 * 2);
+            if (slots + 1024 >= ((int64_t)1 << 31)) return UV_ETOOBIG;
             sptr.push_back((int)slots);
         }
     }
-    h->sptr = balloc<int>(h, sptr.size());
-    h->sidx = balloc<lidx_t>(h, slots);
-    h->sval64 = balloc<double>(h, slots);
-    h->sval = mixed ? (void *)balloc<float>(h, slots) : (void *)h->sval64;
-    if (!h->sptr || !h->sidx || !h->sval64 || !h->sval) return UV_ENOMEM;
-    UV_BTRY(hipMemcpy(h->sptr, sptr.data(), sizeof(int) * sptr.size(), hipMemcpyHostToDevice));
-    UV_BTRY(hipMemcpy(h->inst, h->inst_host, sizeof(BInst) * h->count, hipMemcpyHostToDevice));
+    const size_t room = (size_t)slots + 128 * kPairs;  // a pass reads whole groups of pairs
+    int *dptr = balloc<int>(h, sptr.size());
+    unsigned *idx = balloc<unsigned>(h, room / 2);
+    double *val64 = balloc<double>(h, room);
+    float *val = mixed ? balloc<float>(h, room) : nullptr;
+    if (!dptr || !idx || !val64 || (mixed && !val)) return UV_ENOMEM;
     hipStream_t st = h->stream;
-    k_sell_fill<<<h->count, 256, 0, st>>>(h->inst, h->cp, h->ri, h->vc64, h->sptr, h->sidx, h->sval64);
-    if (mixed && slots > 0)
-        k_narrow<float><<<blocks_for(slots, kWG), kWG, 0, st>>>(slots, h->sval64, (float *)h->sval);
+    UV_BTRY(hipMemcpy(dptr, sptr.data(), sizeof(int) * sptr.size(), hipMemcpyHostToDevice));
+    UV_BTRY(hipMemcpy(h->inst, h->inst_host, sizeof(BInst) * h->count, hipMemcpyHostToDevice));
+    k_sell_fill<<<h->count, 256, 0, st>>>(h->inst, rows ? 1 : 0, rows ? h->rp : h->cp, rows ? h->ci : h->ri,
+                                          rows ? h->va64 : h->vc64, dptr, (lidx_t *)idx, val64);
+    if (mixed && slots > 0) k_narrow<float><<<blocks_for(slots, kWG), kWG, 0, st>>>(slots, val64, val);
     UV_BTRY(hipGetLastError());
     UV_BTRY(hipStreamSynchronize(st));
+    (rows ? h->srow : h->scol) = Slices{dptr, idx, mixed ? (const void *)val : (const void *)val64, val64};
     return UV_OK;
 }
 
@@ -567,8 +757,10 @@ int occupancy_of(uv_batch *h, int *per_cu)
     // LDS above the default 64 KiB per workgroup has to be asked for
     if (h->lds_bytes > 64 * 1024 &&
         hipFuncSetAttribute((const void *)k_batch<T, ZC>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            h->lds_bytes) != hipSuccess)
+                            h->lds_bytes) != hipSuccess) {
+        (void)hipGetLastError();  // the refusal is reported here, not by the next launch's check
         return UV_ETOOBIG;
+    }
     UV_BTRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_batch<T, ZC>, h->threads, h->lds_bytes));
     return UV_OK;
 }
@@ -577,7 +769,7 @@ int occupancy_of(uv_batch *h, int *per_cu)
 // every instance's fit: ZC) and the persistent grid the occupancy allows.
 int occupancy_grid(uv_batch *h)
 {
-    h->zc = h->zc_bytes <= kLdsMax;
+    h->zc = h->zc_bytes <= kLdsFree;
     h->lds_bytes = h->zc ? h->zc_bytes : h->xu_bytes;
     int dev = 0, cus = 0;
     UV_BTRY(hipGetDevice(&dev));
@@ -618,6 +810,7 @@ void batch_destroy(uv_batch *h)
     if (h->graph) (void)hipGraphDestroy(h->graph);
     for (void *p : h->allocs) (void)hipFree(p);
     if (h->inst_host) (void)hipHostFree(h->inst_host);
+    if (h->out) (void)hipHostFree(h->out);
     if (h->budget_host) (void)hipHostFree(h->budget_host);
     if (h->cap) (void)hipStreamDestroy(h->cap);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
@@ -638,7 +831,7 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
         return UV_EINVAL;
     const size_t ts = o.precision == UV_MIXED ? 4 : 8;
     int64_t M = 0, N = 0, NNZ = 0;
-    size_t lds = 0, lds_zc = 0;
+    size_t lds = 0, lds_zc = 0, largest = 0;
     for (int i = 0; i < count; ++i) {
         const uv_csr &a = A[i];
         if (!b[i] || !c[i] || !a.row_ptr || a.m < 1 || a.n < 1 || a.nnz < 0) return UV_EINVAL;
@@ -657,6 +850,7 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
         NNZ += a.nnz;
         lds = std::max(lds, (size_t)(a.m + a.n) * ts);
         lds_zc = std::max(lds_zc, (size_t)(a.m + 3 * (size_t)a.n) * ts);
+        largest = std::max(largest, 3 * (size_t)a.n + a.m);
     }
     if (NNZ >= ((int64_t)1 << 31) || M >= ((int64_t)1 << 31) || N >= ((int64_t)1 << 31)) return UV_ETOOBIG;
     if (lds > (size_t)kLdsMax) return UV_ETOOBIG;  // x and u of every instance must fit in LDS
@@ -668,6 +862,11 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
     h->N = (int)N;
     h->nnz = (int)NNZ;
     h->o = o;
+    h->sliced = (lds + 2 * ts + 15) / 16 * 16 <= (size_t)kLdsFree;
+    if (h->sliced) {
+        lds += 2 * ts;
+        lds_zc += 2 * ts;
+    }
     h->xu_bytes = (int)((lds + 15) / 16 * 16);
     h->zc_bytes = (int)std::min<size_t>((lds_zc + 15) / 16 * 16, (size_t)1 << 30);
     h->lds_bytes = h->xu_bytes;
@@ -716,14 +915,22 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
     h->inst = balloc<BInst>(h, count);
     h->order = balloc<int>(h, count);
     h->queue = balloc<int>(h, 1);
+    h->rmap_d = balloc<int>(h, M);
+    h->cmap_d = balloc<int>(h, N);
+    h->ccnt = balloc<lidx_t>(h, N);
     h->budget = balloc<int>(h, 1);
     int *cnt = balloc<int>(h, N);
     int *bsum = balloc<int>(h, blocks_for(N, 4 * kWG));
     for (void *p : {(void *)h->rp, (void *)h->ci, (void *)h->va64, (void *)h->cp, (void *)h->ri, (void *)h->vc64, (void *)h->cl, (void *)h->rl,
                     (void *)h->b64, (void *)h->c64, (void *)h->lam, (void *)h->delta, (void *)h->scratch, h->x,
                     h->z, h->u, h->fu, h->va, h->vc, h->b, h->c, (void *)h->inst, (void *)h->order,
-                    (void *)h->queue, (void *)h->budget, (void *)cnt, (void *)bsum})
+                    (void *)h->queue, (void *)h->budget, (void *)h->rmap_d, (void *)h->cmap_d, (void *)h->ccnt,
+                    (void *)cnt, (void *)bsum})
         if (!p) return fail(UV_ENOMEM);
+    if (uv::host_malloc(&h->out, sizeof(double) * largest, hipHostMallocDefault) != hipSuccess) {
+        h->out = nullptr;
+        return fail(UV_ENOMEM);
+    }
     if (uv::host_malloc(&h->inst_host, sizeof(BInst) * count, hipHostMallocDefault) != hipSuccess) {
         h->inst_host = nullptr;
         return fail(UV_ENOMEM);
@@ -733,10 +940,23 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
         return fail(UV_ENOMEM);
     }
 
-    // Pack the block-diagonal matrix with global indices.
+    // Pack the block-diagonal matrix with global indices, rows and columns
+    // of an instance in falling order of their entries (stable).
+    std::vector<int> rcnt(M), ccnt(N);
+    h->rmap.resize(M);
+    h->cmap.resize(N);
     {
-        std::vector<int> rp32(M + 1), ci32(NNZ);
+        std::vector<int> rp32(M + 1), ci32(NNZ), inv, cc0, slot;
         std::vector<double> va(NNZ), bb(M), cc(N);
+        // map[slot] = original number, by falling count: a counting sort
+        auto by_count = [&](int len, auto count, int *map) {
+            int top = 0;
+            for (int q = 0; q < len; ++q) top = std::max(top, count(q));
+            slot.assign((size_t)top + 2, 0);
+            for (int q = 0; q < len; ++q) slot[(size_t)(top - count(q)) + 1] += 1;
+            for (int q = 0; q <= top; ++q) slot[(size_t)q + 1] += slot[q];
+            for (int q = 0; q < len; ++q) map[slot[(size_t)(top - count(q))]++] = q;
+        };
         int64_t ro = 0, co = 0, ko = 0;
         for (int i = 0; i < count; ++i) {
             const uv_csr &a = A[i];
@@ -748,13 +968,27 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
             I.col_off = (int)co;
             I.status = UV_STATUS_RUNNING;
             I.check_iter = -1;
-            for (int r = 0; r < a.m; ++r) rp32[ro + r] = (int)(ko + a.row_ptr[r]);
-            for (int64_t k = 0; k < a.nnz; ++k) {
-                ci32[ko + k] = (int)(co + a.col_idx[k]);
-                va[ko + k] = a.val[k];
+            int *rm = h->rmap.data() + ro, *cm = h->cmap.data() + co;
+            by_count(a.m, [&](int r) { return (int)(a.row_ptr[r + 1] - a.row_ptr[r]); }, rm);
+            cc0.assign(a.n, 0);
+            for (int64_t k = 0; k < a.nnz; ++k) cc0[a.col_idx[k]] += 1;
+            by_count(a.n, [&](int j) { return cc0[j]; }, cm);
+            inv.resize(a.n);
+            for (int j = 0; j < a.n; ++j) inv[cm[j]] = j;
+            for (int j = 0; j < a.n; ++j) {
+                ccnt[co + j] = cc0[cm[j]];
+                cc[co + j] = c[i][cm[j]];
             }
-            std::memcpy(&bb[ro], b[i], sizeof(double) * a.m);
-            std::memcpy(&cc[co], c[i], sizeof(double) * a.n);
+            int64_t w = ko;
+            for (int r = 0; r < a.m; ++r) {
+                rp32[ro + r] = (int)w;
+                rcnt[ro + r] = (int)(a.row_ptr[rm[r] + 1] - a.row_ptr[rm[r]]);
+                bb[ro + r] = b[i][rm[r]];
+                for (int64_t k = a.row_ptr[rm[r]]; k < a.row_ptr[rm[r] + 1]; ++k, ++w) {
+                    ci32[w] = (int)(co + inv[a.col_idx[k]]);
+                    va[w] = a.val[k];
+                }
+            }
             ro += a.m;
             co += a.n;
             ko += a.nnz;
@@ -767,6 +1001,9 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
         }
         if (hipMemcpy(h->b64, bb.data(), sizeof(double) * M, hipMemcpyHostToDevice) != hipSuccess) return fail(UV_EHIP);
         if (hipMemcpy(h->c64, cc.data(), sizeof(double) * N, hipMemcpyHostToDevice) != hipSuccess) return fail(UV_EHIP);
+        if (hipMemcpy(h->rmap_d, h->rmap.data(), sizeof(int) * M, hipMemcpyHostToDevice) != hipSuccess ||
+            hipMemcpy(h->cmap_d, h->cmap.data(), sizeof(int) * N, hipMemcpyHostToDevice) != hipSuccess)
+            return fail(UV_EHIP);
     }
     // Longest instances first.
     h->order_host.resize(count);
@@ -802,7 +1039,9 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
     if (hipMemcpyAsync(h->inst_host, h->inst, sizeof(BInst) * count, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return fail(UV_EHIP);
-    if ((rc = build_slices(h)) != UV_OK) return fail(rc);
+    k_col_entries<<<blocks_for(N, 256), 256, 0, st>>>((int)N, h->cp, h->ccnt);
+    if ((rc = build_slices(h, true, rcnt)) != UV_OK) return fail(rc);
+    if ((rc = build_slices(h, false, ccnt)) != UV_OK) return fail(rc);
     if ((rc = apply_tiles(h)) != UV_OK) return fail(rc);
     if ((rc = occupancy_grid(h)) != UV_OK) return fail(rc);
     if ((rc = rebuild_graph(h)) != UV_OK) return fail(rc);
@@ -884,25 +1123,20 @@ int batch_solution(uv_batch *h, int32_t i, double *x, double *z, double *lambda,
     if (!h || i < 0 || i >= h->count) return UV_EINVAL;
     const BInst &I = h->inst_host[i];
     hipStream_t st = h->stream;
-    const bool mixed = h->o.precision == UV_MIXED;
-    auto get_t = [&](double *dst, void *src, int off, int len) -> int {
-        if (!dst) return UV_OK;
-        const void *from;
-        if (mixed) {
-            k_widen<float><<<blocks_for(len, kWG), kWG, 0, st>>>(len, (const float *)src + off, h->scratch);
-            from = h->scratch;
-        } else {
-            from = (const double *)src + off;
-        }
-        if (hipMemcpyAsync(dst, from, 8 * (size_t)len, hipMemcpyDeviceToHost, st) != hipSuccess) return UV_EHIP;
-        return hipStreamSynchronize(st) == hipSuccess ? UV_OK : UV_EHIP;
-    };
-    int rc;
-    if ((rc = get_t(x, h->x, I.col_off, I.n)) != UV_OK) return rc;
-    if ((rc = get_t(z, h->z, I.col_off, I.n)) != UV_OK) return rc;
-    if (lambda) UV_BTRY(hipMemcpyAsync(lambda, h->lam + I.row_off, 8 * (size_t)I.m, hipMemcpyDeviceToHost, st));
-    if (delta) UV_BTRY(hipMemcpyAsync(delta, h->delta + I.col_off, 8 * (size_t)I.n, hipMemcpyDeviceToHost, st));
+    // one launch writes the four vectors to pinned memory, one wait
+    const unsigned g = blocks_for((int64_t)I.n + I.m, 256);
+#define UV_OUT_ARGS(T)                                                                                     \
+    I.col_off, I.n, I.row_off, I.m, (const T *)h->x, (const T *)h->z, h->delta, h->lam, h->cmap_d, h->rmap_d, h->out
+    if (h->o.precision == UV_MIXED) k_batch_out<float><<<g, 256, 0, st>>>(UV_OUT_ARGS(float));
+    else k_batch_out<double><<<g, 256, 0, st>>>(UV_OUT_ARGS(double));
+#undef UV_OUT_ARGS
+    UV_BTRY(hipGetLastError());
     UV_BTRY(hipStreamSynchronize(st));
+    const size_t n = (size_t)I.n;
+    if (x) std::memcpy(x, h->out, 8 * n);
+    if (z) std::memcpy(z, h->out + n, 8 * n);
+    if (delta) std::memcpy(delta, h->out + 2 * n, 8 * n);
+    if (lambda) std::memcpy(lambda, h->out + 3 * n, 8 * (size_t)I.m);
     return UV_OK;
 }
 
@@ -914,10 +1148,18 @@ int batch_set_start(uv_batch *h, int32_t i, const double *x, const double *z, co
     hipStream_t st = h->stream;
     const bool mixed = h->o.precision == UV_MIXED;
     const size_t ts = mixed ? 4 : 8;
+    // in the device's numbering, by way of the pinned buffer
+    auto order = [&](const double *src, const std::vector<int> &map, int off, int len) -> const double * {
+        if (!src) return nullptr;
+        for (int q = 0; q < len; ++q) h->out[q] = src[map[(size_t)off + q]];
+        return h->out;
+    };
     auto put_t = [&](void *dst, const double *src, int off, int len) -> int {
         char *d = (char *)dst + ts * off;
         if (!src) return hipMemsetAsync(d, 0, ts * len, st) == hipSuccess ? UV_OK : UV_EHIP;
-        if (!mixed) return hipMemcpyAsync(d, src, 8 * (size_t)len, hipMemcpyHostToDevice, st) == hipSuccess
+        src = order(src, h->cmap, I.col_off, I.n);
+        if (!mixed) return hipMemcpyAsync(d, src, 8 * (size_t)len, hipMemcpyHostToDevice, st) == hipSuccess &&
+                                   hipStreamSynchronize(st) == hipSuccess
                                ? UV_OK : UV_EHIP;
         if (hipMemcpyAsync(h->scratch, src, 8 * (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess)
             return UV_EHIP;
@@ -927,9 +1169,14 @@ int batch_set_start(uv_batch *h, int32_t i, const double *x, const double *z, co
     int rc;
     if ((rc = put_t(h->x, x, I.col_off, I.n)) != UV_OK) return rc;
     if ((rc = put_t(h->z, z, I.col_off, I.n)) != UV_OK) return rc;
-    if (delta) UV_BTRY(hipMemcpyAsync(h->delta + I.col_off, delta, 8 * (size_t)I.n, hipMemcpyHostToDevice, st));
-    else UV_BTRY(hipMemsetAsync(h->delta + I.col_off, 0, 8 * (size_t)I.n, st));
-    if (lambda) UV_BTRY(hipMemcpyAsync(h->lam + I.row_off, lambda, 8 * (size_t)I.m, hipMemcpyHostToDevice, st));
+    if (delta) {
+        UV_BTRY(hipMemcpyAsync(h->delta + I.col_off, order(delta, h->cmap, I.col_off, I.n), 8 * (size_t)I.n,
+                               hipMemcpyHostToDevice, st));
+        UV_BTRY(hipStreamSynchronize(st));
+    } else UV_BTRY(hipMemsetAsync(h->delta + I.col_off, 0, 8 * (size_t)I.n, st));
+    if (lambda)
+        UV_BTRY(hipMemcpyAsync(h->lam + I.row_off, order(lambda, h->rmap, I.row_off, I.m), 8 * (size_t)I.m,
+                               hipMemcpyHostToDevice, st));
     else UV_BTRY(hipMemsetAsync(h->lam + I.row_off, 0, 8 * (size_t)I.m, st));
     const double im = 1.0 / h->o.mu;
     if (mixed) k_batch_start_u<float><<<blocks_for(I.m, 256), 256, 0, st>>>(I.row_off, I.m, h->lam, (float *)h->u, im);
