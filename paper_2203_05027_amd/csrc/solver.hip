@@ -813,32 +813,35 @@ k_row_gate(int nrow, const double *__restrict__ prow, double eps, double eps_abs
 // 16-bit row and column numbers (m, n < 65536).
 struct ResLayout {
     int d, l, x, z, u, vc, va, cp, rp, ri, ci;
-    int bytes;
+    int need;   // bytes of what it holds: the problem is resident up to kResLdsMax of them
+    int bytes;  // with a zero after lambda, x, z and u (the padding of k_resident_reg)
 };
 
 constexpr int kResThreads = 1024;
-constexpr int kResLdsMax = 160 * 1024 - 2048;  // a CU's LDS less the kernel's static slots
+constexpr int kResLdsMax = 160 * 1024 - 2048;  // a CU's LDS less the kernel's static slots and the zeros (64 bytes)
 
 template <typename T>
 ResLayout resident_layout(int m, int n, int nnz)
 {
     ResLayout L{};
-    size_t o = 0;
-    auto put = [&](int &field, size_t bytes) {
+    size_t o = 0, need = 0;
+    auto put = [&](int &field, size_t bytes, size_t zero = 0) {
         field = (int)o;
-        o = (o + bytes + 15) / 16 * 16;
+        o = (o + bytes + zero + 15) / 16 * 16;
+        need += (bytes + 15) / 16 * 16;
     };
     put(L.d, 8 * (size_t)n);
-    put(L.l, 8 * (size_t)m);
-    put(L.x, sizeof(T) * (size_t)n);
-    put(L.z, sizeof(T) * (size_t)n);
-    put(L.u, sizeof(T) * (size_t)m);
+    put(L.l, 8 * (size_t)m, 8);
+    put(L.x, sizeof(T) * (size_t)n, sizeof(T));
+    put(L.z, sizeof(T) * (size_t)n, sizeof(T));
+    put(L.u, sizeof(T) * (size_t)m, sizeof(T));
     put(L.vc, sizeof(T) * (size_t)nnz);
     put(L.va, sizeof(T) * (size_t)nnz);
     put(L.cp, 4 * ((size_t)n + 1));
     put(L.rp, 4 * ((size_t)m + 1));
     put(L.ri, 2 * (size_t)nnz);
     put(L.ci, 2 * (size_t)nnz);
+    L.need = need > (size_t)INT32_MAX ? INT32_MAX : (int)need;
     L.bytes = o > (size_t)INT32_MAX ? INT32_MAX : (int)o;
     return L;
 }
@@ -889,77 +892,77 @@ __device__ __forceinline__ void lds_dot2(int k0, int k1, int lane, int L, const 
     s2 = uv::lane_sum<double>(b0 + b1, L);
 }
 
-// The FP64 residual check of the resident kernel (every thread calls it):
-// per-thread sums over its rows and columns, then a fixed-order workgroup
-// reduction; thread 0 gets the sums and maxima of finish_check in sv.
-template <typename T>
-__device__ __forceinline__ void res_check(int m, int n, int Lr, int Lc, const int *rps, const unsigned short *cis,
-                                          const int *cps, const unsigned short *ris, const double *cva,
-                                          const double *cvc, const T *xs, const T *zs, const double *ds,
-                                          const double *ls, const double *__restrict__ b64,
-                                          const double *__restrict__ c64, double (*red)[kResThreads / 64],
-                                          double (&sv)[10], const double *gate, int *s_skip)
+// The row sums of the FP64 residual check: row i with (A z)_i and (A x)_i.
+__device__ __forceinline__ void check_row(double (&v)[10], double qz, double qx, double bi, double li)
+{
+    const double rz = qz - bi, rx = qx - bi;
+    v[0] += rz * rz;
+    v[1] += bi * li;
+    v[2] += rx * rx;
+    v[6] = fmax(v[6], fabs(rz));
+    v[7] = fmax(v[7], fabs(qz));
+}
+
+// The column sums: column j with (A'lambda)_j.
+__device__ __forceinline__ void check_col(double (&v)[10], double a, double cj, double dj, double zj, double xj)
+{
+    const double r = a + cj - dj;
+    v[3] += r * r;
+    v[4] += cj * zj;
+    v[5] += cj * xj;
+    v[8] = fmax(v[8], fabs(r));
+    v[9] = fmax(v[9], fabs(a));
+}
+
+// The FP64 residual check of the resident kernels (every thread calls it):
+// rows(v) and cols(v) add a thread's rows and columns (check_row, check_col),
+// then a fixed-order workgroup reduction that leaves the sums and maxima of
+// finish_check in sv (in LDS, written by the first wavefront).  With gate the
+// primal half comes first: when the primal part of the test fails with finite
+// sums the check cannot stop the run, its column half is skipped and the
+// function returns true (sv left as it was).
+template <typename Rows, typename Cols>
+__device__ __forceinline__ bool res_check(Rows rows, Cols cols, double (*red)[kResThreads / 64], double (&sv)[10],
+                                          const double (&nrm)[4], bool gate, double eps, double eps_abs, int crit,
+                                          int *s_skip)
 {
     constexpr int NT = kResThreads;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const int gc = tid / Lc, lc = tid % Lc, gr = tid / Lr, lr = tid % Lr;
     double v[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int i = gr; i < m; i += NT / Lr) {
-        double qz, qx;
-        lds_dot2(rps[i], rps[i + 1], lr, Lr, cis, cva, zs, xs, qz, qx);
-        if (lr == 0) {
-            const double bi = b64[i], rz = qz - bi, rx = qx - bi;
-            v[0] += rz * rz;
-            v[1] += bi * ls[i];
-            v[2] += rx * rx;
-            v[6] = fmax(v[6], fabs(rz));
-            v[7] = fmax(v[7], fabs(qz));
-        }
-    }
+    rows(v);
     if (gate) {
-        // primal half first (gate: eps, eps_abs, crit, ||b||^2, ||b||_inf):
-        // the row values folded as below, bit for bit; when the primal part
-        // of the test fails with finite sums the check cannot stop the run
-        // and its column half is skipped (*s_skip = 1, sv left unset)
-        double g[5] = {uv::wave_fold0<false>(v[0]), uv::wave_fold0<false>(v[1]), uv::wave_fold0<false>(v[2]),
-                       uv::wave_fold0<true>(v[6]), uv::wave_fold0<true>(v[7])};
-        if (lane == 0)
-#pragma unroll
-            for (int k = 0; k < 5; ++k) red[k][w] = g[k];
+        // only what the criterion compares is folded, as below, bit for bit;
+        // the other sums are finite where no thread's part reaches 1e300,
+        // and a larger or non-finite part leaves the decision to the whole
+        // check
+        const bool small = v[0] < 1e300 && fabs(v[1]) < 1e300 && v[2] < 1e300 && v[6] < 1e300 && v[7] < 1e300;
+        const bool all = __all(small);
+        const double g0 = crit == 1 ? uv::wave_fold0<true>(v[6]) : uv::wave_fold0<false>(crit == 2 ? v[2] : v[0]);
+        const double g1 = crit == 1 ? uv::wave_fold0<true>(v[7]) : 0.0;
+        if (lane == 0) {
+            red[0][w] = g0;
+            red[1][w] = g1;
+            red[2][w] = all ? 0.0 : 1.0;
+        }
         __syncthreads();
         if (w == 0) {
             double a = 0.0;
-            if (lane < 5) {
+            if (lane < 3) {
                 a = red[lane][0];
-                for (int q = 1; q < NT / 64; ++q) a = lane < 3 ? a + red[lane][q] : fmax(a, red[lane][q]);
+                for (int q = 1; q < NT / 64; ++q)
+                    a = crit != 1 || lane == 2 ? a + red[lane][q] : fmax(a, red[lane][q]);
             }
-            double f[5];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) f[k] = __shfl(a, k, 64);
-            if (lane == 0) {
-                const int crit = (int)gate[2];
-                bool fails;
-                if (crit == 1) fails = !(f[3] <= gate[1] + gate[0] * fmax(f[4], gate[4]));
-                else if (crit == 2) fails = !(sqrt(f[2]) < gate[1]);
-                else fails = !(sqrt(f[0]) / (1.0 + sqrt(gate[3])) <= gate[0]);
-                *s_skip = fails && isfinite(f[0]) && isfinite(f[1]) && isfinite(f[2]) && isfinite(f[3]) &&
-                          isfinite(f[4]);
-            }
+            const double f0 = uv::read_lane(a, 0), f1 = uv::read_lane(a, 1), bad = uv::read_lane(a, 2);
+            bool fails;
+            if (crit == 1) fails = !(f0 <= eps_abs + eps * fmax(f1, nrm[2]));
+            else if (crit == 2) fails = !(sqrt(f0) < eps_abs);
+            else fails = !(sqrt(f0) / (1.0 + sqrt(nrm[0])) <= eps);
+            if (lane == 0) *s_skip = fails && bad == 0.0;
         }
         __syncthreads();
-        if (*s_skip) return;
+        if (__builtin_amdgcn_readfirstlane(*s_skip)) return true;
     }
-    for (int j = gc; j < n; j += NT / Lc) {
-        const double a = lds_dot<double>(cps[j], cps[j + 1], lc, Lc, ris, cvc, ls);
-        if (lc == 0) {
-            const double cj = c64[j], r = a + cj - ds[j];
-            v[3] += r * r;
-            v[4] += cj * (double)zs[j];
-            v[5] += cj * (double)xs[j];
-            v[8] = fmax(v[8], fabs(r));
-            v[9] = fmax(v[9], fabs(a));
-        }
-    }
+    cols(v);
 #pragma unroll
     for (int k = 0; k < 6; ++k) v[k] = uv::wave_fold0<false>(v[k]);
 #pragma unroll
@@ -968,15 +971,14 @@ __device__ __forceinline__ void res_check(int m, int n, int Lr, int Lc, const in
 #pragma unroll
         for (int k = 0; k < 10; ++k) red[k][w] = v[k];
     __syncthreads();
-    if (w == 0) {  // lane k < 10 of the first wavefront folds value k over the wavefronts, in order
-        double a = 0.0;
-        if (lane < 10) {
-            a = red[lane][0];
-            for (int q = 1; q < NT / 64; ++q) a = lane < 6 ? a + red[lane][q] : fmax(a, red[lane][q]);
-        }
-#pragma unroll
-        for (int k = 0; k < 10; ++k) sv[k] = __shfl(a, k, 64);
+    if (w == 0 && lane < 10) {  // lane k of the first wavefront folds value k over the wavefronts, in order
+        double a = red[lane][0];
+        for (int q = 1; q < NT / 64; ++q) a = lane < 6 ? a + red[lane][q] : fmax(a, red[lane][q]);
+        sv[lane] = a;
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return false;
 }
 
 // Up to `iters` iterations of a small orthant problem in one workgroup: the
@@ -1004,7 +1006,7 @@ k_resident(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp
            HistRing hist, int gated)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ double red[10][kResThreads / 64];
+    __shared__ double red[10][kResThreads / 64], sv[10], nrm[4];
     __shared__ int stop, skip;
     if (!eval_only && st->done) return;
     constexpr int NT = kResThreads;
@@ -1032,22 +1034,38 @@ k_resident(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp
         cis[k] = (unsigned short)ci[k];
         vas[k] = va[k];
     }
-    if (tid == 0) stop = 0;
+    if (tid == 0) {
+        stop = 0;
+        nrm[0] = st->bnorm2;
+        nrm[1] = st->cnorm2;
+        nrm[2] = st->binf;
+        nrm[3] = st->cinf;
+    }
     __syncthreads();
     const long long it0 = st->iter;
-    const double nrm[4] = {st->bnorm2, st->cnorm2, st->binf, st->cinf};
-    const double gate[5] = {eps, eps_abs, (double)crit, nrm[0], nrm[2]};
     // FP64 values of A for the checks: the staged ones in FP64, global ones in the mixed form
     const double *cva = sizeof(T) == sizeof(double) ? (const double *)vas : va64;
     const double *cvc = sizeof(T) == sizeof(double) ? (const double *)vcs : vc64;
+    const int gc = tid / Lc, lc = tid % Lc, gr = tid / Lr, lr = tid % Lr;
+    auto rows = [&](double (&v)[10]) {
+        for (int i = gr; i < m; i += NT / Lr) {
+            double qz, qx;
+            lds_dot2(rps[i], rps[i + 1], lr, Lr, cis, cva, zs, xs, qz, qx);
+            if (lr == 0) check_row(v, qz, qx, b64[i], ls[i]);
+        }
+    };
+    auto cols = [&](double (&v)[10]) {
+        for (int j = gc; j < n; j += NT / Lc) {
+            const double a = lds_dot<double>(cps[j], cps[j + 1], lc, Lc, ris, cvc, ls);
+            if (lc == 0) check_col(v, a, c64[j], ds[j], (double)zs[j], (double)xs[j]);
+        }
+    };
     if (eval_only) {
-        double sv[10];
-        res_check<T>(m, n, Lr, Lc, rps, cis, cps, ris, cva, cvc, xs, zs, ds, ls, b64, c64, red, sv, nullptr, &skip);
+        res_check(rows, cols, red, sv, nrm, false, eps, eps_abs, crit, &skip);
         if (tid == 0) finish_check(sv, nrm, it0, eps, eps_abs, eps_gap, crit, 0, st, hist);
         return;
     }
     const double inv_mu = 1.0 / mu;
-    const int gc = tid / Lc, lc = tid % Lc, gr = tid / Lr, lr = tid % Lr;
     long long done = 0;
     int to_check = check_every - (int)(it0 % check_every);  // iterations left to the next check
     for (long long t = 0; t < iters; ++t) {
@@ -1080,21 +1098,324 @@ k_resident(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp
         const long long itn = it0 + done;
         if (--to_check != 0) continue;
         to_check = check_every;
-        double sv[10];
-        res_check<T>(m, n, Lr, Lc, rps, cis, cps, ris, cva, cvc, xs, zs, ds, ls, b64, c64, red, sv,
-                     gated ? gate : nullptr, &skip);
-        if (gated && skip) continue;
+        if (res_check(rows, cols, red, sv, nrm, gated != 0, eps, eps_abs, crit, &skip)) continue;
         if (tid == 0) {
             st->iter = itn;
             stop = finish_check(sv, nrm, itn, eps, eps_abs, eps_gap, crit, 1, st, hist) ? 1 : 0;
         }
         __syncthreads();
-        if (stop) break;
+        if (__builtin_amdgcn_readfirstlane(stop)) break;
     }
     for (int j = tid; j < n; j += NT) {
         x[j] = xs[j];
         z[j] = zs[j];
         delta[j] = ds[j];
+    }
+    for (int i = tid; i < m; i += NT) {
+        u[i] = us[i];
+        lam[i] = ls[i];
+    }
+    if (tid == 0) st->iter = it0 + done;
+}
+
+// The rest of a lane's share of a row or column of k_resident_reg: the first
+// R entries in registers, as LDS addresses in the gathered vector and values
+// (past the end: the zero after that vector, and 0), the others (from k on)
+// read from LDS.  steps is the wavefront's most entries a lane has (R + 1:
+// more than R).
+template <typename T, int R>
+struct ResSeg {
+    int i;         // row or column (-1: none)
+    int cnt;       // its entries
+    int steps;
+    int k, k1;     // this lane's entries past the registers
+    unsigned off[R];
+    T val[R];
+};
+
+// LDS addresses as the data-share instructions take them.
+__device__ __forceinline__ unsigned lds_at(const void *p)
+{
+    return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+
+template <typename T>
+__device__ __forceinline__ T lds_get(unsigned at)
+{
+    return *(const __attribute__((address_space(3))) T *)(uintptr_t)at;
+}
+
+// v (the same in every lane) as a value the compiler knows nothing about: what is derived from it in
+// a loop is computed there, not kept in a register (and spilled) from before.
+__device__ __forceinline__ int fresh(int v)
+{
+    asm volatile("" : "+v"(v));
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Lays a segment out: row or column i (-1: none) of ptr, this lane `lane` of
+// L, the gathered vector vec with its zero after len numbers.
+template <typename T, int R>
+__device__ __forceinline__ void seg_load(ResSeg<T, R> &s, int i, int lane, int L, const int *ptr,
+                                         const unsigned short *idx, const T *val, const T *vec, int len)
+{
+    const int k0 = i >= 0 ? ptr[i] : 0, k1 = i >= 0 ? ptr[i + 1] : 0;
+    s.i = i;
+    s.cnt = k1 - k0;
+    s.k1 = k1;
+    s.k = k0 + lane + R * L;
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const int k = k0 + lane + e * L;
+        const bool in = k < k1;
+        s.off[e] = lds_at(vec) + (unsigned)sizeof(T) * (in ? (unsigned)idx[k] : (unsigned)len);
+        s.val[e] = in ? val[k] : (T)0;
+        // the address is one register, not the sum the compiler could rebuild it from
+        asm volatile("" : "+v"(s.off[e]));
+    }
+    s.steps = 0;
+#pragma unroll
+    for (int e = 0; e <= R; ++e) s.steps += __ballot(k0 + lane + e * L < k1) != 0 ? 1 : 0;
+}
+
+// The products of the first E register entries with the vector(s) `shift`
+// bytes past the laid-out one, in T.
+template <int E, typename T, int R>
+__device__ __forceinline__ T seg_regs(const ResSeg<T, R> &s, int shift)
+{
+    T g[E], a[4] = {(T)0, (T)0, (T)0, (T)0};
+#pragma unroll
+    for (int e = 0; e < E; ++e) g[e] = lds_get<T>(s.off[e] + shift);
+#pragma unroll
+    for (int e = 0; e < E; ++e) a[e & 3] += s.val[e] * g[e];
+    return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// The segment's whole product, in every lane of its group, with the vector
+// vec that lies `shift` bytes past the laid-out one.
+template <typename T, int R>
+__device__ __forceinline__ T seg_sum(const ResSeg<T, R> &s, int shift, int L, const unsigned short *idx,
+                                     const T *val, const T *vec)
+{
+    const int steps = fresh(s.steps), lanes = fresh(L);
+    T a;
+    if (steps <= 2) a = seg_regs<2>(s, shift);
+    else if (steps <= 4) a = seg_regs<4>(s, shift);
+    else if (steps <= 6) a = seg_regs<(R < 6 ? R : 6)>(s, shift);
+    else a = seg_regs<R>(s, shift);
+    if (steps > R)
+        for (int k = s.k; k < s.k1; k += lanes) a += val[k] * vec[idx[k]];
+    return uv::lane_sum<T>(a, lanes);
+}
+
+// num / den for a whole number 1 <= den <= 2^16 with r = 1 / den rounded:
+// the product corrected by its exact remainder is the rounded quotient (a
+// quotient by such a den is no closer than 2^-18 of its last place to the
+// middle of two numbers, and the correction is within 2^-22 of it), away
+// from the ends of the type's range, where the division itself is taken.
+template <typename T>
+__device__ __forceinline__ T div_whole(T num, T den, T r)
+{
+    const T q = num * r;
+    T out;
+    bool mid;
+    if constexpr (sizeof(T) == 8) {
+        mid = ((unsigned)(__builtin_bit_cast(unsigned long long, q) >> 52) & 0x7ff) - 100u < 1900u;
+        out = __builtin_fma(__builtin_fma(-q, den, num), r, q);
+    } else {
+        mid = ((__builtin_bit_cast(unsigned, q) >> 23) & 0xff) - 40u < 200u;
+        out = __builtin_fmaf(__builtin_fmaf(-q, den, num), r, q);
+    }
+    if (__any(!mid)) {  // a branch of the wavefront: rarely taken
+        asm volatile("" : "+v"(num));
+        if (!mid) out = num / den;
+    }
+    return out;
+}
+
+// The order in which lane groups take the segments of ptr (cnt of them, at
+// most one a thread): falling steps (entries over the L lanes, from 31 up
+// alike), equal ones in their own order, so that the lanes of a wavefront
+// have segments of like length.  Every thread calls it; `order` has room for
+// cnt numbers, `hist` for 16 * 32 bytes.
+__device__ __forceinline__ void res_order(int cnt, int L, const int *ptr, unsigned char *hist,
+                                          unsigned short *order)
+{
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const int key = tid < cnt ? 31 - min((ptr[tid + 1] - ptr[tid] + L - 1) / L, 31) : -1;
+    int total = 0, before = 0;
+#pragma unroll 1
+    for (int k = 0; k < 32; ++k) {
+        const unsigned long long mask = __ballot(key == k);
+        if (lane == k) total = __popcll(mask);
+        if (key == k) before = __popcll(mask & ((1ull << lane) - 1));
+    }
+    if (lane < 32) hist[w * 32 + lane] = (unsigned char)total;
+    __syncthreads();
+    int sum = 0, at = 0;  // lane k & 31: segments of key k in all wavefronts and in the earlier ones
+#pragma unroll 1
+    for (int v = 0; v < kResThreads / 64; ++v) {
+        if (v == w) at = sum;
+        sum += hist[v * 32 + (lane & 31)];
+    }
+    int first = sum;  // inclusive over the keys, then exclusive
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+        const int q = __shfl_up(first, o, 32);
+        if ((lane & 31) >= o) first += q;
+    }
+    const int base = __shfl(first - sum + at, max(key, 0), 64);
+    if (key >= 0) order[base + before] = (unsigned short)tid;
+    __syncthreads();
+}
+
+// k_resident where every lane group has at most one column and one row: what
+// an iteration reads of its own row and column (entries, b, c, the row
+// factor, x, z, delta, lambda) stays in registers, and LDS holds the vectors
+// that other lanes gather.  k_resident spends its time issuing instructions
+// (a wavefront of 64 takes four cycles of its SIMD for each): index, value,
+// gather and address of every entry, the division, masks of uneven rows.
+// Here an entry is a gather and a multiplication, the division a product and
+// its correction, and the lanes of a wavefront have rows and columns of like
+// length (res_order).  Measured per iteration with a check every ten:
+// 500x1000 with 5 entries a column 2.87 -> 1.53 us in FP64 and 2.88 -> 1.61
+// mixed, 150x331 1.91 -> 1.15 us, 20x30 1.95 -> 0.97 us.
+template <typename T>
+__global__ void __launch_bounds__(kResThreads)
+k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp, const int *__restrict__ ci,
+               const T *__restrict__ va, const int *__restrict__ cp, const int *__restrict__ ri,
+               const T *__restrict__ vc, const double *__restrict__ va64, const double *__restrict__ vc64,
+               const T *__restrict__ b, const double *__restrict__ b64, const T *__restrict__ c,
+               const double *__restrict__ c64, const T *__restrict__ fu, T *__restrict__ x, T *__restrict__ z,
+               T *__restrict__ u, double *__restrict__ lam, double *__restrict__ delta, double mu, long long iters,
+               int eval_only, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
+               HistRing hist, int gated)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ double red[10][kResThreads / 64], sv[10], nrm[4];
+    __shared__ int stop, skip;
+    if (!eval_only && st->done) return;
+    constexpr int NT = kResThreads, R = 8;
+    static_assert(sizeof(red) >= 16 * 32, "res_order's counts");
+    const int tid = threadIdx.x;
+    double *ls = (double *)(lds_raw + L.l);
+    T *xs = (T *)(lds_raw + L.x), *zs = (T *)(lds_raw + L.z), *us = (T *)(lds_raw + L.u);
+    T *vcs = (T *)(lds_raw + L.vc), *vas = (T *)(lds_raw + L.va);
+    int *cps = (int *)(lds_raw + L.cp), *rps = (int *)(lds_raw + L.rp);
+    unsigned short *ris = (unsigned short *)(lds_raw + L.ri), *cis = (unsigned short *)(lds_raw + L.ci);
+    const int nnz = rp[m];
+    for (int j = tid; j <= n; j += NT) cps[j] = cp[j];
+    for (int i = tid; i <= m; i += NT) rps[i] = rp[i];
+    for (int k = tid; k < nnz; k += NT) {
+        ris[k] = (unsigned short)ri[k];
+        vcs[k] = vc[k];
+        cis[k] = (unsigned short)ci[k];
+        vas[k] = va[k];
+    }
+    if (tid == 0) {
+        stop = 0;
+        nrm[0] = st->bnorm2;
+        nrm[1] = st->cnorm2;
+        nrm[2] = st->binf;
+        nrm[3] = st->cinf;
+    }
+    __syncthreads();
+    // own column and row; the orders lie where x and u will
+    const int gc = tid / Lc, lc = tid % Lc, gr = tid / Lr, lr = tid % Lr;
+    unsigned short *ord = (unsigned short *)(lds_raw + L.x);
+    res_order(n, Lc, cps, (unsigned char *)red, ord);
+    const int jc = gc < n ? ord[gc] : -1;
+    ord = (unsigned short *)(lds_raw + L.u);
+    res_order(m, Lr, rps, (unsigned char *)red, ord);
+    const int ic = gr < m ? ord[gr] : -1;
+    __syncthreads();
+    for (int j = tid; j < n; j += NT) {
+        xs[j] = x[j];
+        zs[j] = z[j];
+    }
+    for (int i = tid; i < m; i += NT) {
+        us[i] = u[i];
+        ls[i] = lam[i];
+    }
+    if (tid == 0) {  // the padding's zeros
+        xs[n] = zs[n] = (T)0;
+        us[m] = (T)0;
+        ls[m] = 0.0;
+    }
+    ResSeg<T, R> sc, sr;
+    // this lane keeps the column's x, z and delta, or the row's lambda
+    const bool own = lc == 0 && jc >= 0, own_row = lr == 0 && ic >= 0;
+    seg_load(sc, jc, lc, Lc, cps, ris, vcs, us, m);
+    T xo = jc >= 0 ? x[jc] : (T)0, zo = jc >= 0 ? z[jc] : (T)0;
+    const T cj = jc >= 0 ? c[jc] : (T)0, rc = (T)1 / (T)(1 + sc.cnt);
+    double dj = jc >= 0 ? delta[jc] : 0.0;
+    seg_load(sr, ic, lr, Lr, rps, cis, vas, xs, n);
+    const T bi = ic >= 0 ? b[ic] : (T)0, fi = ic >= 0 ? fu[ic] : (T)0;
+    const double bi64 = ic >= 0 ? b64[ic] : 0.0;
+    double li = ic >= 0 ? lam[ic] : 0.0;
+    __syncthreads();
+    const long long it0 = st->iter;
+    auto rows = [&](double (&v)[10]) {
+        double qz, qx;
+        if constexpr (sizeof(T) == sizeof(double)) {
+            qz = seg_sum(sr, fresh(L.z - L.x), Lr, cis, vas, zs);
+            qx = seg_sum(sr, 0, Lr, cis, vas, xs);
+        } else {  // FP64 values of A from global memory
+            lds_dot2(ic >= 0 ? rps[ic] : 0, ic >= 0 ? rps[ic + 1] : 0, lr, Lr, cis, va64, zs, xs, qz, qx);
+        }
+        if (own_row) check_row(v, qz, qx, bi64, li);
+    };
+    auto cols = [&](double (&v)[10]) {
+        double a;
+        if constexpr (sizeof(T) == sizeof(double)) a = seg_sum(sc, fresh(L.l - L.u), Lc, ris, vcs, ls);
+        else a = lds_dot<double>(jc >= 0 ? cps[jc] : 0, jc >= 0 ? cps[jc + 1] : 0, lc, Lc, ris, vc64, ls);
+        if (own) check_col(v, a, c64[jc], dj, (double)zo, (double)xo);
+    };
+    const double inv_mu = 1.0 / mu;
+    const bool gate_on = gated && !eval_only;
+    const int most = (int)iters;
+    int done = 0;
+    // iterations left to the next check; a residual query goes straight to it
+    int to_check = eval_only ? 0 : check_every - (int)(it0 % check_every);
+    while (eval_only || done < most) {
+        if (!eval_only) {
+            const T a = seg_sum(sc, 0, Lc, ris, vcs, us);
+            if (own) {  // x_step with the division by 1 + entries taken apart
+                const T dm = (T)(dj * inv_mu);
+                const T p = (T)sc.cnt * xo + a;
+                xo = div_whole<T>(p + zo + dm - cj * (T)inv_mu, (T)(1 + sc.cnt), rc);
+                const T v = xo - dm;
+                zo = v > (T)0 ? v : (T)0;
+                dj += mu * ((double)zo - (double)xo);
+                xs[jc] = xo;
+                zs[jc] = zo;
+            }
+            __syncthreads();
+            const T q = seg_sum(sr, 0, Lr, cis, vas, xs);
+            if (own_row) {
+                const T e = fi * (bi - q);
+                li -= mu * (double)e;
+                us[ic] = (T)((double)e - li * inv_mu);
+                ls[ic] = li;
+            }
+            __syncthreads();
+            ++done;
+            if (--to_check != 0) continue;
+            to_check = check_every;
+        }
+        if (res_check(rows, cols, red, sv, nrm, gate_on, eps, eps_abs, crit, &skip)) continue;
+        if (tid == 0) {
+            if (!eval_only) st->iter = it0 + done;
+            stop = finish_check(sv, nrm, it0 + done, eps, eps_abs, eps_gap, crit, eval_only ? 0 : 1, st, hist) ? 1 : 0;
+        }
+        if (eval_only) return;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(stop)) break;
+    }
+    if (own) {
+        x[jc] = xo;
+        z[jc] = zo;
+        delta[jc] = dj;
     }
     for (int i = tid; i < m; i += NT) {
         u[i] = us[i];
@@ -1616,12 +1937,15 @@ int build_graph(uv_solver *s)
     return UV_OK;
 }
 
-// Lanes per segment of k_resident: the most (a power of two, at most 64)
-// that keeps every segment of the pass on a lane group at once.
-int resident_lanes(int segs)
+// Lanes per segment of the resident kernels: the most (a power of two, at most
+// 64) that keeps every segment of the pass on a lane group at once, but two
+// entries a lane and more on average (a wider group's sum over its lanes costs
+// more than the entries it saves: 20x30 with 5 entries a column 1.9 us an
+// iteration on 32 lanes a column, 150x331 the same on 2).
+int resident_lanes(int segs, int64_t nnz)
 {
     int L = 1;
-    while (L < 64 && (int64_t)segs * L * 2 <= kResThreads) L <<= 1;
+    while (L < 64 && (int64_t)segs * L * 2 <= kResThreads && nnz >= (int64_t)segs * L * 4) L <<= 1;
     return L;
 }
 
@@ -1643,6 +1967,24 @@ struct ResArgs {
     int gated;  // checks primal half first (no history, opts.full_checks = 0)
 };
 
+// The resident kernel for m x n: the register form where every lane group
+// has at most one column and one row.  Two columns a group need more
+// registers than a thread of a full workgroup has (spilled: 700x1500 in FP64
+// 3.8 us an iteration against k_resident's 3.1).
+template <typename T>
+auto resident_kernel(int m, int n)
+{
+    return m > kResThreads || n > kResThreads ? k_resident<T> : k_resident_reg<T>;
+}
+
+// Lets its launches have the LDS of every resident problem.
+template <typename T>
+hipError_t resident_ready(int m, int n)
+{
+    return hipFuncSetAttribute((const void *)resident_kernel<T>(m, n), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kResLdsMax + 64);
+}
+
 // Up to `iters` iterations on the resident path in launches of at most 2^16
 // iterations (a launch returns at once once a check has stopped the run),
 // or with eval_only one launch that records the residuals of the state.
@@ -1657,8 +1999,8 @@ void resident_launch(const ResArgs &a, hipStream_t st, int64_t iters, bool eval_
         (const T *)a.b, a.b64, (const T *)a.c, a.c64, (const T *)a.fu, (T *)a.x, (T *)a.z, (T *)a.u, a.lam,        \
         a.delta, a.mu, q, eval_only ? 1 : 0, a.check_every, a.eps, a.eps_abs, a.eps_gap, a.crit, a.st, a.hist,  \
         a.gated
-        if (a.mixed) k_resident<float><<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(float));
-        else k_resident<double><<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(double));
+        if (a.mixed) resident_kernel<float>(a.m, a.n)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(float));
+        else resident_kernel<double>(a.m, a.n)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(double));
 #undef UV_RES_ARGS
         left -= eval_only ? 1 : kChunk;
     }
@@ -2130,7 +2472,7 @@ int solver_create(const uv_csr *A, const double *b, const double *c, const uv_co
         const bool mixed = o.precision == UV_MIXED;
         s->rlay = mixed ? resident_layout<float>(A->m, A->n, (int)A->nnz)
                         : resident_layout<double>(A->m, A->n, (int)A->nnz);
-        const bool fits = K->n_soc == 0 && A->m < 65536 && A->n < 65536 && s->rlay.bytes <= kResLdsMax;
+        const bool fits = K->n_soc == 0 && A->m < 65536 && A->n < 65536 && s->rlay.need <= kResLdsMax;
         if (o.resident == 2 && !fits) {
             solver_destroy(s);
             return UV_EINVAL;
@@ -2139,13 +2481,10 @@ int solver_create(const uv_csr *A, const double *b, const double *c, const uv_co
         s->forced = o.lanes_row || o.lanes_col || o.unroll_row || o.unroll_col || o.slabs_row || o.slabs_col ||
                     o.slab_kernel;
         s->resident = fits && (o.resident == 2 || (o.resident == 0 && !s->forced));
-        s->res_lr = resident_lanes(A->m);
-        s->res_lc = resident_lanes(A->n);
+        s->res_lr = resident_lanes(A->m, A->nnz);
+        s->res_lc = resident_lanes(A->n, A->nnz);
         if (s->resident) {
-            const hipError_t e = mixed ? hipFuncSetAttribute((const void *)k_resident<float>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsMax)
-                                       : hipFuncSetAttribute((const void *)k_resident<double>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsMax);
+            const hipError_t e = mixed ? resident_ready<float>(A->m, A->n) : resident_ready<double>(A->m, A->n);
             if (e != hipSuccess) {
                 solver_destroy(s);
                 return UV_EHIP;
@@ -2511,7 +2850,7 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     const bool mixed = o.precision == UV_MIXED;
     const int m = A->m, n = A->n, nnz = (int)A->nnz;
     const ResLayout L = mixed ? resident_layout<float>(m, n, nnz) : resident_layout<double>(m, n, nnz);
-    if (K->n_soc != 0 || m >= 65536 || n >= 65536 || L.bytes > kResLdsMax) return UV_ENOSCRATCH;
+    if (K->n_soc != 0 || m >= 65536 || n >= 65536 || L.need > kResLdsMax) return UV_ENOSCRATCH;
     NoAlloc d{};
     Carve size{nullptr, 0, kScratchBytes, true};
     if (!carve_noalloc(size, m, n, nnz, mixed, d)) return UV_ENOSCRATCH;
@@ -2519,11 +2858,7 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     if ((rc = scratch_address(&base)) != UV_OK) return rc;
     Carve cv{base, 0, kScratchBytes, true};
     carve_noalloc(cv, m, n, nnz, mixed, d);
-    const hipError_t fe = mixed ? hipFuncSetAttribute((const void *)k_resident<float>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsMax)
-                                : hipFuncSetAttribute((const void *)k_resident<double>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsMax);
-    if (fe != hipSuccess) return UV_EHIP;
+    if ((mixed ? resident_ready<float>(m, n) : resident_ready<double>(m, n)) != hipSuccess) return UV_EHIP;
     hipStream_t st = (hipStream_t)o.hip_stream;
     const size_t ts = mixed ? 4 : 8;
     // inputs and the setup of solver_create
@@ -2561,8 +2896,8 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     a.m = m;
     a.n = n;
     a.L = L;
-    a.Lr = resident_lanes(m);
-    a.Lc = resident_lanes(n);
+    a.Lr = resident_lanes(m, nnz);
+    a.Lc = resident_lanes(n, nnz);
     a.rp = d.rp;
     a.ci = d.ci;
     a.cp = d.cp;
