@@ -73,9 +73,10 @@ struct HistRing {
 
 constexpr int kSocTile = 256;  // columns per SOC tile when cones are small
 
-// ||b||^2 and ||c||^2 in FP64 (one workgroup, fixed order).
-__global__ void __launch_bounds__(kWG)
-k_norms(int m, const double *__restrict__ b, int n, const double *__restrict__ c, DevStatus *st)
+// ||b||^2 and ||c||^2 in FP64 (the first kWG threads of one workgroup, fixed
+// order).
+__device__ __forceinline__ void norms(int m, const double *__restrict__ b, int n, const double *__restrict__ c,
+                                      DevStatus *st)
 {
     double v[2] = {0.0, 0.0}, w[2] = {0.0, 0.0};
     for (int i = threadIdx.x; i < m; i += kWG) {
@@ -96,6 +97,23 @@ k_norms(int m, const double *__restrict__ b, int n, const double *__restrict__ c
     }
 }
 
+__global__ void __launch_bounds__(kWG)
+k_norms(int m, const double *__restrict__ b, int n, const double *__restrict__ c, DevStatus *st)
+{
+    norms(m, b, n, c, st);
+}
+
+__device__ __forceinline__ void start_status(DevStatus *st)
+{
+    st->iter = 0;
+    st->check_iter = -1;
+    st->hist_n = 0;
+    st->clock0 = wall_clock64();
+    st->done = 0;
+    st->status = UV_STATUS_RUNNING;
+    st->skip_col = 0;
+}
+
 // Start: u = -lambda/mu (see the header comment), iteration state reset.
 template <typename T>
 __global__ void __launch_bounds__(kWG)
@@ -103,15 +121,7 @@ k_start(int m, const double *__restrict__ lam, T *__restrict__ u, double inv_mu,
 {
     int i = blockIdx.x * kWG + threadIdx.x;
     if (i < m) u[i] = (T)(-lam[i] * inv_mu);
-    if (i == 0) {
-        st->iter = 0;
-        st->check_iter = -1;
-        st->hist_n = 0;
-        st->clock0 = wall_clock64();
-        st->done = 0;
-        st->status = UV_STATUS_RUNNING;
-        st->skip_col = 0;
-    }
+    if (i == 0) start_status(st);
 }
 
 // ---------------------------------------------------------------------------
@@ -818,6 +828,10 @@ struct ResLayout {
 };
 
 constexpr int kResThreads = 1024;
+// Modes of the resident kernels: iterate; record the state's residuals; iterate
+// and leave the final iterate's residuals (k_resident_reg; k_resident iterates
+// only, and a query follows).
+constexpr int kResIterate = 0, kResEval = 1, kResRecord = 2;
 constexpr int kResLdsMax = 160 * 1024 - 2048;  // a CU's LDS less the kernel's static slots and the zeros (64 bytes)
 
 template <typename T>
@@ -991,8 +1005,8 @@ __device__ __forceinline__ bool res_check(Rows rows, Cols cols, double (*red)[kR
 // fixed-order workgroup reduction) and its stop decision; with gated the
 // check's column half is skipped when its primal half fails the stopping
 // test (res_check); the state goes back to global memory at the end.  Same
-// per-entry arithmetic as the sweep kernels.  eval_only: no iteration, the
-// residuals of the current state are recorded without a stop decision (a
+// per-entry arithmetic as the sweep kernels.  Mode kResEval: no iteration,
+// the residuals of the current state are recorded without a stop decision (a
 // residual query).
 template <typename T>
 __global__ void __launch_bounds__(kResThreads)
@@ -1002,12 +1016,13 @@ k_resident(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp
            const T *__restrict__ b, const double *__restrict__ b64, const T *__restrict__ c,
            const double *__restrict__ c64, const T *__restrict__ fu, T *__restrict__ x, T *__restrict__ z,
            T *__restrict__ u, double *__restrict__ lam, double *__restrict__ delta, double mu, long long iters,
-           int eval_only, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
+           int mode, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
            HistRing hist, int gated)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ double red[10][kResThreads / 64], sv[10], nrm[4];
     __shared__ int stop, skip;
+    const bool eval_only = mode == kResEval;
     if (!eval_only && st->done) return;
     constexpr int NT = kResThreads;
     const int tid = threadIdx.x;
@@ -1278,8 +1293,10 @@ __device__ __forceinline__ void res_order(int cnt, int L, const int *ptr, unsign
 // Here an entry is a gather and a multiplication, the division a product and
 // its correction, and the lanes of a wavefront have rows and columns of like
 // length (res_order).  Measured per iteration with a check every ten:
-// 500x1000 with 5 entries a column 2.87 -> 1.53 us in FP64 and 2.88 -> 1.61
-// mixed, 150x331 1.91 -> 1.15 us, 20x30 1.95 -> 0.97 us.
+// 500x1000 with 5 entries a column 2.87 -> 1.31 us in FP64 and 2.88 -> 1.37
+// mixed, 150x331 1.91 -> 0.98 us, 20x30 1.95 -> 0.84 us.  The iterations
+// between two checks are a loop of their own: with the check's branches in
+// it the same arithmetic took 1.49 us (masks and counters spilled).
 template <typename T>
 __global__ void __launch_bounds__(kResThreads)
 k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp, const int *__restrict__ ci,
@@ -1288,12 +1305,13 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
                const T *__restrict__ b, const double *__restrict__ b64, const T *__restrict__ c,
                const double *__restrict__ c64, const T *__restrict__ fu, T *__restrict__ x, T *__restrict__ z,
                T *__restrict__ u, double *__restrict__ lam, double *__restrict__ delta, double mu, long long iters,
-               int eval_only, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
+               int mode, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
                HistRing hist, int gated)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ double red[10][kResThreads / 64], sv[10], nrm[4];
     __shared__ int stop, skip;
+    const bool eval_only = mode == kResEval, record = mode == kResRecord;
     if (!eval_only && st->done) return;
     constexpr int NT = kResThreads, R = 8;
     static_assert(sizeof(red) >= 16 * 32, "res_order's counts");
@@ -1372,13 +1390,12 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
         if (own) check_col(v, a, c64[jc], dj, (double)zo, (double)xo);
     };
     const double inv_mu = 1.0 / mu;
-    const bool gate_on = gated && !eval_only;
-    const int most = (int)iters;
-    int done = 0;
+    int done = 0, left = eval_only ? 0 : (int)iters;
     // iterations left to the next check; a residual query goes straight to it
     int to_check = eval_only ? 0 : check_every - (int)(it0 % check_every);
-    while (eval_only || done < most) {
-        if (!eval_only) {
+    do {
+        const int run = min(to_check, left);
+        for (int t = run; t > 0; --t) {
             const T a = seg_sum(sc, 0, Lc, ris, vcs, us);
             if (own) {  // x_step with the division by 1 + entries taken apart
                 const T dm = (T)(dj * inv_mu);
@@ -1399,19 +1416,23 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
                 ls[ic] = li;
             }
             __syncthreads();
-            ++done;
-            if (--to_check != 0) continue;
-            to_check = check_every;
         }
-        if (res_check(rows, cols, red, sv, nrm, gate_on, eps, eps_abs, crit, &skip)) continue;
+        done += run;
+        left -= run;
+        to_check -= run;
+        // with record the launch ends with a whole check, decided only if it is due
+        const bool due = !eval_only && to_check == 0, whole = record && left == 0;
+        if (!eval_only && !due && !whole) break;
+        if (to_check == 0) to_check = check_every;
+        if (res_check(rows, cols, red, sv, nrm, gated && due && !whole, eps, eps_abs, crit, &skip)) continue;
         if (tid == 0) {
             if (!eval_only) st->iter = it0 + done;
-            stop = finish_check(sv, nrm, it0 + done, eps, eps_abs, eps_gap, crit, eval_only ? 0 : 1, st, hist) ? 1 : 0;
+            stop = finish_check(sv, nrm, it0 + done, eps, eps_abs, eps_gap, crit, due ? 1 : 0, st, hist) ? 1 : 0;
         }
         if (eval_only) return;
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(stop)) break;
-    }
+    } while (left > 0);
     if (own) {
         x[jc] = xo;
         z[jc] = zo;
@@ -1940,8 +1961,8 @@ int build_graph(uv_solver *s)
 // Lanes per segment of the resident kernels: the most (a power of two, at most
 // 64) that keeps every segment of the pass on a lane group at once, but two
 // entries a lane and more on average (a wider group's sum over its lanes costs
-// more than the entries it saves: 20x30 with 5 entries a column 1.9 us an
-// iteration on 32 lanes a column, 150x331 the same on 2).
+// more than the entries it saves: 20x30 with 5 entries a column took 1.67 us an
+// iteration on 32 lanes a column and row, 0.97 us on 1 and 2).
 int resident_lanes(int segs, int64_t nnz)
 {
     int L = 1;
@@ -1987,17 +2008,20 @@ hipError_t resident_ready(int m, int n)
 
 // Up to `iters` iterations on the resident path in launches of at most 2^16
 // iterations (a launch returns at once once a check has stopped the run),
-// or with eval_only one launch that records the residuals of the state.
-void resident_launch(const ResArgs &a, hipStream_t st, int64_t iters, bool eval_only)
+// the last one in the given mode, or with kResEval one launch that records
+// the residuals of the state.
+void resident_launch(const ResArgs &a, hipStream_t st, int64_t iters, int mode)
 {
     constexpr int64_t kChunk = (int64_t)1 << 16;
+    const bool eval_only = mode == kResEval;
     int64_t left = eval_only ? 1 : iters;
     while (left > 0) {
         const long long q = eval_only ? 0 : (long long)std::min(left, kChunk);
+        const int what = mode == kResRecord && left > kChunk ? kResIterate : mode;
 #define UV_RES_ARGS(T)                                                                                         \
     a.m, a.n, a.L, a.Lr, a.Lc, a.rp, a.ci, (const T *)a.va, a.cp, a.ri, (const T *)a.vc, a.va64, a.vc64,         \
         (const T *)a.b, a.b64, (const T *)a.c, a.c64, (const T *)a.fu, (T *)a.x, (T *)a.z, (T *)a.u, a.lam,        \
-        a.delta, a.mu, q, eval_only ? 1 : 0, a.check_every, a.eps, a.eps_abs, a.eps_gap, a.crit, a.st, a.hist,  \
+        a.delta, a.mu, q, what, a.check_every, a.eps, a.eps_abs, a.eps_gap, a.crit, a.st, a.hist,  \
         a.gated
         if (a.mixed) resident_kernel<float>(a.m, a.n)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(float));
         else resident_kernel<double>(a.m, a.n)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(double));
@@ -2593,17 +2617,12 @@ struct Carve {
 };
 
 // int64 row offsets (m + 1, validated below 2^31) to the 32-bit device form.
-__global__ void __launch_bounds__(kWG) k_narrow_offsets(int len, const int64_t *__restrict__ src, int *__restrict__ dst)
-{
-    const int i = blockIdx.x * kWG + threadIdx.x;
-    if (i < len) dst[i] = (int)src[i];
-}
 
 // Device buffers of one no-allocation solve.
 struct NoAlloc {
     DevStatus *st;
     int64_t *rp64;
-    int *rp, *ci, *cp, *ri, *cnt, *bsum;
+    int *rp, *ci, *cp, *ri;
     double *va64, *vc64, *b64, *c64, *lam, *delta, *wide;
     void *va, *vc, *b, *c, *fu, *x, *z, *u;
 };
@@ -2617,8 +2636,6 @@ bool carve_noalloc(Carve &cv, int m, int n, int nnz, bool mixed, NoAlloc &d)
     d.ci = cv.take<int>(nnz);
     d.cp = cv.take<int>((size_t)n + 1);
     d.ri = cv.take<int>(nnz);
-    d.cnt = cv.take<int>(n);
-    d.bsum = cv.take<int>(blocks_for(n, 4 * kWG));
     d.va64 = cv.take<double>(nnz);
     d.vc64 = cv.take<double>(nnz);
     d.b64 = cv.take<double>(m);
@@ -2635,6 +2652,124 @@ bool carve_noalloc(Carve &cv, int m, int n, int nnz, bool mixed, NoAlloc &d)
     d.z = cv.take<char>(ts * n);
     d.u = cv.take<char>(ts * m);
     return cv.ok;
+}
+
+constexpr int kSetupThreads = 1024;
+
+// The set-up of a no-allocation solve in one launch, bit for bit what
+// solver_create and solver_set_start prepare: workgroup 0 the offsets and the
+// column copy of A, workgroup 1 the norms, the status and the zero start,
+// workgroup 2 the row factors and the narrowed values and vectors.  Fifteen
+// launches and fills of a few microseconds each came before, and a launch of
+// its own for the last residuals after (150x331 with 100 iterations: 378 ->
+// 277 us a call).
+// Workgroup 0 counts, scans and scatters the entries' rows in LDS; an entry's
+// place in its column is the number of smaller rows there, so the order does
+// not depend on the scatter's.
+template <typename T>
+__global__ void __launch_bounds__(kSetupThreads)
+k_noalloc_setup(int m, int n, int nnz, NoAlloc d, double inv_mu)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    constexpr int NT = kSetupThreads;
+    constexpr bool narrow = sizeof(T) == sizeof(float);
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    if (blockIdx.x == 1) {
+        for (int j = tid; j < n; j += NT) {
+            ((T *)d.x)[j] = ((T *)d.z)[j] = (T)0;
+            d.delta[j] = 0.0;
+        }
+        for (int i = tid; i < m; i += NT) {
+            d.lam[i] = 0.0;
+            ((T *)d.u)[i] = (T)(-0.0 * inv_mu);
+        }
+        if (tid == 0) start_status(d.st);
+        if (tid < kWG) norms(m, d.b64, n, d.c64, d.st);  // whole wavefronts; the others are done
+        return;
+    }
+    if (blockIdx.x == 2) {
+        for (int i = tid; i < m; i += NT) {
+            const int k1 = (int)d.rp64[i + 1];
+            double s = 0.0;
+            int k = (int)d.rp64[i];
+            for (; k + 3 < k1; k += 4) {
+                const double a0 = d.va64[k], a1 = d.va64[k + 1], a2 = d.va64[k + 2], a3 = d.va64[k + 3];
+                s += a0 * a0;
+                s += a1 * a1;
+                s += a2 * a2;
+                s += a3 * a3;
+            }
+            for (; k < k1; ++k) s += d.va64[k] * d.va64[k];
+            ((T *)d.fu)[i] = (T)(1.0 / (1.0 + s));
+        }
+        if constexpr (narrow) {
+            for (int k = tid; k < nnz; k += NT) ((T *)d.va)[k] = (T)d.va64[k];
+            for (int i = tid; i < m; i += NT) ((T *)d.b)[i] = (T)d.b64[i];
+            for (int j = tid; j < n; j += NT) ((T *)d.c)[j] = (T)d.c64[j];
+        }
+        return;
+    }
+    int *rps = (int *)lds_raw, *cps = rps + m + 1, *fill = cps + n + 1;
+    unsigned short *rows = (unsigned short *)(fill + n);
+    __shared__ int wsum[NT / 64];
+    for (int i = tid; i <= m; i += NT) {
+        const int q = (int)d.rp64[i];
+        rps[i] = q;
+        d.rp[i] = q;
+    }
+    for (int j = tid; j < n; j += NT) fill[j] = 0;
+    __syncthreads();
+    for (int k = tid; k < nnz; k += NT) atomicAdd(&fill[d.ci[k]], 1);
+    __syncthreads();
+    // exclusive offsets of the columns, NT columns at a time
+    int carry = 0;
+    for (int j0 = 0; j0 < n; j0 += NT) {
+        const int j = j0 + tid, cnt = j < n ? fill[j] : 0;
+        int s = cnt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int q = __shfl_up(s, o, 64);
+            if (lane >= o) s += q;
+        }
+        if (lane == 63) wsum[w] = s;
+        __syncthreads();
+        int before = carry;
+        for (int v = 0; v < NT / 64; ++v) {
+            if (v < w) before += wsum[v];
+            carry += wsum[v];
+        }
+        if (j < n) {
+            cps[j] = d.cp[j] = before + s - cnt;
+            fill[j] = 0;
+        }
+        __syncthreads();
+    }
+    if (tid == 0) cps[n] = d.cp[n] = nnz;
+    __syncthreads();
+    // the row of entry k: the last one that starts at or before it
+    auto row_of = [&](int k) {
+        int lo = 0, hi = m;  // rps[lo] <= k < rps[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (rps[mid] <= k) lo = mid;
+            else hi = mid;
+        }
+        return lo;
+    };
+    for (int k = tid; k < nnz; k += NT) {
+        const int j = d.ci[k];
+        rows[cps[j] + atomicAdd(&fill[j], 1)] = (unsigned short)row_of(k);
+    }
+    __syncthreads();
+    for (int k = tid; k < nnz; k += NT) {
+        const int j = d.ci[k], i = row_of(k), c0 = cps[j], c1 = cps[j + 1];
+        int at = c0;
+        for (int q = c0; q < c1; ++q) at += rows[q] < i;
+        const double v = d.va64[k];
+        d.ri[at] = i;
+        d.vc64[at] = v;
+        if constexpr (narrow) ((T *)d.vc)[at] = (T)v;
+    }
 }
 
 }  // namespace
@@ -2693,7 +2828,7 @@ int solver_iterate(uv_solver *s, int64_t k, int32_t *done)
         const int ce = s->o.check_every;
         const int64_t look = 50 * (int64_t)ce;  // read the stop flag every 50 checks
         if (s->resident && left > 0) {
-            resident_launch(res_args(s), s->stream, left, false);
+            resident_launch(res_args(s), s->stream, left, kResIterate);
             left = 0;
         }
         while (left > 0) {
@@ -2735,7 +2870,7 @@ int solver_residuals(uv_solver *s, uv_residuals *r)
 {
     if (!s || !r) return UV_EINVAL;
     if (s->st_host->check_iter != s->st_host->iter) {
-        if (s->resident) resident_launch(res_args(s), s->stream, 0, true);
+        if (s->resident) resident_launch(res_args(s), s->stream, 0, kResEval);
         else launch_residuals(s, s->stream, false, false);
         UV_TRY(hipGetLastError());
         int rc = sync_status(s);
@@ -2860,37 +2995,20 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     carve_noalloc(cv, m, n, nnz, mixed, d);
     if ((mixed ? resident_ready<float>(m, n) : resident_ready<double>(m, n)) != hipSuccess) return UV_EHIP;
     hipStream_t st = (hipStream_t)o.hip_stream;
-    const size_t ts = mixed ? 4 : 8;
     // inputs and the setup of solver_create
     UV_TRY(hipMemcpyAsync(d.rp64, A->row_ptr, 8 * ((size_t)m + 1), hipMemcpyHostToDevice, st));
-    k_narrow_offsets<<<blocks_for(m + 1, kWG), kWG, 0, st>>>(m + 1, d.rp64, d.rp);
     if (nnz > 0) {
         UV_TRY(hipMemcpyAsync(d.ci, A->col_idx, 4 * (size_t)nnz, hipMemcpyHostToDevice, st));
         UV_TRY(hipMemcpyAsync(d.va64, A->val, 8 * (size_t)nnz, hipMemcpyHostToDevice, st));
     }
     UV_TRY(hipMemcpyAsync(d.b64, b, 8 * (size_t)m, hipMemcpyHostToDevice, st));
     UV_TRY(hipMemcpyAsync(d.c64, c, 8 * (size_t)n, hipMemcpyHostToDevice, st));
-    if (!build_csc(m, n, nnz, d.rp, d.ci, d.va64, d.cp, d.ri, d.vc64, d.cnt, d.bsum, st)) return UV_EHIP;
-    if (mixed) {
-        k_row_factor<float><<<blocks_for(m, kWG), kWG, 0, st>>>(m, d.rp, d.va64, (float *)d.fu);
-        if (nnz > 0) {
-            k_narrow<float><<<blocks_for(nnz, kWG), kWG, 0, st>>>(nnz, d.va64, (float *)d.va);
-            k_narrow<float><<<blocks_for(nnz, kWG), kWG, 0, st>>>(nnz, d.vc64, (float *)d.vc);
-        }
-        k_narrow<float><<<blocks_for(m, kWG), kWG, 0, st>>>(m, d.b64, (float *)d.b);
-        k_narrow<float><<<blocks_for(n, kWG), kWG, 0, st>>>(n, d.c64, (float *)d.c);
-    } else {
-        k_row_factor<double><<<blocks_for(m, kWG), kWG, 0, st>>>(m, d.rp, d.va64, (double *)d.fu);
-    }
-    k_norms<<<1, kWG, 0, st>>>(m, d.b64, n, d.c64, d.st);
-    // the zero start (everything the last call left in the scratch is overwritten)
-    UV_TRY(hipMemsetAsync(d.x, 0, ts * n, st));
-    UV_TRY(hipMemsetAsync(d.z, 0, ts * n, st));
-    UV_TRY(hipMemsetAsync(d.delta, 0, 8 * (size_t)n, st));
-    UV_TRY(hipMemsetAsync(d.lam, 0, 8 * (size_t)m, st));
+    // (everything the last call left in the scratch is overwritten)
     const double im = 1.0 / o.mu;
-    if (mixed) k_start<float><<<blocks_for(m, kWG), kWG, 0, st>>>(m, d.lam, (float *)d.u, im, d.st);
-    else k_start<double><<<blocks_for(m, kWG), kWG, 0, st>>>(m, d.lam, (double *)d.u, im, d.st);
+    // at most 65 kB where the problem fits the resident layout (20 n + 16 m + 12 nnz bytes and more)
+    const size_t lds = 4 * ((size_t)m + 1) + 4 * ((size_t)n + 1) + 4 * (size_t)n + 2 * (size_t)nnz;
+    if (mixed) k_noalloc_setup<float><<<3, kSetupThreads, lds, st>>>(m, n, nnz, d, im);
+    else k_noalloc_setup<double><<<3, kSetupThreads, lds, st>>>(m, n, nnz, d, im);
     UV_TRY(hipGetLastError());
     ResArgs a{};
     a.m = m;
@@ -2928,13 +3046,13 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     a.crit = o.criterion;
     int64_t left = iters;
     if (o.max_iter > 0) left = std::min<int64_t>(left, o.max_iter);
-    resident_launch(a, st, left, false);
+    resident_launch(a, st, left, r ? kResRecord : kResIterate);
     UV_TRY(hipGetLastError());
     DevStatus h{};
     UV_TRY(hipMemcpyAsync(&h, d.st, sizeof(DevStatus), hipMemcpyDeviceToHost, st));
     UV_TRY(hipStreamSynchronize(st));
-    if (r && h.check_iter != h.iter) {  // residuals of the final iterate (no decision)
-        resident_launch(a, st, 0, true);
+    if (r && h.check_iter != h.iter) {  // residuals of the final iterate where the launch left none (no decision)
+        resident_launch(a, st, 0, kResEval);
         UV_TRY(hipGetLastError());
         const int status = h.status, stopped = h.done;
         UV_TRY(hipMemcpyAsync(&h, d.st, sizeof(DevStatus), hipMemcpyDeviceToHost, st));
