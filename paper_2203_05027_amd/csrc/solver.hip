@@ -1299,8 +1299,8 @@ __device__ __forceinline__ void res_order(int cnt, int L, const int *ptr, unsign
 // Here an entry is a gather and a multiplication, the division a product and
 // its correction, and the lanes of a wavefront have rows and columns of like
 // length (res_order).  Measured per iteration with a check every ten:
-// 500x1000 with 5 entries a column 2.87 -> 1.31 us in FP64 and 2.88 -> 1.37
-// mixed, 150x331 1.91 -> 0.98 us, 20x30 1.95 -> 0.84 us.  The iterations
+// 500x1000 with 5 entries a column 2.87 -> 1.35 us in FP64 and 2.88 -> 1.37
+// mixed, 150x331 1.91 -> 0.99 us, 20x30 1.95 -> 0.85 us.  The iterations
 // between two checks are a loop of their own: with the check's branches in
 // it the same arithmetic took 1.49 us (masks and counters spilled).
 template <typename T>
@@ -1397,8 +1397,10 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
     };
     const double inv_mu = 1.0 / mu;
     int done = 0, left = eval_only ? 0 : (int)iters;
-    // iterations left to the next check; a residual query goes straight to it
-    int to_check = eval_only ? 0 : check_every - (int)(it0 % check_every);
+    int to_check = check_every - (int)(it0 % check_every);  // iterations left to the next check
+    // a whole check without a decision comes next: a residual query, or with
+    // record the last iterate's where no check is due or the due one was skipped
+    bool query = eval_only;
     do {
         const int run = min(to_check, left);
         for (int t = run; t > 0; --t) {
@@ -1426,19 +1428,22 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
         done += run;
         left -= run;
         to_check -= run;
-        // with record the launch ends with a whole check, decided only if it is due
-        const bool due = !eval_only && to_check == 0, whole = record && left == 0;
-        if (!eval_only && !due && !whole) break;
-        if (to_check == 0) to_check = check_every;
-        if (res_check(rows, cols, red, sv, nrm, gated && due && !whole, eps, eps_abs, crit, &skip)) continue;
+        const bool due = !query && to_check == 0;
+        if (due) to_check = check_every;
+        else if (!query && !record) break;
+        if (res_check(rows, cols, red, sv, nrm, gated && due, eps, eps_abs, crit, &skip)) {
+            query = record && left == 0;
+            continue;
+        }
         if (tid == 0) {
             if (!eval_only) st->iter = it0 + done;
             stop = finish_check(sv, nrm, it0 + done, eps, eps_abs, eps_gap, crit, due ? 1 : 0, st, hist) ? 1 : 0;
         }
         if (eval_only) return;
+        query = false;
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(stop)) break;
-    } while (left > 0);
+    } while (left > 0 || query);
     if (own) {
         x[jc] = xo;
         z[jc] = zo;

@@ -42,3 +42,20 @@ def test_noalloc_setup_equals_the_general_one(shape, precision):
         for k in KEYS:
             assert np.array_equal(a[k], b[k]), (iters, k)
         assert ra == rb, iters
+
+
+def test_a_query_after_a_skipped_check_decides_nothing():
+    """An empty column with a cost of 1e200: the primal half of every check is
+    finite and fails, the column half overflows, and only a check that is not
+    skipped may stop the run for it."""
+    inst = _instance(40, 90, 0.1, 3)
+    c = inst["c"].copy()
+    c[inst["n"] // 3] = 1e200
+    inst = dict(inst, c=c)
+    for iters in (10, 15, 20):
+        rc_a, a, ra = solve(inst, iters, eps=0.0, check_every=10)
+        rc_b, b, rb = solve(inst, iters, noalloc=True, eps=0.0, check_every=10)
+        assert rc_a == rc_b
+        for k in KEYS:
+            assert np.array_equal(a[k], b[k], equal_nan=True), (iters, k)
+        assert repr(ra) == repr(rb), iters
