@@ -446,7 +446,7 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
         __syncthreads();
         // lane groups per segment, or the sliced copies (a wavefront per 64)
         const bool sc = sliced && Lc <= 1, sr = sliced && Lr == 1;
-        const int Lc1 = Lc > 0 ? Lc : 1;
+        const int Lc1 = Lc > 0 ? Lc : 1;  // lane groups step by it: never zero
         const int gc = tid / Lc1, lc = tid % Lc1, Gc = nthr / Lc1;
         const int wv = tid >> 6, lane64 = tid & 63, nwv = nthr >> 6, nch = (n + 63) >> 6;
         const int *sp_c = scol.ptr + I->ch_off, *sp_r = srow.ptr + I->rh_off;
@@ -481,9 +481,9 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                         zj = zi[j];
                         cj = ci_[j];
                     }
-                    atu = seg_sum<4, T>(beg, end, lc, Lc, rl, vc, us);
+                    atu = seg_sum<4, T>(beg, end, lc, Lc1, rl, vc, us);
                 }
-                atu = group_sum_rt(atu, Lc);
+                atu = group_sum_rt(atu, Lc1);
                 if (j < n && lc == 0) col_update(j, end - beg, atu, d, zj, cj);
             }
             __syncthreads();
@@ -581,8 +581,8 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                 for (int jb = 0; jb < n; jb += Gc) {
                     const int j = jb + gc;
                     double atl = 0.0;
-                    if (j < n) atl = seg_sum<4, double>(cp[c0 + j], cp[c0 + j + 1], lc, Lc, rl, vc64, lam + r0);
-                    atl = group_sum_rt(atl, Lc);
+                    if (j < n) atl = seg_sum<4, double>(cp[c0 + j], cp[c0 + j + 1], lc, Lc1, rl, vc64, lam + r0);
+                    atl = group_sum_rt(atl, Lc1);
                     if (j < n && lc == 0) col_res(j, atl);
                 }
                 block_sum_rt<5>(a);
@@ -740,11 +740,12 @@ int build_slices(uv_batch *h, bool rows, const std::vector<int> &counts)
 
 int apply_tiles(uv_batch *h)
 {
-    // lanes per row / column from the tile table, by size bucket
+    // lanes per row / column from the tile table, by size bucket; without the
+    // sliced copies their columns (0 lanes) are walked by one lane each
     for (int i = 0; i < h->count; ++i) {
         const int bk = bucket_of(h->inst_host[i].m);
         h->inst_host[i].Lr = h->tiles[2 * bk];
-        h->inst_host[i].Lc = h->tiles[2 * bk + 1];
+        h->inst_host[i].Lc = h->sliced ? h->tiles[2 * bk + 1] : std::max(1, h->tiles[2 * bk + 1]);
     }
     UV_BTRY(hipMemcpyAsync(h->inst, h->inst_host, sizeof(BInst) * h->count, hipMemcpyHostToDevice, h->stream));
     UV_BTRY(hipStreamSynchronize(h->stream));

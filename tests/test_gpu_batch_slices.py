@@ -107,3 +107,20 @@ def test_instances_that_just_fill_lds(extra):
     A = sp.csr_matrix((np.abs(inst["val"]), inst["col_idx"], inst["row_ptr"]), shape=(inst["m"], inst["n"]))
     scale["lambda"] = (A @ np.abs(so["x"])).max()
     assert all(np.abs(sol[k] - so[k]).max() <= 1e-9 * scale[k] for k in KEYS), errs
+
+
+@pytest.mark.parametrize("precision,total", [("fp64", 20349), ("fp64", 20350), ("mixed", 40699), ("mixed", 40700)])
+def test_sliced_columns_asked_for_without_room_for_them(precision, total):
+    """x and u fit LDS, the padding's two zeros do not: zero lanes per column
+    (the sliced copy) are then one lane a column, in the sweep and the checks."""
+    m = total // 3
+    inst = _instance(m, total - m, 5.0 / m, 13)
+    out = []
+    for lanes in ([2, 0] * 4, [2, 1] * 4):
+        with Batch([inst], precision=precision, eps=0.0, check_every=3, full_checks=True) as b:
+            b.set_tiles(512, lanes)
+            b.iterate(7)
+            out.append((b.solution(0), b.residuals(0)))
+    for k in KEYS:
+        assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    assert out[0][1] == out[1][1] and out[0][1]["iter"] == 7
