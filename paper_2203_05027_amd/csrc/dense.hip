@@ -7,7 +7,8 @@
 //   q rounds of Z <- orth(Y (orth(Y' Z))),  Q = orth(Z),  B = Q' Y (l x D),
 //   B B' = U S^2 U' (Jacobi),  basis = top-k rows of S^{-1} U' B,
 // i.e. the randomized range finder with power iterations of Halko,
-// Martinsson and Tropp; orth() is Cholesky QR applied twice.
+// Martinsson and Tropp; orth() is Cholesky QR of FP64 Gram matrices, applied
+// until the columns are orthonormal, with a random column for a dependent one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -193,6 +194,64 @@ k_gemm_sum(int M, int N, int splits, const float *__restrict__ W, float *__restr
     *p = alpha * s + (beta != 0.f ? beta * *p : 0.f);
 }
 
+// Gram matrix of l vectors of length K in FP64 (FP32 elements, whose products
+// are exact): element k of vector i at P[i * rs + k * ks].  A workgroup owns a
+// 64 x 64 block for a share of k (blockIdx.z of `splits`), 4 x 4 entries a
+// thread, and leaves its sums in W[split][l][l]; k_gram_sum adds them in order.
+// FP64 because the factor of a Gram matrix resolves singular values only down
+// to the root of its rounding: 5e-4 of the largest in FP32, which is where a
+// smooth family's spectrum goes on, 1e-7 in FP64, where the FP32 samples end.
+template <int MODE>
+__global__ void __launch_bounds__(256)
+k_gram(int l, int K, const float *__restrict__ P, int64_t rs, int64_t ks, int splits, double *__restrict__ W)
+{
+    __shared__ __align__(16) float As[kLds], Bs[kLds];
+    const int t = threadIdx.x, ty = t >> 4, tx = t & 15, i0 = blockIdx.y * kTile, j0 = blockIdx.x * kTile;
+    const int steps = (K + kTK - 1) / kTK, z = blockIdx.z;
+    const int s0 = (int)((int64_t)steps * z / splits), s1 = (int)((int64_t)steps * (z + 1) / splits);
+    double acc[4][4] = {};
+    Tile<MODE> ta, tb;
+    for (int s = s0; s < s1; ++s) {
+        ta.load(t, P, rs, ks, i0, l, s * kTK, K);
+        tb.load(t, P, rs, ks, j0, l, s * kTK, K);
+        __syncthreads();  // the last step's tiles are no longer read
+        ta.store(t, As);
+        tb.store(t, Bs);
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < kTK; ++k) {
+            double a[4], b[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[e] = MODE == LD_MC ? As[k * kPM + ty * 4 + e] : As[(ty * 4 + e) * kPK + k];
+                b[e] = MODE == LD_MC ? Bs[k * kPM + tx * 4 + e] : Bs[(tx * 4 + e) * kPK + k];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int f = 0; f < 4; ++f) acc[e][f] += a[e] * b[f];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const int i = i0 + ty * 4 + e, j = j0 + tx * 4 + f;
+            if (i < l && j < l) W[((int64_t)z * l + i) * l + j] = acc[e][f];
+        }
+}
+
+__global__ void __launch_bounds__(256)
+k_gram_sum(int ll, int splits, const double *__restrict__ W, double *__restrict__ G)
+{
+    const int o = blockIdx.x * 256 + threadIdx.x;
+    if (o >= ll) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) s += W[(int64_t)z * ll + o];
+    G[o] = s;
+}
+
 // Column means of Y (N x D, leading dimension ld) and Y -= mean: FP64 sums
 // of `per` rows each (part[chunk * D + j]), added in order.
 __global__ void __launch_bounds__(256)
@@ -239,14 +298,26 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t x)
     return x ^ (x >> 31);
 }
 
-__global__ void __launch_bounds__(256) k_gauss(int64_t len, uint64_t seed, float *__restrict__ out)
+__device__ __forceinline__ double gauss(uint64_t seed, int64_t t)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= len) return;
     const uint64_t r = splitmix64(seed ^ splitmix64((uint64_t)t));
     const double u1 = ((r >> 11) + 1.0) * (1.0 / 9007199254740993.0);  // (0, 1]
     const double u2 = (double)(splitmix64(r) >> 11) * (1.0 / 9007199254740992.0);
-    out[t] = (float)(sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2));
+    return sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2);
+}
+
+__global__ void __launch_bounds__(256) k_gauss(int64_t len, uint64_t seed, float *__restrict__ out)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t < len) out[t] = (float)gauss(seed, t);
+}
+
+// A random vector of about unit length: out[t * stride] for t < len.
+__global__ void __launch_bounds__(256)
+k_gauss_unit(int64_t len, int64_t stride, uint64_t seed, float *__restrict__ out)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t < len) out[t * stride] = (float)(gauss(seed, t) / sqrt((double)len));
 }
 
 // y_i += v (row-broadcast add): Y (N x D, ld).
@@ -332,11 +403,11 @@ k_jacobi(int l, int L, int round, const double *__restrict__ S, double *__restri
 }
 
 __global__ void __launch_bounds__(256)
-k_jacobi_init(int l, const float *__restrict__ G, double *__restrict__ S, double *__restrict__ V)
+k_jacobi_init(int l, const double *__restrict__ G, double *__restrict__ S, double *__restrict__ V)
 {
     const int n = blockIdx.x * 256 + threadIdx.x;
     if (n >= l * l) return;
-    S[n] = (double)G[n];
+    S[n] = G[n];
     V[n] = n / l == n % l ? 1.0 : 0.0;
 }
 
@@ -414,47 +485,61 @@ int gemm(hipStream_t st, int M, int N, int K, const float *A, int64_t a_rs, int6
 
 // ---- host-side small dense factorizations (l x l, row-major) ----
 
-// Lower Cholesky G = L L' of FP32 products.  A pivot at their rounding level
-// (rank loss) is replaced by the largest diagonal entry: the dependent column
-// then fades by that much instead of being scaled up to overflow.
-void chol_lower(std::vector<double> &G, int l)
+// Lower Cholesky G = L L' of an FP64 Gram matrix, over G.  A column whose
+// pivot is at the rounding level of the products (1e-14 of the largest
+// diagonal entry: a singular value under 1e-7 of the largest) has no
+// direction of its own left: it goes to `lost` and its row and column of L
+// are the identity's.  Returns the smallest other pivot over the largest
+// diagonal entry.
+double chol_lower(std::vector<double> &G, int l, std::vector<int> &lost)
 {
-    double scale = 0.0;
+    double scale = 0.0, least = 1.0;
     for (int i = 0; i < l; ++i) scale = std::max(scale, G[(size_t)i * l + i]);
-    if (!(scale > 0.0)) scale = 1.0;
-    const double floor_ = scale * 2.4e-7;  // 4 u of FP32
+    lost.clear();
     for (int j = 0; j < l; ++j) {
         double d = G[(size_t)j * l + j];
         for (int k = 0; k < j; ++k) d -= G[(size_t)j * l + k] * G[(size_t)j * l + k];
-        d = std::sqrt(d > floor_ ? d : scale);
+        const bool gone = !(d > 1e-14 * scale);
+        if (gone) {
+            lost.push_back(j);
+            for (int k = 0; k < j; ++k) G[(size_t)j * l + k] = 0.0;
+            d = 1.0;
+        } else {
+            least = std::min(least, d / scale);
+        }
+        d = std::sqrt(d);
         G[(size_t)j * l + j] = d;
         for (int i = j + 1; i < l; ++i) {
             double s = G[(size_t)i * l + j];
             for (int k = 0; k < j; ++k) s -= G[(size_t)i * l + k] * G[(size_t)j * l + k];
-            G[(size_t)i * l + j] = s / d;
+            G[(size_t)i * l + j] = gone ? 0.0 : s / d;
         }
         for (int k = j + 1; k < l; ++k) G[(size_t)j * l + k] = 0.0;
     }
+    return least;
 }
 
-// Inverse of a lower-triangular matrix (forward substitution per column).
+// Inverse of a lower-triangular matrix (forward substitution, a row of the
+// inverse at a time).
 std::vector<double> inv_lower(const std::vector<double> &L, int l)
 {
     std::vector<double> X((size_t)l * l, 0.0);
-    for (int c = 0; c < l; ++c) {
-        for (int i = c; i < l; ++i) {
-            double s = (i == c) ? 1.0 : 0.0;
-            for (int k = c; k < i; ++k) s -= L[(size_t)i * l + k] * X[(size_t)k * l + c];
-            X[(size_t)i * l + c] = s / L[(size_t)i * l + i];
+    for (int i = 0; i < l; ++i) {
+        double *x = X.data() + (size_t)i * l;
+        x[i] = 1.0;
+        for (int k = 0; k < i; ++k) {
+            const double f = L[(size_t)i * l + k], *y = X.data() + (size_t)k * l;
+            for (int c = 0; c <= k; ++c) x[c] -= f * y[c];
         }
+        for (int c = 0; c <= i; ++c) x[c] /= L[(size_t)i * l + i];
     }
     return X;
 }
 
 // Eigenvalues (descending) and eigenvectors (columns of the row-major V) of
-// the symmetric l x l FP32 matrix G, by k_jacobi; dev: 3 l^2 + 2 doubles of
+// the symmetric l x l matrix G, by k_jacobi; dev: 3 l^2 + 2 doubles of
 // device scratch.
-int sym_eig_device(int l, const float *G, double *dev, std::vector<double> &w, std::vector<double> &V, hipStream_t st)
+int sym_eig_device(int l, const double *G, double *dev, std::vector<double> &w, std::vector<double> &V, hipStream_t st)
 {
     const size_t ll = (size_t)l * l;
     double *S = dev, *T = dev + ll, *Vd = dev + 2 * ll, *off = dev + 3 * ll;
@@ -586,9 +671,10 @@ int pca_fit(float *Y, int64_t N, int64_t D, int64_t ld, int32_t k, int32_t overs
     const int l = (int)std::min<int64_t>(std::min<int64_t>(k + oversample, N), D);
     if (k > l || l > 1024 || N >= ((int64_t)1 << 31) || D >= ((int64_t)1 << 31)) return UV_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    // one allocation: Om and W (D x l), Z (N x l), G and R (l x l), Bm (l x
-    // D), Tm (max(N, D) x l), the centring's partial sums, the eigen-decomposition's
-    // matrices and the products' workspace (a product is split while it has fewer than 1024 blocks of C)
+    // one allocation: Om and W (D x l), Z (N x l), G (l x l, FP64) and R (l x
+    // l), Bm (l x D), Tm (max(N, D) x l), the centring's partial sums, the
+    // eigen-decomposition's matrices and the products' workspace (a product is
+    // split while it has fewer than 1024 blocks of C)
     const int per = (int)std::max<int64_t>(64, (N + 1023) / 1024), chunks = (int)((N + per - 1) / per);
     const size_t nl = (size_t)N * l, dl = (size_t)D * l, ll = (size_t)l * l;
     const size_t wlen = (size_t)2048 * kTile * kTile;
@@ -599,38 +685,72 @@ int pca_fit(float *Y, int64_t N, int64_t D, int64_t ld, int32_t k, int32_t overs
         len += (floats + 63) / 64 * 64;
         return at;
     };
-    const size_t oOm = room(dl), oZ = room(nl), oW = room(dl), oG = room(ll), oR = room(ll), oB = room(dl),
+    const size_t oOm = room(dl), oZ = room(nl), oW = room(dl), oG = room(2 * ll), oR = room(ll), oB = room(dl),
                  oT = room(std::max(nl, dl)), oP = room(2 * (size_t)chunks * D), oE = room(6 * ll + 4), oS = room(wlen);
     if (uv::dev_malloc(&base, sizeof(float) * len) != hipSuccess) return UV_ENOMEM;
-    float *Om = base + oOm, *Z = base + oZ, *W = base + oW, *G = base + oG, *R = base + oR, *Bm = base + oB,
-          *Tm = base + oT;
-    double *part = (double *)(base + oP), *eig = (double *)(base + oE);
+    float *Om = base + oOm, *Z = base + oZ, *W = base + oW, *R = base + oR, *Bm = base + oB, *Tm = base + oT;
+    double *G = (double *)(base + oG), *part = (double *)(base + oP), *eig = (double *)(base + oE);
     const GemmWork work{base + oS, wlen};
     auto cleanup = [&]() { (void)hipFree(base); };
     int rc = UV_OK;
-    std::vector<float> gh((size_t)l * l), rh((size_t)l * l);
-    std::vector<double> gd((size_t)l * l);
-    // orthonormalize the columns of X (rows x l, row-major): X <- X R^{-1}
-    // with G = X'X = L L', R = L'  (Cholesky QR; applied twice)
-    auto orth = [&](float *X, int64_t rows) -> int {
-        for (int pass = 0; pass < 2; ++pass) {
-            int r = gemm(st, l, l, (int)rows, X, 1, l, X, l, 1, G, l, 1.f, 0.f, work);
+    std::vector<float> rh(ll);
+    std::vector<double> gd(ll);
+    std::vector<int> lost;
+    uint64_t drawn = 0;  // random columns so far
+    // FP64 Gram matrix of c vectors (vector i, element e at X[i * rs + e * es])
+    // into G and gd; whether it is finite
+    auto gram = [&](const float *X, int c, int64_t rs, int64_t es, int64_t rows, bool &finite) -> int {
+        const unsigned g = nblk(c, kTile);
+        const int steps = (int)((rows + kTK - 1) / kTK);
+        const int64_t most = (int64_t)(wlen / 2) / ((int64_t)c * c);  // at least four for c = 1024
+        const int splits = (int)std::max<int64_t>(1, std::min<int64_t>({(512 + g * g - 1) / (g * g), steps / 4, most}));
+        double *sums = (double *)(base + oS);
+        if (rs == 1) k_gram<LD_MC><<<dim3(g, g, splits), 256, 0, st>>>(c, (int)rows, X, rs, es, splits, sums);
+        else k_gram<LD_KC><<<dim3(g, g, splits), 256, 0, st>>>(c, (int)rows, X, rs, es, splits, sums);
+        k_gram_sum<<<nblk((int64_t)c * c, 256), 256, 0, st>>>(c * c, splits, sums, G);
+        const size_t cc = (size_t)c * c;
+        if (hipGetLastError() != hipSuccess ||
+            hipMemcpyAsync(gd.data(), G, sizeof(double) * cc, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return UV_EHIP;
+        finite = true;
+        for (size_t t = 0; t < cc; ++t) finite = finite && std::isfinite(gd[t]);
+        return UV_OK;
+    };
+    // Orthonormalizes c vectors of length rows, the columns of a row-major
+    // rows x c matrix or (`byrow`) the rows of a c x rows one: X <- X L^{-T}
+    // with X'X = L L' (Cholesky QR), twice at least, until the Gram matrix was
+    // that of well-conditioned vectors.  A vector without a direction of its
+    // own is replaced by a random one, which the next pass makes orthogonal to
+    // the others.  Samples with NaN or Inf leave NaN.
+    auto orth = [&](float *X, int c, int64_t rows, bool byrow) -> int {
+        for (int pass = 0; pass < 8; ++pass) {
+            bool finite = false;
+            int r = byrow ? gram(X, c, rows, 1, rows, finite) : gram(X, c, 1, c, rows, finite);
             if (r != UV_OK) return r;
-            if (hipMemcpyAsync(gh.data(), G, sizeof(float) * l * l, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                hipStreamSynchronize(st) != hipSuccess)
+            if (byrow && pass == 0 && finite) {  // the rows of the basis mostly are orthonormal as they come
+                double off = 0.0;
+                for (int i = 0; i < c; ++i)
+                    for (int j = 0; j < c; ++j) off = std::max(off, std::fabs(gd[(size_t)i * c + j] - (i == j ? 1.0 : 0.0)));
+                if (off <= 4e-6) return UV_OK;
+            }
+            const double least = finite ? chol_lower(gd, c, lost) : 1.0;
+            const std::vector<double> Li = finite ? inv_lower(gd, c) : std::vector<double>((size_t)c * c, std::nan(""));
+            for (int i = 0; i < c; ++i)  // R^{-1} = (L^{-1})' for columns, L^{-1} for rows
+                for (int j = 0; j < c; ++j) rh[(size_t)i * c + j] = (float)(byrow ? Li[(size_t)i * c + j] : Li[(size_t)j * c + i]);
+            if (hipMemcpyAsync(R, rh.data(), sizeof(float) * c * c, hipMemcpyHostToDevice, st) != hipSuccess)
                 return UV_EHIP;
-            for (size_t t = 0; t < gd.size(); ++t) gd[t] = gh[t];
-            chol_lower(gd, l);
-            std::vector<double> Li = inv_lower(gd, l);
-            for (int i = 0; i < l; ++i)  // R^{-1} = (L^{-1})'
-                for (int j = 0; j < l; ++j) rh[(size_t)i * l + j] = (float)Li[(size_t)j * l + i];
-            if (hipMemcpyAsync(R, rh.data(), sizeof(float) * l * l, hipMemcpyHostToDevice, st) != hipSuccess)
-                return UV_EHIP;
-            // X <- X R^{-1} through the scratch Tm (max(N, D) x l)
-            r = gemm(st, (int)rows, l, l, X, l, 1, R, l, 1, Tm, l, 1.f, 0.f, work);
+            // through the scratch Tm (max(N, D) x l)
+            r = byrow ? gemm(st, c, (int)rows, c, R, c, 1, X, rows, 1, Tm, rows, 1.f, 0.f, work)
+                      : gemm(st, (int)rows, c, c, X, c, 1, R, c, 1, Tm, c, 1.f, 0.f, work);
             if (r != UV_OK) return r;
-            if (hipMemcpyAsync(X, Tm, sizeof(float) * rows * l, hipMemcpyDeviceToDevice, st) != hipSuccess)
+            if (hipMemcpyAsync(X, Tm, sizeof(float) * rows * c, hipMemcpyDeviceToDevice, st) != hipSuccess)
                 return UV_EHIP;
+            if (!finite) return UV_OK;
+            for (int j : lost)
+                k_gauss_unit<<<nblk(rows, 256), 256, 0, st>>>(rows, byrow ? 1 : c, seed + 0x632be59bd9b4e019ull * ++drawn,
+                                                              X + (byrow ? j * rows : j));
+            if (pass > 0 && lost.empty() && least >= 0.01) break;
         }
         return UV_OK;
     };
@@ -643,17 +763,18 @@ int pca_fit(float *Y, int64_t N, int64_t D, int64_t ld, int32_t k, int32_t overs
         if (hipGetLastError() != hipSuccess) { rc = UV_EHIP; break; }
         if ((rc = gemm(st, (int)N, l, (int)D, Y, ld, 1, Om, l, 1, Z, l, 1.f, 0.f, work)) != UV_OK) break;   // Z = Y Om
         for (int q = 0; q < power_iters && rc == UV_OK; ++q) {
-            if ((rc = orth(Z, N)) != UV_OK) break;
+            if ((rc = orth(Z, l, N, false)) != UV_OK) break;
             if ((rc = gemm(st, (int)D, l, (int)N, Y, 1, ld, Z, l, 1, W, l, 1.f, 0.f, work)) != UV_OK) break;  // W = Y'Z
-            if ((rc = orth(W, D)) != UV_OK) break;
+            if ((rc = orth(W, l, D, false)) != UV_OK) break;
             rc = gemm(st, (int)N, l, (int)D, Y, ld, 1, W, l, 1, Z, l, 1.f, 0.f, work);                          // Z = Y W
         }
         if (rc != UV_OK) break;
-        if ((rc = orth(Z, N)) != UV_OK) break;
+        if ((rc = orth(Z, l, N, false)) != UV_OK) break;
         if ((rc = gemm(st, l, (int)D, (int)N, Z, 1, l, Y, ld, 1, Bm, D, 1.f, 0.f, work)) != UV_OK) break;   // Bm = Z'Y
-        if ((rc = gemm(st, l, l, (int)D, Bm, D, 1, Bm, 1, D, G, l, 1.f, 0.f, work)) != UV_OK) break;        // G = Bm Bm'
-        std::vector<double> w(l), V((size_t)l * l);
-        if ((rc = sym_eig_device(l, G, eig, w, V, st)) != UV_OK) break;
+        bool finite = false;
+        if ((rc = gram(Bm, l, D, 1, D, finite)) != UV_OK) break;                                             // G = Bm Bm'
+        std::vector<double> w(l, std::nan("")), V(ll, std::nan(""));
+        if (finite && (rc = sym_eig_device(l, G, eig, w, V, st)) != UV_OK) break;
         // basis row c = (V[:, c]' Bm) / sigma_c for the top k
         std::vector<float> P((size_t)k * l);
         for (int c = 0; c < k; ++c) {
@@ -664,6 +785,7 @@ int pca_fit(float *Y, int64_t N, int64_t D, int64_t ld, int32_t k, int32_t overs
         }
         if (hipMemcpyAsync(R, P.data(), sizeof(float) * k * l, hipMemcpyHostToDevice, st) != hipSuccess) { rc = UV_EHIP; break; }
         rc = gemm(st, k, (int)D, l, R, l, 1, Bm, D, 1, basis, D, 1.f, 0.f, work);
+        if (rc == UV_OK) rc = orth(basis, k, D, true);  // small singular values leave their rows rough, zeros none at all
         if (rc == UV_OK && hipStreamSynchronize(st) != hipSuccess) rc = UV_EHIP;
     } while (false);
     if (hipStreamSynchronize(st) != hipSuccess && rc == UV_OK) rc = UV_EHIP;

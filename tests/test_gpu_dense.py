@@ -80,3 +80,78 @@ def test_pca_spans_and_odd_sizes(N, D, k, over):
     back = (Y - m) @ B.T @ B
     want = (Uo[:, :k] * so[:k]) @ Vo[:k]
     assert np.linalg.norm(back - want) <= 2e-3 * np.linalg.norm(want) + 1e-3
+
+
+def _spectrum(N, D, s, seed):
+    """Samples whose centered singular values are s (and a mean), in FP32; the values are made again in FP64."""
+    rng = np.random.default_rng(seed)
+    U = rng.standard_normal((N, s.size))
+    U = np.linalg.qr(U - U.mean(0))[0]
+    V = np.linalg.qr(rng.standard_normal((D, s.size)))[0]
+    return ((U * s) @ V.T + rng.standard_normal(D)).astype(np.float32)
+
+
+def _fit(Y, k, over):
+    import torch
+    from paper_2203_05027_amd import learn
+    mean, basis, sv = learn.pca_fit(torch.from_numpy(Y).cuda(), k, oversample=over)
+    return Y - mean.cpu().numpy().astype(np.float64), basis.cpu().numpy().astype(np.float64), sv
+
+
+# FP32 samples and products: an absolute error of some tens of units of the
+# largest singular value's rounding
+SV_TOL = 64 * U32
+
+
+@pytest.mark.parametrize("decades", [3.4, 4.2])
+@pytest.mark.parametrize("N,D,k,over", [(300, 8, 8, 32), (60, 200, 8, 0), (100, 100, 4, 0), (500, 400, 48, 16)])
+def test_pca_keeps_small_directions(N, D, k, over, decades):
+    """Singular values over three and four decades: each of them, its
+    direction and orthonormal rows."""
+    s = np.logspace(0.0, -decades, k) * np.sqrt(N)
+    Yc, B, sv = _fit(_spectrum(N, D, s, N + k), k, over)
+    _, so, Vo = np.linalg.svd(Yc, full_matrices=False)
+    assert np.abs(sv - so[:k]).max() <= SV_TOL * so[0]
+    assert np.abs(B @ B.T - np.eye(k)).max() <= 1e-5
+    cos = np.abs((B * Vo[:k]).sum(1))
+    # mixing with its neighbours: the error over the gap to the next value
+    gap = np.minimum(so[:k] - np.append(so[1:k], 0.0), np.append(np.inf, so[: k - 1] - so[1:k]))
+    assert (cos >= 1.0 - (SV_TOL * so[0] / gap) ** 2 - 1e-5).all(), (cos, gap / so[0])
+
+
+@pytest.mark.parametrize("N,D,rank,noise,k,over", [(300, 200, 10, 0.0, 32, 32), (300, 200, 32, 0.0, 64, 32),
+                                                   (300, 200, 10, 1e-3, 32, 32), (40, 50, 10, 0.0, 32, 32),
+                                                   (20, 30, 0, 0.0, 4, 3), (1, 7, 0, 0.0, 1, 3), (2, 5, 1, 0.0, 2, 3),
+                                                   (64, 64, 63, 0.0, 64, 0)])
+def test_pca_beyond_the_rank(N, D, rank, noise, k, over):
+    """More components than the samples have directions: orthonormal rows all
+    the same, the samples come back from them, and zeros as singular values."""
+    rng = np.random.default_rng(N + D + rank)
+    Y = (rng.standard_normal((N, rank)) @ rng.standard_normal((rank, D)) if rank else np.zeros((N, D)))
+    Y = (Y + noise * rng.standard_normal((N, D)) + rng.standard_normal(D)).astype(np.float32)
+    Yc, B, sv = _fit(Y, k, over)
+    _, so, Vo = np.linalg.svd(Yc, full_matrices=False)
+    top = max(so[0], 1e-30)
+    assert np.abs(B @ B.T - np.eye(k)).max() <= 1e-5
+    want = np.zeros(k)
+    want[: min(k, so.size)] = so[:k]
+    assert np.abs(sv - want).max() <= SV_TOL * top + 1e-5 * np.abs(Y).max()
+    best = np.sqrt((so[k:] ** 2).sum())  # what no k directions can hold
+    assert np.linalg.norm(Yc - Yc @ B.T @ B) <= 1.05 * best + 1e-5 * np.linalg.norm(Yc) + 1e-5 * np.abs(Y).max()
+
+
+@pytest.mark.parametrize("scale", [1e-15, 1e15])
+def test_pca_of_very_small_and_large_samples(scale):
+    """Squares that leave FP32's range."""
+    Y = _spectrum(90, 60, np.logspace(0.0, -2.0, 6) * 9.0, 8)
+    Yc, B, sv = _fit((Y * np.float32(scale)).astype(np.float32), 6, 8)
+    so = np.linalg.svd(Yc, compute_uv=False)
+    assert np.abs(sv - so[:6]).max() <= SV_TOL * so[0]
+    assert np.abs(B @ B.T - np.eye(6)).max() <= 1e-5
+
+
+def test_pca_of_samples_with_nan_says_so():
+    Y = _spectrum(90, 60, np.ones(6), 9)
+    Y[3, 5] = np.nan
+    _, B, sv = _fit(Y, 6, 8)
+    assert np.isnan(sv).all() and np.isnan(B).all()
