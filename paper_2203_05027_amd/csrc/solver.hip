@@ -2357,13 +2357,23 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
         int dev = 0, cus = 0;
         UV_TRY(hipGetDevice(&dev));
         UV_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        p.per = std::max(1, cus / S);
-        p.wseg = dalloc<int>(s, (size_t)S * (p.per + 1));
+        std::vector<int64_t> entries(S, nnz);
+        if (S > 1) {
+            std::vector<int> at((size_t)S + 1);
+            for (int q = 0; q <= S; ++q)
+                UV_TRY(hipMemcpyAsync(&at[q], ptr + (size_t)q * nr, 4, hipMemcpyDeviceToHost, st));
+            UV_TRY(hipStreamSynchronize(st));
+            for (int q = 0; q < S; ++q) entries[q] = (int64_t)at[q + 1] - at[q];
+        }
+        const std::vector<StagedShare> shares = staged_shares(cus, S, nr, p.L * kStagedE, entries);
+        p.grid = (int)shares.size();
+        p.share = dalloc<StagedShare>(s, shares.size());
         p.place = dalloc<unsigned short>(s, nnz);
         void *part = dalloc<char>(s, ts * (size_t)(pass == 0 ? 2 * S : S) * nr);
-        if (!p.wseg || !p.place || !part) return UV_ENOMEM;
+        if (!p.share || !p.place || !part) return UV_ENOMEM;
         (pass == 0 ? s->P_row : s->P_col) = part;
-        k_staged_split<<<blocks_for(S * (p.per + 1), kWG), kWG, 0, st>>>(nr, S, p.per, ptr, p.wseg);
+        UV_TRY(hipMemcpy(p.share, shares.data(), sizeof(StagedShare) * shares.size(), hipMemcpyHostToDevice));
+        k_staged_split<<<blocks_for(p.grid, kWG), kWG, 0, st>>>(p.grid, nr, p.L * kStagedE, ptr, p.share);
         k_staged_place<<<blocks_for(nnz, kWG), kWG, 0, st>>>(nnz, idx, S, p.width, p.place);
         UV_TRY(hipGetLastError());
         p.S = S;

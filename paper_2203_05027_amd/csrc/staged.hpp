@@ -19,10 +19,11 @@
 // slower (neighbouring segments share their first and last lines).
 #pragma once
 
-
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <utility>
+#include <vector>
 
 #include "common.hpp"
 #include "setup.hpp"
@@ -34,35 +35,77 @@ constexpr int kStagedBytes = 160000;  // LDS for the staged part
 constexpr int kStagedParts = 8;
 constexpr int kStagedE = 8;           // entries in flight per lane
 
+// A workgroup's share: segments s0..s1-1 of a part.
+struct StagedShare {
+    int part, s0, s1, pad;
+};
+
 // One direction's plan (device pointers).
 struct StagedPlan {
-    int nseg = 0, len = 0, S = 0, width = 0, L = 4, per = 0;  // per: workgroups a part
+    int nseg = 0, len = 0, S = 0, width = 0, L = 4, grid = 0;
     const int *off = nullptr;        // S * nseg + 1 offsets (the matrix's own with one part)
-    int *wseg = nullptr;             // S * (per + 1) first segments
+    StagedShare *share = nullptr;    // a workgroup's share (grid of them)
     unsigned short *place = nullptr;
     const double *val64 = nullptr;
     const void *val = nullptr;
     bool on() const { return S > 0; }
 };
 
-// First segments of each part's workgroups, equal shares of the entries.
+// Shares of equal work: a segment's entries and `each` more for the segment
+// itself (a lane group takes a whole chunk of L * kStagedE entries for the
+// shortest one).  In: part, s0 = share i of s1 of the part's; out: its segments.
+// Shares of the entries alone gave a run of short segments to one workgroup:
+// 1e4 x 3e4 with 3e6 entries, column pass 14 us, and 333 us with 1e4 slack
+// columns after them, 1075 us with 1.3e5 empty ones (lane groups 30 us); now 17
+// and 21 us.
 __global__ void __launch_bounds__(kWG)
-k_staged_split(int nseg, int S, int per, const int *__restrict__ off, int *__restrict__ wseg)
+k_staged_split(int grid, int nseg, int each, const int *__restrict__ off, StagedShare *__restrict__ share)
 {
     const int t = blockIdx.x * kWG + threadIdx.x;
-    if (t >= S * (per + 1)) return;
-    const int p = t / (per + 1), i = t % (per + 1);
-    const int *o = off + (size_t)p * nseg;
-    int lo = 0, hi = nseg;
-    if (i == 0) hi = 0;
-    else if (i == per) lo = nseg;
-    const int64_t want = o[0] + ((int64_t)o[nseg] - o[0]) * i / per;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (o[mid] >= want) hi = mid;
-        else lo = mid + 1;
+    if (t >= grid) return;
+    StagedShare &w = share[t];
+    const int *o = off + (size_t)w.part * nseg;
+    const int i = w.s0, per = w.s1;
+    const int64_t all = (int64_t)o[nseg] - o[0] + (int64_t)nseg * each;
+    auto first = [&](int q) {
+        int lo = 0, hi = nseg;
+        if (q == 0) hi = 0;
+        else if (q == per) lo = nseg;
+        const int64_t want = o[0] + all * q / per;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (o[mid] + (int64_t)mid * each >= want) hi = mid;
+            else lo = mid + 1;
+        }
+        return lo;
+    };
+    w.s0 = first(i);
+    w.s1 = first(i + 1);
+}
+
+// The workgroups of the parts, as many for each as it has of the work (at
+// least one), the parts' taken in turn; `entries` of each part.  The entries
+// may lie in few of the parts: 7e4 x 3e4 with 3e6 entries in the first seventh
+// of the rows, column pass 34 us with as many workgroups for each of the four
+// parts (lane groups 28 us), 21 us so.
+inline std::vector<StagedShare> staged_shares(int cus, int S, int nseg, int each, const std::vector<int64_t> &entries)
+{
+    std::vector<int> per(S, 1);
+    std::vector<double> work(S);
+    for (int p = 0; p < S; ++p) work[p] = (double)entries[p] + (double)nseg * each;
+    for (int left = cus - S; left > 0; --left) {  // the next one where the shares are largest
+        int at = 0;
+        for (int p = 1; p < S; ++p)
+            if (work[p] / per[p] > work[at] / per[at]) at = p;
+        per[at] += 1;
     }
-    wseg[t] = lo;
+    std::vector<std::pair<double, StagedShare>> w;
+    for (int p = 0; p < S; ++p)
+        for (int i = 0; i < per[p]; ++i) w.push_back({(i + 0.5) / per[p], StagedShare{p, i, per[p], 0}});
+    std::stable_sort(w.begin(), w.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    std::vector<StagedShare> out;
+    for (const auto &e : w) out.push_back(e.second);
+    return out;
 }
 
 // Place of each entry in its part (k_slab_count's parts).
@@ -77,18 +120,18 @@ k_staged_place(int nnz, const int *__restrict__ idx, int S, int w, unsigned shor
 // sum) is called for part 0 of a one-part plan, else out takes the partials.
 template <typename T, typename TV, typename G, int L, typename E>
 __global__ void __launch_bounds__(kStagedThreads)
-k_staged(int nseg, int len, int S, int width, int per, const int *__restrict__ off, const int *__restrict__ wseg,
+k_staged(int nseg, int len, int width, const int *__restrict__ off, const StagedShare *__restrict__ share,
          const unsigned short *__restrict__ place, const TV *__restrict__ val, const G *__restrict__ vec, E epi,
          const int *skip)
 {
     if (skip && *skip) return;
     extern __shared__ __align__(16) unsigned char staged_lds[];
     G *xs = (G *)staged_lds;
-    const int p = blockIdx.x % S, i = blockIdx.x / S;
+    const StagedShare own = share[blockIdx.x];
+    const int p = own.part, s1 = own.s1;
     const int *o = off + (size_t)p * nseg;
-    const int s1 = wseg[p * (per + 1) + i + 1];
     const int lane = threadIdx.x & (L - 1);
-    int s = wseg[p * (per + 1) + i] + threadIdx.x / L;
+    int s = own.s0 + threadIdx.x / L;
     const int cnt = min(width, len - p * width);
     constexpr int EL = L * kStagedE, step = kStagedThreads / L;
     // A lane group's chunks in order: the next chunk's entries (of this
@@ -153,9 +196,9 @@ k_staged(int nseg, int len, int S, int width, int per, const int *__restrict__ o
 template <typename T, typename TV, typename G, typename E>
 void staged(const StagedPlan &p, const TV *val, const G *vec, E epi, const int *skip, hipStream_t st)
 {
-    const unsigned grid = (unsigned)(p.S * p.per);
+    const unsigned grid = (unsigned)p.grid;
     const size_t lds = (size_t)p.width * sizeof(G);
-#define UV_STAGED_ARGS p.nseg, p.len, p.S, p.width, p.per, p.off, p.wseg, p.place, val, vec, epi, skip
+#define UV_STAGED_ARGS p.nseg, p.len, p.width, p.off, p.share, p.place, val, vec, epi, skip
     switch (p.L) {
     case 4: k_staged<T, TV, G, 4, E><<<grid, kStagedThreads, lds, st>>>(UV_STAGED_ARGS); break;
     case 8: k_staged<T, TV, G, 8, E><<<grid, kStagedThreads, lds, st>>>(UV_STAGED_ARGS); break;

@@ -78,3 +78,45 @@ def test_staged_product_matches_oracle(kind, precision):
     ro = orc.residuals()
     for k in ("r_prim", "r_dual", "r_gap", "pobj", "dobj", "res_ax_b", "prim_inf", "dual_inf", "scale_p", "scale_d"):
         assert abs(r28[k] - ro[k]) <= 1e-11 * max(abs(ro[k]), 1e-3), (k, r28[k], ro[k])
+
+
+def _with(kind, B):
+    """B with short or empty segments beside its long ones."""
+    m, n = B.shape
+    if kind == "slack columns":
+        return sp.hstack([B, sp.eye(m, format="csr")])
+    if kind == "empty columns":
+        return sp.hstack([B, sp.csr_matrix((m, 130_000))])
+    if kind == "short rows":
+        return sp.vstack([B, sp.csr_matrix((np.ones(60_000), (np.arange(60_000), np.arange(60_000) % n)), shape=(60_000, n))])
+    return B
+
+
+@pytest.mark.parametrize("kind", ["slack columns", "empty columns", "short rows"])
+def test_short_segments_share_the_workgroups(kind):
+    """Segments of one entry or none after ones of a hundred, and parts that
+    hold nearly all or none of the entries: the oracle's iterates, and passes
+    at most three times those without them (shares of the entries alone took
+    4 to 75 times)."""
+    g = np.random.default_rng(1)
+    B = sp.csr_matrix((g.standard_normal(3_000_000), (g.integers(0, 10_000, 3_000_000), np.repeat(np.arange(30_000), 100))),
+                      shape=(10_000, 30_000))
+    ms = {}
+    for k in ("plain", kind):
+        A = _with(k, B).tocsr()
+        A.sort_indices()
+        rng = np.random.default_rng(3)
+        m, n = A.shape
+        inst = dict(m=m, n=n, nnz=A.nnz, row_ptr=A.indptr.astype(np.int64), col_idx=A.indices.astype(np.int32), val=A.data,
+                    b=A @ np.maximum(rng.standard_normal(n), 0.0), c=A.T @ rng.standard_normal(m) + rng.uniform(0, 1, n),
+                    n_orth=n, soc_sizes=np.zeros(0, np.int32))
+        with Solver.from_instance(inst, eps=0.0) as s:
+            s.iterate(12)
+            g = s.solution()
+            ms[k] = min(max(s.time_kernels(20)) for _ in range(3))
+    orc = oracle.Oracle.from_instance(inst)
+    orc.iterate(12)
+    o = orc.state()
+    sys.__stderr__.write(f"[gpu-test] staged {kind}: slower pass {ms}\n")
+    assert max(rel(g[k], o[k]) for k in g) <= 1e-9
+    assert ms[kind] <= 3.0 * ms["plain"], ms
