@@ -354,6 +354,23 @@ bool bin_sum_ready()
 // only 11 entries long, still 724 / 1261 and 412 / 854.
 inline bool bins_pay(int S, int nseg, int nnz) { return (int64_t)nnz + (int64_t)2 * S * nseg >= 5600000; }
 
+// Device scratch of a plan's set-up, given back at its end.
+struct BinScratch {
+    std::vector<void *> held;
+    template <typename T>
+    T *get(size_t count)
+    {
+        T *p = nullptr;
+        if (uv::dev_malloc(&p, std::max<size_t>(count, 1) * sizeof(T)) != hipSuccess) return nullptr;
+        held.push_back(p);
+        return p;
+    }
+    ~BinScratch()
+    {
+        for (void *p : held) (void)hipFree(p);
+    }
+};
+
 enum BinBuilt { BIN_OK = 0, BIN_NO = 1, BIN_NOMEM = 2, BIN_HIP = 3 };  // BIN_NO: the matrix does not suit the plan
 
 // Builds the plan of a compressed matrix (nseg segments, ptr, idx, FP64
@@ -373,7 +390,8 @@ BinBuilt build_bins(int nseg, int len, int nnz, const int *ptr, const int *idx, 
     if (nnz < 1 || p.parts > kMaxParts) return BIN_NO;
 #define UV_BIN(expr) \
     if ((expr) != hipSuccess) return BIN_HIP
-    int longest = 0, *dl = (int *)alloc(4);
+    BinScratch tmp;
+    int longest = 0, *dl = tmp.get<int>(1);
     if (!dl) return BIN_NOMEM;
     UV_BIN(hipMemsetAsync(dl, 0, 4, st));
     k_bin_longest<<<blocks_for(nseg, kWG), kWG, 0, st>>>(nseg, ptr, dl);
@@ -385,9 +403,9 @@ BinBuilt build_bins(int nseg, int len, int nnz, const int *ptr, const int *idx, 
     const int64_t cells = (int64_t)p.groups * p.parts;
     if (cells >= (1 << 28)) return BIN_NO;
     p.gseg = (int *)alloc(4 * ((size_t)p.groups + 1));
-    int *cnt = (int *)alloc(4 * cells), *off = (int *)alloc(4 * (cells + 1)), *dest = (int *)alloc(4 * cells);
-    int *bsum = (int *)alloc(4 * (size_t)blocks_for(cells, 4 * kWG));
-    int *start = (int *)alloc(4 * ((size_t)p.parts + 1)), *adj = (int *)alloc(4 * (size_t)p.parts);
+    int *cnt = tmp.get<int>(cells), *off = tmp.get<int>(cells + 1), *dest = tmp.get<int>(cells);
+    int *bsum = tmp.get<int>((size_t)blocks_for(cells, 4 * kWG));
+    int *start = tmp.get<int>((size_t)p.parts + 1), *adj = tmp.get<int>((size_t)p.parts);
     p.pend = (int *)alloc(4 * (size_t)p.parts);
     p.shift = (int *)alloc(4 * cells);
     if (!p.gseg || !cnt || !off || !dest || !bsum || !start || !adj || !p.pend || !p.shift) return BIN_NOMEM;
