@@ -107,3 +107,21 @@ def test_standard_baseline_with_binned_products(kind):
     errs = {k: rel(g[k], o[k]) for k in ("x1", "x2", "lam", "nu", "delta")}
     sys.__stderr__.write(f"[gpu-test] standard binned {kind}: {errs}\n")
     assert max(errs.values()) <= 1e-9, errs
+
+
+def test_empty_rows_share_the_workgroups():
+    """A run of empty rows is not left to one workgroup: the passes take at
+    most twice the time without it (a group of entries alone: seventeen times)."""
+    inst = _instance("ragged")
+    more = dict(inst, m=inst["m"] + 900_000, b=np.append(inst["b"], np.zeros(900_000)),
+                row_ptr=np.append(inst["row_ptr"], np.full(900_000, inst["nnz"])))
+    ms, sol = [], []
+    for i in (inst, more):
+        with Solver.from_instance(i, eps=0.0) as s:
+            s.iterate(5)
+            sol.append(s.solution())
+            ms.append(min(s.time_kernels(20)[1] for _ in range(3)))
+    sys.__stderr__.write(f"[gpu-test] binned row pass without and with empty rows: {ms} ms\n")
+    for k in ("x", "z", "delta"):
+        assert rel(sol[1][k], sol[0][k]) <= 1e-12, k
+    assert ms[1] <= 2.0 * ms[0], ms
