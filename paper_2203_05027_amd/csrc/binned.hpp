@@ -12,8 +12,9 @@
 //               multiplies and writes the products group by group, so the
 //               run of one (part, group) pair is contiguous on both sides
 //   k_bin_sum   a workgroup reads its group's products, puts each at its
-//               entry's place in LDS (16 bits), and a thread per segment
-//               adds them in entry order and goes on with the update
+//               entry's place in LDS (16 bits), and a thread per segment (a
+//               wavefront for a long one) adds them in a fixed order and goes
+//               on with the update
 // What bounds it: streaming, 28 bytes an entry in FP64 (8 + 2 read, 8
 // written, 8 + 2 read) and 16 in FP32, against 12 (8) bytes and one random
 // 64-byte L2 request an entry of the slab product.  On the 1e6 x 2e6 LP (2e7
@@ -26,8 +27,7 @@
 // stores of the products 14-20 % slower (they then leave the Infinity Cache
 // before k_bin_sum reads them).
 // The order in which a run stores its entries is not fixed, but each product
-// is added at its entry's place, so results are bitwise reproducible (and
-// those of one running sum a segment, in entry order).
+// is added at its entry's place, so results are bitwise reproducible.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -48,6 +48,7 @@ constexpr int kMultThreads = 1024;
 constexpr int kSumThreads = 512;
 constexpr int kMaxParts = 1024;    // LDS counters of the set-up kernels
 constexpr int kGroupSegs = 5120;   // segments a group may hold
+constexpr int kLong = 64;          // entries from which a wavefront adds a segment
 constexpr unsigned kFirst = 0x8000u;  // flag of a run's first entry
 
 // A batch of k_bin_mult: the part, the run of its first entry (an index of
@@ -279,30 +280,45 @@ k_bin_sum(const int *__restrict__ ptr, const int *__restrict__ gseg, const unsig
         for (int u = 0; u < U; ++u)
             if (i + u * kSumThreads < cnt) ps[o[u]] = q[u];
     }
-    int s = s0 + threadIdx.x;
-    int a = 0, z = 0;
-    if (s < s1) {
-        a = ptr[s] - k0;
-        z = ptr[s + 1] - k0;
-        epi.load(s);
-    }
-    __syncthreads();
-    while (s < s1) {
-        T acc = 0;
-        for (int k = a; k < z; k += 4) {  // four LDS reads in flight, added one by one
-            T v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = ps[min(k + u, z - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc = k + u < z ? acc + v[u] : acc;
-        }
-        epi.put(s, z - a, acc);
-        s += kSumThreads;
+    const int lane = threadIdx.x & 63;
+    int s = s0 + threadIdx.x, a = 0, z = 0;
+    auto next = [&]() {
+        a = z = 0;
         if (s < s1) {
             a = ptr[s] - k0;
             z = ptr[s + 1] - k0;
             epi.load(s);
         }
+    };
+    next();
+    __syncthreads();
+    // A thread adds entry k in sum k mod 4 of its segment, four LDS reads in
+    // flight; the wavefront adds each long segment among its 64 (a thread took
+    // 150 us for 5000 entries while the group waited, and the rounding error of
+    // its one running sum grew with them).
+    for (int sb = s0 + (int)(threadIdx.x & ~63u); sb < s1; sb += kSumThreads) {
+        const bool chain = z - a <= kLong;
+        T p[4] = {0, 0, 0, 0};
+        if (chain)
+            for (int k = a; k < z; k += 4) {
+                T v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = ps[min(k + u, z - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p[u] = k + u < z ? p[u] + v[u] : p[u];
+            }
+        T acc = (p[0] + p[1]) + (p[2] + p[3]);
+        for (unsigned long long left = __ballot(!chain); left; left &= left - 1) {
+            const int j = __ffsll(left) - 1;
+            const int aj = __builtin_amdgcn_readlane(a, j), zj = __builtin_amdgcn_readlane(z, j);
+            T t = 0;
+            for (int k = aj + lane; k < zj; k += 64) t += ps[k];
+            t = uv::group_sum<64>(t);
+            if (lane == j) acc = t;
+        }
+        if (s < s1) epi.put(s, z - a, acc);
+        s += kSumThreads;
+        next();
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) epi.once();
 }

@@ -125,3 +125,23 @@ def test_empty_rows_share_the_workgroups():
     for k in ("x", "z", "delta"):
         assert rel(sol[1][k], sol[0][k]) <= 1e-12, k
     assert ms[1] <= 2.0 * ms[0], ms
+
+
+def test_long_segments_do_not_hold_their_group():
+    """Forty rows of 5000 entries among rows of nineteen: the row pass takes
+    at most 1.5 times the pass without them (a thread a row: four times)."""
+    inst = _instance("ragged")
+    rng = np.random.default_rng(76)
+    A = sp.csr_matrix((inst["val"], inst["col_idx"], inst["row_ptr"]), shape=(inst["m"], inst["n"]))
+    rows = np.repeat(np.arange(40) * 7_000, 5000)
+    cols = np.concatenate([rng.choice(inst["n"], size=5000, replace=False) for _ in range(40)])
+    D = (A + sp.csr_matrix((rng.standard_normal(rows.size) * 0.02, (rows, cols)), shape=A.shape)).tocsr()
+    D.sort_indices()
+    longer = dict(inst, row_ptr=D.indptr.astype(np.int64), col_idx=D.indices.astype(np.int32), val=D.data, nnz=D.nnz)
+    ms = []
+    for i in (inst, longer):
+        with Solver.from_instance(i, eps=0.0) as s:
+            s.iterate(5)
+            ms.append(min(s.time_kernels(20)[1] for _ in range(3)))
+    sys.__stderr__.write(f"[gpu-test] binned row pass without and with long rows: {ms} ms\n")
+    assert ms[1] <= 1.5 * ms[0], ms
