@@ -369,7 +369,11 @@ bool bin_sum_ready()
 // (FP64); 2.2e6 25.9 / 20.4, 4.3e6 30.9 / 30.0, 5.6e6 29.0 / 36.9, 9.6e6
 // 38.9 / 56.6 (mixed); at 6e7 entries and vectors of 15e6, whose runs are
 // only 11 entries long, still 724 / 1261 and 412 / 854.
-inline bool bins_pay(int S, int nseg, int nnz) { return (int64_t)nnz + (int64_t)2 * S * nseg >= 5600000; }
+// (Not at the end of the 32-bit range, where the set-up's strides would pass it.)
+inline bool bins_pay(int S, int nseg, int nnz)
+{
+    return (int64_t)nnz + (int64_t)2 * S * nseg >= 5600000 && nnz <= INT32_MAX - (1 << 20);
+}
 
 // Device scratch of a plan's set-up, given back at its end.
 struct BinScratch {

@@ -242,7 +242,7 @@ inline int staged_width(int len, int S) { return ((len + S - 1) / S + 3) / 4 * 4
 // 20.2).
 inline bool staged_pays(int S, int nseg, int nnz)
 {
-    return S > 0 && nnz >= 900000 && (int64_t)nnz >= (int64_t)10 * S * nseg;
+    return S > 0 && nnz >= 900000 && nnz <= INT32_MAX - (1 << 20) && (int64_t)nnz >= (int64_t)10 * S * nseg;
 }
 
 }  // namespace
