@@ -150,8 +150,9 @@ __device__ __forceinline__ void seg_sum2(int beg, int end, int lane, int L, cons
 // 16-bit numbers and one 8- or 16-byte load of their values.  A slice is as
 // wide as its longest segment (rounded up to two); the slots past a segment's
 // end hold the value 0 and the number `pad` (the gathered vector's length:
-// the sweep's vectors in LDS have a zero there).  A lane adds its entries in
-// order: the sums of one lane walking its segment.
+// the sweep's vectors in LDS have a zero there).  A lane adds its column's
+// entries in order, and its row's even and odd ones apart: the sums of one lane
+// walking the column and of two lanes walking the row.
 struct Slices {
     const int *ptr;               // first slot of every slice, all instances
     const unsigned *idx;          // pairs of numbers
@@ -177,7 +178,8 @@ struct Two {
 // 10000 LP with 6e4 entries alone, mixed (FP64), checks included: 44 (52) ->
 // 21 (28) us; streaming the entries 64 wide through LDS instead measured 46
 // (56) us.
-template <typename T, typename Op>
+// PAIR: the even and the odd entries are added apart.
+template <bool PAIR, typename T, typename Op>
 __device__ __forceinline__ void sell_pass(int wv, int nwv, int lane, int nseg, const int *__restrict__ sp,
                                           const unsigned *__restrict__ idx,
                                           const typename Two<T>::type *__restrict__ val, const T *vs, Op op)
@@ -201,7 +203,7 @@ __device__ __forceinline__ void sell_pass(int wv, int nwv, int lane, int nseg, c
         const int nbase = sp[hh] >> 1, nnp = ((sp[hh + 1] >> 1) - nbase) >> 6;
         Op nop = op;
         nop.load(min(hh * 64 + lane, nseg - 1));
-        T acc = 0;
+        T acc = 0, odd = 0;
         for (int p = 0;; p += kPairs) {
             const bool more = p + kPairs < np;
             const int from = more ? base + ((p + kPairs) << 6) : nbase;
@@ -215,7 +217,8 @@ __device__ __forceinline__ void sell_pass(int wv, int nwv, int lane, int nseg, c
             for (int q = 0; q < kPairs; ++q)
                 if (p + q < np) {
                     acc += v[q].x * vs[j[q] & 0xffffu];
-                    acc += v[q].y * vs[j[q] >> 16];
+                    T &a = PAIR ? odd : acc;
+                    a += v[q].y * vs[j[q] >> 16];
                 }
 #pragma unroll
             for (int q = 0; q < kPairs; ++q) {
@@ -224,7 +227,7 @@ __device__ __forceinline__ void sell_pass(int wv, int nwv, int lane, int nseg, c
             }
             if (!more) break;
         }
-        if (h * 64 + lane < nseg) op.put(h * 64 + lane, acc);
+        if (h * 64 + lane < nseg) op.put(h * 64 + lane, PAIR ? acc + odd : acc);
         if (hn >= nch) return;
         h = hn;
         op = nop;
@@ -234,13 +237,14 @@ __device__ __forceinline__ void sell_pass(int wv, int nwv, int lane, int nseg, c
 }
 
 // FP64 sums of one slice's segments over one or two vectors (a check's
-// products), lane l reading only its cnt entries.
+// products of columns, V = 1, and rows, V = 2), lane l reading only its cnt
+// entries, in the order of sell_pass.
 template <int V, typename S>
 __device__ __forceinline__ void sell_check(int s0, int cnt, int w, int lane, const unsigned *__restrict__ idx,
                                            const double *__restrict__ val64, const S *v1, const S *v2, double &q1,
                                            double &q2)
 {
-    double a1 = 0.0, a2 = 0.0;
+    double a1 = 0.0, a2 = 0.0, b1 = 0.0, b2 = 0.0;
 #pragma unroll 4
     for (int t = 0; t < w; t += 2) {
         const int o = ((s0 + 64 * t) >> 1) + lane;
@@ -251,12 +255,16 @@ __device__ __forceinline__ void sell_check(int s0, int cnt, int w, int lane, con
             if (V == 2) a2 += v.x * (double)v2[j & 0xffffu];
         }
         if (t + 1 < cnt) {
-            a1 += v.y * (double)v1[j >> 16];
-            if (V == 2) a2 += v.y * (double)v2[j >> 16];
+            if (V == 2) {
+                b1 += v.y * (double)v1[j >> 16];
+                b2 += v.y * (double)v2[j >> 16];
+            } else {
+                a1 += v.y * (double)v1[j >> 16];
+            }
         }
     }
-    q1 = a1;
-    q2 = a2;
+    q1 = a1 + b1;
+    q2 = a2 + b2;
 }
 
 // The updates of a sliced sweep pass; pointers are the instance's own.
@@ -465,7 +473,7 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                 delta[c0 + j] = d + mu * ((double)zn - (double)xn);
             };
             if (sc) {
-                sell_pass<T>(wv, nwv, lane64, n, sp_c, scol.idx, (const typename Two<T>::type *)scol.val, us,
+                sell_pass<false, T>(wv, nwv, lane64, n, sp_c, scol.idx, (const typename Two<T>::type *)scol.val, us,
                              SellCol<T>{xs, zi, ci_, delta + c0, ccnt + c0, mu, inv_mu, 0.0, 0, 0, 0});
             } else
             for (int jb = 0; jb < n; jb += Gc) {
@@ -500,7 +508,7 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                 a[2] += (qx - bd) * (qx - bd);
             };
             if (sr && !chk) {
-                sell_pass<T>(wv, nwv, lane64, m, sp_r, srow.idx, (const typename Two<T>::type *)srow.val, xs,
+                sell_pass<true, T>(wv, nwv, lane64, m, sp_r, srow.idx, (const typename Two<T>::type *)srow.val, xs,
                              SellRow<T>{us, fu + r0, b + r0, lam + r0, mu, inv_mu, 0.0, 0, 0});
             } else if (sr) {
                 for (int h = wv; h < (m + 63) >> 6; h += nwv) {

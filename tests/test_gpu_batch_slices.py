@@ -124,3 +124,20 @@ def test_sliced_columns_asked_for_without_room_for_them(precision, total):
     for k in KEYS:
         assert np.array_equal(out[0][0][k], out[1][0][k]), k
     assert out[0][1] == out[1][1] and out[0][1]["iter"] == 7
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("m,n,density", [(70, 300, 0.2), (600, 900, 0.02), (530, 4000, 0.3)])
+def test_sliced_rows_are_the_sums_of_two_lanes(m, n, density, precision):
+    """The sliced rows add even and odd entries apart, as two lanes a row do
+    (one running sum has twice their rounding error): the same iterates bit
+    for bit, checks included."""
+    inst = _instance(m, n, density, 21)
+    out = []
+    for lanes in ([1, 0] * 4, [2, 0] * 4):
+        with Batch([inst], precision=precision, eps=0.0, check_every=3) as b:
+            b.set_tiles(256, lanes)
+            b.iterate(8)
+            out.append(b.solution(0))
+    for k in KEYS:
+        assert np.array_equal(out[0][k], out[1][k]), k
