@@ -376,7 +376,8 @@ int batch_set_start(uv_batch *h, int32_t i, const double *x, const double *z,
  * Lanes per column 0 selects the sliced column copy: a wavefront per 64
  * columns whose t-th entries are stored side by side, so every entry load
  * is one coalesced access; the sums are those of one lane per column, bit
- * for bit.  UV_EINVAL for any other value. */
+ * for bit.  Lanes per row 1 selects a sliced copy of the rows likewise, with
+ * the sums of two lanes per row.  UV_EINVAL for any other value. */
 int batch_set_tiles(uv_batch *h, int32_t threads, const int32_t *lanes);
 int batch_get_tiles(const uv_batch *h, int32_t *threads, int32_t *lanes);
 

@@ -19,15 +19,16 @@ DEFAULT_CACHE = os.environ.get(
     "UVADMM_TILE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "uvadmm", "tiles.json"))
 
 THREADS = (256, 512, 1024)
-# (lanes per row, lanes per column); lanes per column 0 = the sliced column
-# copy (a wavefront per 64 columns, coalesced entry loads)
+# (lanes per row, lanes per column); 1 lane per row and 0 per column = the
+# sliced copies (a wavefront per 64 rows or columns, coalesced entry loads)
 LANE_PAIRS = ((1, 1), (2, 1), (4, 1), (2, 2), (4, 2), (8, 2), (8, 4), (1, 0), (2, 0), (4, 0), (8, 0))
 
 
 def signature(batch) -> str:
+    """Key of a batch's tiles (the number after "tiles" changes with what they mean)."""
     counts = batch.bucket_counts()
     rounded = [0 if c == 0 else 2 ** round(math.log2(c)) for c in counts]
-    return f"{batch.precision}|buckets={rounded}"
+    return f"tiles2|{batch.precision}|buckets={rounded}"
 
 
 def _load(path):

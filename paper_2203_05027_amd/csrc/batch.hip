@@ -143,7 +143,7 @@ __device__ __forceinline__ void seg_sum2(int beg, int end, int lane, int L, cons
     s2 = a2;
 }
 
-// Sliced copies (lanes per row 1, lanes per column 0 or 1): the segments of
+// Sliced copies (lanes per row 1, lanes per column 0): the segments of
 // an instance are cut into slices of 64, a lane each; entry t of the slice's
 // lane l is stored at s0 + 128 (t / 2) + 2 l + t % 2 (s0 the slice's first
 // slot), so a wavefront reads two entries a lane with one 4-byte load of their
@@ -453,7 +453,7 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
         }
         __syncthreads();
         // lane groups per segment, or the sliced copies (a wavefront per 64)
-        const bool sc = sliced && Lc <= 1, sr = sliced && Lr == 1;
+        const bool sc = sliced && Lc == 0, sr = sliced && Lr == 1;
         const int Lc1 = Lc > 0 ? Lc : 1;  // lane groups step by it: never zero
         const int gc = tid / Lc1, lc = tid % Lc1, Gc = nthr / Lc1;
         const int wv = tid >> 6, lane64 = tid & 63, nwv = nthr >> 6, nch = (n + 63) >> 6;
@@ -666,7 +666,7 @@ struct uv_batch {
     // (Lr, Lc) per size bucket: the sliced copies, but four lanes a row while
     // an instance has fewer rows than the workgroup a quarter of its threads
     // (m < 128: 3.6 against 4.2 us an iteration, m < 512: 6.9 against 8.1)
-    int tiles[2 * 4] = {4, 1, 4, 1, 1, 1, 1, 1};
+    int tiles[2 * 4] = {4, 0, 4, 0, 1, 0, 1, 0};
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
