@@ -39,10 +39,10 @@ constexpr int kLdsFree = 160 * 1024 - 1040; // what a launch is really left with
 struct BInst {
     int m, n;
     int row_off, col_off;  // first global row / column of the instance
-    int Lr, Lc;            // lanes per row / per column
+    int Lr, Lc;            // lanes per row / per column, 0: its sliced copy
     int status;
-    int ch_off;            // first 64-column slice of the instance
-    int rh_off;            // first 64-row slice
+    int ch_off;            // first 64-column slice of the instance (-1: it has none)
+    int rh_off;            // first 64-row slice (likewise)
     long long iter, check_iter;
     double r_prim, r_dual, r_gap, kkt, pobj, dobj, res_ax_b;
     double bnorm2, cnorm2;
@@ -143,7 +143,7 @@ __device__ __forceinline__ void seg_sum2(int beg, int end, int lane, int L, cons
     s2 = a2;
 }
 
-// Sliced copies (lanes per row 1, lanes per column 0): the segments of
+// Sliced copies (0 lanes): the segments of
 // an instance are cut into slices of 64, a lane each; entry t of the slice's
 // lane l is stored at s0 + 128 (t / 2) + 2 l + t % 2 (s0 the slice's first
 // slot), so a wavefront reads two entries a lane with one 4-byte load of their
@@ -331,6 +331,7 @@ k_sell_fill(const BInst *__restrict__ inst, int rows, const int *__restrict__ pt
     const BInst &I = inst[blockIdx.x];
     const int nseg = rows ? I.m : I.n, off = rows ? I.row_off : I.col_off, sub = rows ? I.col_off : I.row_off;
     const int pad = rows ? I.n : I.m, h0 = rows ? I.rh_off : I.ch_off;
+    if (h0 < 0) return;
     const int nch = (nseg + 63) >> 6;
     for (int p = threadIdx.x; p < nch * 64; p += 256) {
         const int h = p >> 6, l = p & 63;
@@ -453,12 +454,12 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
         }
         __syncthreads();
         // lane groups per segment, or the sliced copies (a wavefront per 64)
-        const bool sc = sliced && Lc == 0, sr = sliced && Lr == 1;
-        const int Lc1 = Lc > 0 ? Lc : 1;  // lane groups step by it: never zero
+        const bool sc = Lc == 0, sr = Lr == 0;
+        const int Lc1 = max(Lc, 1), Lr1 = max(Lr, 1);  // lane groups step by them: never zero
         const int gc = tid / Lc1, lc = tid % Lc1, Gc = nthr / Lc1;
         const int wv = tid >> 6, lane64 = tid & 63, nwv = nthr >> 6, nch = (n + 63) >> 6;
         const int *sp_c = scol.ptr + I->ch_off, *sp_r = srow.ptr + I->rh_off;
-        const int gr = tid / Lr, lr = tid % Lr, Gr = nthr / Lr;
+        const int gr = tid / Lr1, lr = tid % Lr1, Gr = nthr / Lr1;
         int stop = 0;
         for (int k = 0; k < budget && !stop; ++k) {
             // column pass: p = N x + A'u, x-step, projection onto R_+, delta
@@ -536,15 +537,15 @@ k_batch(BInst *__restrict__ inst, const int *__restrict__ order, int nq, int *__
                         bi = b[r0 + i];
                         l0 = lam[r0 + i];
                     }
-                    if (chk) seg_sum2<4>(beg, end, lr, Lr, cl, va64, zi, xs, qz, qx);
-                    else q = seg_sum<4, T>(beg, end, lr, Lr, cl, va, xs);
+                    if (chk) seg_sum2<4>(beg, end, lr, Lr1, cl, va64, zi, xs, qz, qx);
+                    else q = seg_sum<4, T>(beg, end, lr, Lr1, cl, va, xs);
                 }
                 if (chk) {
-                    qz = group_sum_rt(qz, Lr);
-                    qx = group_sum_rt(qx, Lr);
+                    qz = group_sum_rt(qz, Lr1);
+                    qx = group_sum_rt(qx, Lr1);
                     q = (T)qx;
                 } else {
-                    q = group_sum_rt(q, Lr);
+                    q = group_sum_rt(q, Lr1);
                 }
                 if (i < m && lr == 0) {
                     const T e = fi * (bi - q);
@@ -642,7 +643,7 @@ struct uv_batch {
     std::vector<void *> allocs;
     int *rp = nullptr, *ci = nullptr, *cp = nullptr, *ri = nullptr;
     lidx_t *cl = nullptr, *rl = nullptr;  // instance-local column (CSR) and row (CSC) numbers
-    Slices srow{}, scol{};       // sliced copies of the rows and columns
+    Slices srow{}, scol{};       // sliced copies of the rows and columns, made when tiles first ask for them
     lidx_t *ccnt = nullptr;      // entries of each column
     bool sliced = false;         // their padding's zeros fit LDS with x and u
     std::vector<int> rmap, cmap; // instance-local numbers of the caller for the device's rows and columns
@@ -708,24 +709,41 @@ int batch_launch(uv_batch *h, hipStream_t st, const int *order, int nq)
     return hipGetLastError() == hipSuccess ? UV_OK : UV_EHIP;
 }
 
-// A sliced copy of the rows or columns: slices of 64 segments, each as wide
-// as its longest (counts: the segments' entries), filled on the device from
-// the compressed form.  Sets every instance's rh_off or ch_off on the host.
-int build_slices(uv_batch *h, bool rows, const std::vector<int> &counts)
+// Slots a sliced copy of an instance with `entries` entries may take.  A slice
+// is 64 times its longest segment, so one dense row of 20,000 entries would
+// take 1.3e6 slots (18 MB in mixed precision); padded that far, the slices also
+// lose the time they save.  Instances past it keep their lane groups, whose
+// sums are the same.
+inline int64_t slots_allowed(int64_t entries) { return 4 * entries + 8192; }
+
+// A sliced copy of the rows or columns of every instance it suits: slices of
+// 64 segments, each as wide as its longest, filled on the device from the
+// compressed form.  Sets every instance's rh_off or ch_off on the host.
+int build_slices(uv_batch *h, bool rows)
 {
     const bool mixed = h->o.precision == UV_MIXED;
-    std::vector<int> sptr(1, 0);
+    hipStream_t st = h->stream;
+    std::vector<int> ptr((size_t)(rows ? h->M : h->N) + 1), sptr(1, 0);
+    UV_BTRY(hipMemcpy(ptr.data(), rows ? h->rp : h->cp, sizeof(int) * ptr.size(), hipMemcpyDeviceToHost));
     int64_t slots = 0;
     for (int i = 0; i < h->count; ++i) {
         BInst &I = h->inst_host[i];
         const int off = rows ? I.row_off : I.col_off, nseg = rows ? I.m : I.n;
-        (rows ? I.rh_off : I.ch_off) = (int)sptr.size() - 1;
+        int &first = rows ? I.rh_off : I.ch_off;
+        const size_t at = sptr.size();
+        const int64_t before = slots;
+        first = (int)at - 1;
         for (int j0 = 0; j0 < nseg; j0 += 64) {
             int w = 0;
-            for (int j = j0; j < std::min(j0 + 64, nseg); ++j) w = std::max(w, counts[(size_t)off + j]);
+            for (int j = j0; j < std::min(j0 + 64, nseg); ++j) w = std::max(w, ptr[(size_t)off + j + 1] - ptr[(size_t)off + j]);
             slots += 64 * (int64_t)((w + 1) / 2 * 2);
-            if (slots + 1024 >= ((int64_t)1 << 31)) return UV_ETOOBIG;
+            if (slots + 1024 >= ((int64_t)1 << 31)) break;
             sptr.push_back((int)slots);
+        }
+        if (slots - before > slots_allowed(ptr[(size_t)off + nseg] - ptr[off]) || slots + 1024 >= ((int64_t)1 << 31)) {
+            first = -1;
+            slots = before;
+            sptr.resize(at);
         }
     }
     const size_t room = (size_t)slots + 128 * kPairs;  // a pass reads whole groups of pairs
@@ -734,7 +752,6 @@ int build_slices(uv_batch *h, bool rows, const std::vector<int> &counts)
     double *val64 = balloc<double>(h, room);
     float *val = mixed ? balloc<float>(h, room) : nullptr;
     if (!dptr || !idx || !val64 || (mixed && !val)) return UV_ENOMEM;
-    hipStream_t st = h->stream;
     UV_BTRY(hipMemcpy(dptr, sptr.data(), sizeof(int) * sptr.size(), hipMemcpyHostToDevice));
     UV_BTRY(hipMemcpy(h->inst, h->inst_host, sizeof(BInst) * h->count, hipMemcpyHostToDevice));
     k_sell_fill<<<h->count, 256, 0, st>>>(h->inst, rows ? 1 : 0, rows ? h->rp : h->cp, rows ? h->ci : h->ri,
@@ -746,14 +763,23 @@ int build_slices(uv_batch *h, bool rows, const std::vector<int> &counts)
     return UV_OK;
 }
 
+// The instances' lanes from the tile table, by size bucket: one lane per row
+// asks for the sliced rows (two lanes a row, the same sums, where an instance
+// has none), none per column for the sliced columns (one lane likewise).
 int apply_tiles(uv_batch *h)
 {
-    // lanes per row / column from the tile table, by size bucket; without the
-    // sliced copies their columns (0 lanes) are walked by one lane each
+    for (int d = 0; d < 2; ++d) {  // a copy is made when an instance first asks for it
+        bool asked = false;
+        for (int i = 0; i < h->count; ++i) asked = asked || h->tiles[2 * bucket_of(h->inst_host[i].m) + d] == (d == 0 ? 1 : 0);
+        if (!asked || !h->sliced || (d == 0 ? h->srow : h->scol).ptr) continue;
+        const int rc = build_slices(h, d == 0);
+        if (rc != UV_OK) return rc;
+    }
     for (int i = 0; i < h->count; ++i) {
-        const int bk = bucket_of(h->inst_host[i].m);
-        h->inst_host[i].Lr = h->tiles[2 * bk];
-        h->inst_host[i].Lc = h->sliced ? h->tiles[2 * bk + 1] : std::max(1, h->tiles[2 * bk + 1]);
+        BInst &I = h->inst_host[i];
+        const int *t = h->tiles + 2 * bucket_of(I.m);
+        I.Lr = t[0] > 1 ? t[0] : h->srow.ptr && I.rh_off >= 0 ? 0 : 2;
+        I.Lc = t[1] > 0 ? t[1] : h->scol.ptr && I.ch_off >= 0 ? 0 : 1;
     }
     UV_BTRY(hipMemcpyAsync(h->inst, h->inst_host, sizeof(BInst) * h->count, hipMemcpyHostToDevice, h->stream));
     UV_BTRY(hipStreamSynchronize(h->stream));
@@ -951,7 +977,6 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
 
     // Pack the block-diagonal matrix with global indices, rows and columns
     // of an instance in falling order of their entries (stable).
-    std::vector<int> rcnt(M), ccnt(N);
     h->rmap.resize(M);
     h->cmap.resize(N);
     {
@@ -984,14 +1009,10 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
             by_count(a.n, [&](int j) { return cc0[j]; }, cm);
             inv.resize(a.n);
             for (int j = 0; j < a.n; ++j) inv[cm[j]] = j;
-            for (int j = 0; j < a.n; ++j) {
-                ccnt[co + j] = cc0[cm[j]];
-                cc[co + j] = c[i][cm[j]];
-            }
+            for (int j = 0; j < a.n; ++j) cc[co + j] = c[i][cm[j]];
             int64_t w = ko;
             for (int r = 0; r < a.m; ++r) {
                 rp32[ro + r] = (int)w;
-                rcnt[ro + r] = (int)(a.row_ptr[rm[r] + 1] - a.row_ptr[rm[r]]);
                 bb[ro + r] = b[i][rm[r]];
                 for (int64_t k = a.row_ptr[rm[r]]; k < a.row_ptr[rm[r] + 1]; ++k, ++w) {
                     ci32[w] = (int)(co + inv[a.col_idx[k]]);
@@ -1049,8 +1070,6 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
         hipStreamSynchronize(st) != hipSuccess)
         return fail(UV_EHIP);
     k_col_entries<<<blocks_for(N, 256), 256, 0, st>>>((int)N, h->cp, h->ccnt);
-    if ((rc = build_slices(h, true, rcnt)) != UV_OK) return fail(rc);
-    if ((rc = build_slices(h, false, ccnt)) != UV_OK) return fail(rc);
     if ((rc = apply_tiles(h)) != UV_OK) return fail(rc);
     if ((rc = occupancy_grid(h)) != UV_OK) return fail(rc);
     if ((rc = rebuild_graph(h)) != UV_OK) return fail(rc);

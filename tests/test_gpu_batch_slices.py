@@ -141,3 +141,24 @@ def test_sliced_rows_are_the_sums_of_two_lanes(m, n, density, precision):
             out.append(b.solution(0))
     for k in KEYS:
         assert np.array_equal(out[0][k], out[1][k]), k
+
+
+def test_dense_rows_do_not_grow_the_batch():
+    """One row of 40,000 entries beside an empty one, 850 instances: slices 64
+    times that row would pass 2^31 slots, so such rows keep their lane groups."""
+    n = 40_000
+    rng = np.random.default_rng(31)
+    a, x = rng.standard_normal(n) / 200.0, np.maximum(rng.standard_normal(n), 0.0)
+    inst = dict(m=2, n=n, row_ptr=np.array([0, n, n], np.int64), col_idx=np.arange(n, dtype=np.int32), val=a,
+                b=np.array([a @ x, 0.0]), c=a * 0.3 + rng.uniform(0, 1, n), n_orth=n, soc_sizes=np.zeros(0, np.int32))
+    with Batch([inst] * 850, precision="mixed", eps=0.0) as b:
+        for lanes in ([4, 0] * 4, [1, 0] * 4):
+            b.set_tiles(256, lanes)
+        b.iterate(3)
+        sols = [b.solution(i) for i in (0, 849)]
+    o = oracle.Oracle.from_instance(inst)
+    o.iterate(3)
+    so = o.state()
+    scale = max(np.abs(so[k]).max() for k in KEYS)
+    for s in sols:
+        assert max(float(np.abs(s[k] - so[k]).max()) for k in KEYS) <= 1e-5 * scale
