@@ -22,8 +22,10 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <numeric>
+#include <queue>
 #include <vector>
 
 #include "../../include/uvadmm.h"
@@ -658,16 +660,13 @@ struct uv_batch {
     int *order = nullptr, *queue = nullptr, *budget = nullptr;
     int *budget_host = nullptr;  // pinned
     std::vector<int> order_host;
-    int threads = 1024;
+    int threads = 0;
     int xu_bytes = 0;   // x and u of the largest instance with the sliced copies' zeros (16-byte aligned)
     int zc_bytes = 0;   // x, u, z and c likewise
     bool zc = false;    // z and c staged in LDS too
     int lds_bytes = 0;  // dynamic LDS per workgroup of the launch
     int grid = 0;
-    // (Lr, Lc) per size bucket: the sliced copies, but four lanes a row while
-    // an instance has fewer rows than the workgroup a quarter of its threads
-    // (m < 128: 3.6 against 4.2 us an iteration, m < 512: 6.9 against 8.1)
-    int tiles[2 * 4] = {4, 0, 4, 0, 1, 0, 1, 0};
+    int tiles[2 * 4] = {};  // (Lr, Lc) per size bucket
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
@@ -816,6 +815,58 @@ int occupancy_grid(uv_batch *h)
         rc = h->zc ? occupancy_of<double, true>(h, &per_cu) : occupancy_of<double, false>(h, &per_cu);
     if (rc != UV_OK) return rc;
     h->grid = std::max(1, per_cu) * cus;
+    return UV_OK;
+}
+
+// The default tiles.  A workgroup's time for an iteration of an instance with
+// w = rows + columns + entries on T threads is about 2.5 + 0.2 w / T us (0.27 on
+// 1024; in FP64 a fifth more), and a compute unit cannot do it in less than 0.25
+// + 0.0005 w us (0.35 + 0.0007 w in FP64) whatever the number of workgroups that share it; a sweep
+// takes what the workgroups need that fetch the instances one by one, or the
+// compute units, whichever is longer.  Large or few instances want the
+// widest workgroup, many small ones as many workgroups as a compute unit
+// holds.  Measured (us a sweep, mixed, T = 128 / 256 / 512 / 1024): 4096 of 20 x
+// 40 6.4 / 9.1 / 19 / 37, of 50 x 100 10.6 / 11.3 / 23 / 42, of 200 x 400 31 /
+// 29 / 37 / 50, 1024 of 1200 x 2400 43 / 36 / 35 / 38, of 5000 x 10000 - / 318 /
+// 192 / 146; 64 of 200 x 400 7.7 / 3.9 / 3.5 / 3.2.
+// Rows: the sliced copy, but four lanes while an instance has fewer rows than
+// the workgroup about a quarter of its threads (200 rows on 1024: 3.2 against
+// 3.7 us; on 256: 5.6 against 3.9), two on the narrow workgroup (4096 of 20 x 40
+// 6.4 against 7.4 us sliced and 6.0 with four, of 100 x 200 17.5 against 17.3
+// and 18.3).
+int default_tiles(uv_batch *h, const std::vector<double> &weight)  // the instances', longest first
+{
+    static const int rows[4][2] = {{2, 2}, {4, 1}, {4, 1}, {4, 4}};  // buckets 0 and 1 on 128, 256, 512, 1024 threads
+    const bool fp64 = h->o.precision == UV_FP64;
+    int dev = 0, cus = 0, best_t = 1024;
+    UV_BTRY(hipGetDevice(&dev));
+    UV_BTRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    double best = 0.0;
+    for (int t = 1024, rc; t >= 128; t /= 2) {
+        h->threads = t;
+        if ((rc = occupancy_grid(h)) != UV_OK) return rc;
+        std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+        double last = 0.0, cu = 0.0;
+        for (double w : weight) {
+            double at = (fp64 ? 1.2 : 1.0) * (2.5 + (t == 1024 ? 0.27 : 0.2) * w / t);
+            if ((int)free_at.size() == h->grid) {
+                at += free_at.top();
+                free_at.pop();
+            }
+            free_at.push(at);
+            last = std::max(last, at);
+            cu += fp64 ? 0.35 + 0.0007 * w : 0.25 + 0.0005 * w;
+        }
+        const double us = std::max(last, cu / cus);
+        if (t == 1024 || us < 0.97 * best) {  // a wider one unless a narrower is clearly faster
+            best = us;
+            best_t = t;
+        }
+    }
+    h->threads = best_t;
+    const int *r = rows[best_t == 128 ? 0 : best_t == 256 ? 1 : best_t == 512 ? 2 : 3];
+    const int tiles[2 * 4] = {r[0], 0, r[1], 0, 1, 0, 1, 0};
+    std::memcpy(h->tiles, tiles, sizeof(tiles));
     return UV_OK;
 }
 
@@ -1070,6 +1121,12 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
         hipStreamSynchronize(st) != hipSuccess)
         return fail(UV_EHIP);
     k_col_entries<<<blocks_for(N, 256), 256, 0, st>>>((int)N, h->cp, h->ccnt);
+    std::vector<double> weight(count);
+    for (int q = 0; q < count; ++q) {
+        const uv_csr &a = A[h->order_host[q]];
+        weight[q] = (double)a.nnz + a.m + a.n;
+    }
+    if ((rc = default_tiles(h, weight)) != UV_OK) return fail(rc);
     if ((rc = apply_tiles(h)) != UV_OK) return fail(rc);
     if ((rc = occupancy_grid(h)) != UV_OK) return fail(rc);
     if ((rc = rebuild_graph(h)) != UV_OK) return fail(rc);

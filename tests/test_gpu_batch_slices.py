@@ -162,3 +162,23 @@ def test_dense_rows_do_not_grow_the_batch():
     scale = max(np.abs(so[k]).max() for k in KEYS)
     for s in sols:
         assert max(float(np.abs(s[k] - so[k]).max()) for k in KEYS) <= 1e-5 * scale
+
+
+@pytest.mark.parametrize("count,m", [(4096, 20), (2048, 100), (1024, 500), (64, 200), (300, 1500)])
+def test_default_tiles_are_near_the_best_workgroup(count, m):
+    """The workgroup that the batch chooses for itself, against the others:
+    at most 1.25 times the fastest (one of 1024 threads for every batch took
+    4.5 times the time of narrow ones with many small instances)."""
+    insts = [_instance(m, 2 * m, min(1.0, 4.0 / m), 41 + i) for i in range(4)]
+    for i in insts:  # no dense segments
+        A = sp.random(i["m"], i["n"], density=min(1.0, 6.0 / m), random_state=i["m"], format="csr")
+        i.update(row_ptr=A.indptr.astype(np.int64), col_idx=A.indices.astype(np.int32), val=A.data - 0.5)
+    with Batch((insts * ((count + 3) // 4))[:count], precision="mixed", eps=0.0) as b:
+        threads, lanes = b.get_tiles()
+        own = min(b.time(-1, 50) for _ in range(3))
+        others = {}
+        for t in (64, 128, 256, 512, 1024):
+            b.set_tiles(t, [2 if t < 256 else 4, 0, 1, 0, 1, 0, 1, 0])
+            others[t] = min(b.time(-1, 50) for _ in range(3))
+    sys.__stderr__.write(f"[gpu-test] batch {count} x {m}: own {threads} {lanes} {own:.3f} ms, {others}\n")
+    assert own <= 1.25 * min(others.values()), (threads, own, others)
