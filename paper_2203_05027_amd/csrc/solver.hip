@@ -834,6 +834,7 @@ struct ResLayout {
 };
 
 constexpr int kResThreads = 1024;
+constexpr int kResRegs = 8;    // entries of a row or column that a lane of k_resident_reg keeps in registers
 // Modes of the resident kernels: iterate; record the state's residuals; iterate
 // and leave the final iterate's residuals (k_resident_reg; k_resident iterates
 // only, and a query follows).
@@ -1319,7 +1320,7 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
     __shared__ int stop, skip;
     const bool eval_only = mode == kResEval, record = mode == kResRecord;
     if (!eval_only && st->done) return;
-    constexpr int NT = kResThreads, R = 8;
+    constexpr int NT = kResThreads, R = kResRegs;
     static_assert(sizeof(red) >= 16 * 32, "res_order's counts");
     const int tid = threadIdx.x;
     double *ls = (double *)(lds_raw + L.l);
@@ -1508,6 +1509,7 @@ struct uv_solver {
     const int *res_skip = nullptr;  // skip flag of the column residual kernels being launched
     ResLayout rlay{};
     int res_lr = 1, res_lc = 1;  // lanes per row and per column of k_resident
+    bool res_reg = false;        // k_resident_reg, not k_resident
     HistRec *hist = nullptr;     // residual history ring (opts.history records)
     double clock_khz = 0.0;      // rate of the GPU wall clock
     hipGraph_t graph = nullptr;
@@ -1993,27 +1995,48 @@ struct ResArgs {
     double *lam, *delta;
     DevStatus *st;
     HistRing hist;
-    bool mixed;
+    bool mixed, reg;
     double mu, eps, eps_abs, eps_gap;
     int check_every, crit;
     int gated;  // checks primal half first (no history, opts.full_checks = 0)
 };
 
-// The resident kernel for m x n: the register form where every lane group
-// has at most one column and one row.  Two columns a group need more
-// registers than a thread of a full workgroup has (spilled: 700x1500 in FP64
-// 3.8 us an iteration against k_resident's 3.1).
-template <typename T>
-auto resident_kernel(int m, int n)
+// Whether a resident problem takes the register form: every lane group has at
+// most one column and one row, and the longest of them leave little past the
+// registers, where k_resident_reg takes the entries one by one and k_resident
+// four at a time (the same in its loop took the plain 500x1000 from 1.45 to 1.9
+// us).  k_resident / k_resident_reg, us an iteration of 600x1000, entries past
+// the registers in the longest row and column: 5 2.36 / 1.39, 16 2.45 / 2.17, 24
+// 2.67 / 2.70, 43 3.13 / 3.79, 99 4.8 / 8.0; of 300x900 (4500 entries): 12 2.79 /
+// 1.95, 30 3.14 / 3.23, 49 3.75 / 4.57; of 100x200 (1000): 10 1.91 / 1.58, 19 2.12
+// / 2.22; 300x600 (4800): 30 3.29 / 2.71; one row of a thousand 49 / 105.
+// (Two columns a group need more registers than a thread of a full workgroup
+// has: spilled, 700x1500 in FP64 took 3.8 us an iteration against k_resident's
+// 3.1.)
+bool resident_registers(const uv_csr *A)
 {
-    return m > kResThreads || n > kResThreads ? k_resident<T> : k_resident_reg<T>;
+    const int m = A->m, n = A->n;
+    if (m > kResThreads || n > kResThreads) return false;
+    unsigned short count[kResThreads] = {};
+    int row = 0, col = 0;
+    for (int i = 0; i < m; ++i) row = std::max(row, (int)(A->row_ptr[i + 1] - A->row_ptr[i]));
+    for (int64_t k = 0; k < A->nnz; ++k) col = std::max(col, (int)++count[A->col_idx[k]]);
+    const int Lr = resident_lanes(m, A->nnz), Lc = resident_lanes(n, A->nnz);
+    return std::max((row + Lr - 1) / Lr - kResRegs, 0) + std::max((col + Lc - 1) / Lc - kResRegs, 0) <=
+           16 + A->nnz / 300;
+}
+
+template <typename T>
+auto resident_kernel(bool reg)
+{
+    return reg ? k_resident_reg<T> : k_resident<T>;
 }
 
 // Lets its launches have the LDS of every resident problem.
 template <typename T>
-hipError_t resident_ready(int m, int n)
+hipError_t resident_ready(bool reg)
 {
-    return hipFuncSetAttribute((const void *)resident_kernel<T>(m, n), hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void *)resident_kernel<T>(reg), hipFuncAttributeMaxDynamicSharedMemorySize,
                                kResLdsMax + 64);
 }
 
@@ -2034,8 +2057,8 @@ void resident_launch(const ResArgs &a, hipStream_t st, int64_t iters, int mode)
         (const T *)a.b, a.b64, (const T *)a.c, a.c64, (const T *)a.fu, (T *)a.x, (T *)a.z, (T *)a.u, a.lam,        \
         a.delta, a.mu, q, what, a.check_every, a.eps, a.eps_abs, a.eps_gap, a.crit, a.st, a.hist,  \
         a.gated
-        if (a.mixed) resident_kernel<float>(a.m, a.n)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(float));
-        else resident_kernel<double>(a.m, a.n)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(double));
+        if (a.mixed) resident_kernel<float>(a.reg)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(float));
+        else resident_kernel<double>(a.reg)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(double));
 #undef UV_RES_ARGS
         left -= eval_only ? 1 : kChunk;
     }
@@ -2071,6 +2094,7 @@ ResArgs res_args(const uv_solver *s)
     a.hist = HistRing{s->hist, s->o.history};
     a.gated = s->o.full_checks == 0 && !s->hist ? 1 : 0;
     a.mixed = s->o.precision == UV_MIXED;
+    a.reg = s->res_reg;
     a.mu = s->o.mu;
     a.eps = s->o.eps_kkt;
     a.eps_abs = s->o.eps_abs;
@@ -2529,7 +2553,8 @@ int solver_create(const uv_csr *A, const double *b, const double *c, const uv_co
         s->res_lr = resident_lanes(A->m, A->nnz);
         s->res_lc = resident_lanes(A->n, A->nnz);
         if (s->resident) {
-            const hipError_t e = mixed ? resident_ready<float>(A->m, A->n) : resident_ready<double>(A->m, A->n);
+            s->res_reg = resident_registers(A);
+            const hipError_t e = mixed ? resident_ready<float>(s->res_reg) : resident_ready<double>(s->res_reg);
             if (e != hipSuccess) {
                 solver_destroy(s);
                 return UV_EHIP;
@@ -3014,7 +3039,8 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     if ((rc = scratch_address(&base)) != UV_OK) return rc;
     Carve cv{base, 0, kScratchBytes, true};
     carve_noalloc(cv, m, n, nnz, mixed, d);
-    if ((mixed ? resident_ready<float>(m, n) : resident_ready<double>(m, n)) != hipSuccess) return UV_EHIP;
+    const bool reg = resident_registers(A);
+    if ((mixed ? resident_ready<float>(reg) : resident_ready<double>(reg)) != hipSuccess) return UV_EHIP;
     hipStream_t st = (hipStream_t)o.hip_stream;
     // inputs and the setup of solver_create
     UV_TRY(hipMemcpyAsync(d.rp64, A->row_ptr, 8 * ((size_t)m + 1), hipMemcpyHostToDevice, st));
@@ -3059,6 +3085,7 @@ int solver_solve_noalloc(const uv_csr *A, const double *b, const double *c, cons
     a.hist = HistRing{nullptr, 0};
     a.gated = o.full_checks == 0 ? 1 : 0;
     a.mixed = mixed;
+    a.reg = reg;
     a.mu = o.mu;
     a.eps = o.eps_kkt;
     a.eps_abs = o.eps_abs;

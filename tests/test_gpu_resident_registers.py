@@ -109,3 +109,41 @@ def test_a_problem_that_just_fills_lds(over):
     o.iterate(11)
     errs = _errors(sol, o.state())
     assert max(errs.values()) <= TOL["fp64"], errs
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("row,col", [(16, 0), (40, 0), (0, 60), (1000, 600)])
+def test_a_long_row_or_column_keeps_its_speed(row, col, precision):
+    """One long row or column: the oracle's iterates on both sides of the rule
+    that leaves the register form, and at most 1.25 times the time of the same
+    problem with more (empty) columns than threads, which the rule never takes."""
+    import time
+
+    import scipy.sparse as sp
+    m, n = 600, 1000
+    rng = np.random.default_rng(5)
+    A = sp.csr_matrix((rng.standard_normal(3 * n), (rng.integers(0, m, 3 * n), np.repeat(np.arange(n), 3))), shape=(m, n)).tolil()
+    A[0, :row] = 0.1
+    A[:col, 0] = 0.1
+    us = []
+    for pad in (0, 40):
+        B = sp.hstack([A, sp.csr_matrix((m, pad))]).tocsr() if pad else A.tocsr()
+        B.sort_indices()
+        inst = dict(m=m, n=n + pad, nnz=B.nnz, row_ptr=B.indptr.astype(np.int64), col_idx=B.indices.astype(np.int32), val=B.data,
+                    b=B @ np.linspace(0, 1, n + pad), c=np.linspace(1, 2, n + pad), n_orth=n + pad, soc_sizes=np.zeros(0, np.int32))
+        with Solver.from_instance(inst, precision=precision, eps=0.0, resident="required") as s:
+            s.iterate(13)
+            if not pad:
+                o = oracle.Oracle.from_instance(inst)
+                o.iterate(13)
+                so, g = o.state(), s.solution()
+                scale = max(np.abs(so[k]).max() for k in g)
+                assert max(float(np.abs(g[k] - so[k]).max()) for k in g) <= (1e-9 if precision == "fp64" else 1e-5) * scale
+            best = 1e9
+            for _ in range(4):
+                t0 = time.perf_counter()
+                s.iterate(1000)
+                best = min(best, time.perf_counter() - t0)
+            us.append(best * 1e3)
+    sys.__stderr__.write(f"[gpu-test] resident row {row} column {col} {precision}: {us[0]:.2f} us an iteration, padded {us[1]:.2f}\n")
+    assert us[0] <= 1.25 * us[1], us
