@@ -1,11 +1,12 @@
 // family.hip -- one matrix A and cost c, B right-hand sides b_1..b_B (a
 // parametric family of LPs, orthant cone), iterated together.
 //
-// The instances are cut into groups of 128 bytes of the sweep type (32 in
-// FP32, 16 in FP64) and every per-instance vector is stored group by group,
+// The instances are cut into groups of 32 (fam_group: 16 in some FP64
+// families) and every per-instance vector is stored group by group,
 // instance-fastest within a group: entry j of instance l is
 // v[((l / G) * len + j) * G + l % G].  A gather of x or u is one cache line
-// for a whole group, and a group's gathered vector is 6.4 MB for u at m = 5e4.
+// (two in FP64) for a whole group, and a group's gathered vector is 6.4 MB for
+// u at m = 5e4 in FP32.
 // G lanes take one row (or column) of A for a group; a workgroup takes a
 // block of them with the block's entries in LDS, and each XCD works through
 // its groups one after the other.
@@ -14,9 +15,9 @@
 // 8e5 entries, 256 instances, mixed: column pass 220 -> 185 us, row pass 167
 // -> 146 us, the check's two passes 322 + 319 -> 314 + 225 us; an iteration,
 // checks included, 434 -> 373 us (FP64 661 -> 618) against groups of 64
-// instances, a wavefront each, with the entries in scalar registers.  Groups
-// of 64 bytes hit L2 more often but ask for twice the lines: 455 us; groups
-// of 256 bytes 420 us; reading a segment's operands and gathers ahead of the
+// instances, a wavefront each, with the entries in scalar registers.  In mixed
+// precision groups of 64 bytes hit L2 more often but ask for twice the lines:
+// 455 us; groups of 256 bytes 420 us; reading a segment's operands and gathers ahead of the
 // last one's stores 405 us.
 // The iteration is the reduced form of Algorithm 1 used by the single
 // solver; each instance is checked every check_every iterations and frozen
@@ -57,9 +58,15 @@ struct FShared {
 
 constexpr int kFamThreads = 256;
 
-// Instances a group holds.
-template <typename T>
-constexpr int fam_group() { return 128 / (int)sizeof(T); }
+// Instances a group holds: 32.  In FP64 that is two lines a gather, which costs
+// nothing while the gathered vectors stay in L2, and half the instructions of
+// groups of 16, 128 instances of 2000 x 4000 with 60 entries a column: 61 us with
+// 16, 51 with 32 (50 with the entries in scalar registers); 256 of 1e4 x 2e4 with
+// 30: 274, 221 (277).  Groups of 16 keep u in an XCD's L2 twice as long and pay
+// where each XCD has at most one of them and the 32 instances' u passes its 4
+// MiB: 128 of 2e4 x 3.6e4 with 8 104, 117 (128), 64 of 5e4 x 1e5 172, 181 (189);
+// 256 of 2e4 x 3.6e4 246, 227 (264).
+inline int fam_group(bool fp64, int B, int m) { return fp64 && B <= 128 && m > 16384 ? 16 : 32; }
 
 // Place of entry j of instance l in a vector of len entries an instance.
 __device__ __forceinline__ size_t fam_at(int len, int G, int j, int l)
@@ -226,14 +233,13 @@ __device__ __forceinline__ void fam_dot2(int beg, int end, const int *__restrict
 }
 
 // column pass: G lanes = (column j, one group)
-template <typename T, bool NT>
+template <typename T, int G, bool NT>
 __global__ void __launch_bounds__(kFamThreads)
 k_fam_col(int n, int m, int ng, int nb, int segs, const int *__restrict__ cp, const int *__restrict__ ri,
           const T *__restrict__ vc, const T *__restrict__ U, T *__restrict__ X, T *__restrict__ Z,
           double *__restrict__ D, const T *__restrict__ c, const int *__restrict__ run, double mu, double inv_mu,
           const FShared *__restrict__ sh)
 {
-    constexpr int G = fam_group<T>();
     int g, blk;
     if (sh->active == 0 || !fam_unit(ng, nb, g, blk)) return;
     const int lane = threadIdx.x % G;
@@ -265,14 +271,13 @@ k_fam_col(int n, int m, int ng, int nb, int segs, const int *__restrict__ cp, co
 }
 
 // row pass: G lanes = (row i, one group)
-template <typename T, bool NT>
+template <typename T, int G, bool NT>
 __global__ void __launch_bounds__(kFamThreads)
 k_fam_row(int m, int n, int ng, int nb, int segs, const int *__restrict__ rp, const int *__restrict__ ci,
           const T *__restrict__ va, const T *__restrict__ X, const T *__restrict__ BV, const T *__restrict__ fu,
           double *__restrict__ LAM, T *__restrict__ U, const int *__restrict__ run, double mu, double inv_mu,
           FShared *sh)
 {
-    constexpr int G = fam_group<T>();
     int g, blk;
     if (sh->active == 0 || !fam_unit(ng, nb, g, blk)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) sh->iter += 1;
@@ -322,7 +327,7 @@ __device__ __forceinline__ void fam_partials(const double (&a)[K], int blk, int 
 // updates from that A x (rounded to the sweep type), and the row partials of
 // the check with the updated lambda: per instance ||A z - b||^2, b'lambda,
 // ||A x - b||^2.
-template <typename T>
+template <typename T, int G>
 __global__ void __launch_bounds__(kFamThreads)
 k_fam_row_check(int m, int n, int B, const int *__restrict__ rp, const int *__restrict__ ci,
                 const double *__restrict__ va, const T *__restrict__ X, const T *__restrict__ Z,
@@ -330,7 +335,7 @@ k_fam_row_check(int m, int n, int B, const int *__restrict__ rp, const int *__re
                 double *__restrict__ LAM, T *__restrict__ U, const int *__restrict__ run, double mu,
                 double inv_mu, FShared *sh, double *__restrict__ part)
 {
-    constexpr int G = fam_group<T>(), SEG = kFamThreads / G;
+    constexpr int SEG = kFamThreads / G;
     int g, blk;
     if (sh->active == 0 || !fam_unit(B / G, kResBlocks, g, blk)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) sh->iter += 1;
@@ -370,14 +375,14 @@ k_fam_row_check(int m, int n, int B, const int *__restrict__ rp, const int *__re
 
 // Residual partials over columns: ||A'lambda + c - delta||^2, c'z (same
 // blocks as the row partials).
-template <typename T>
+template <typename T, int G>
 __global__ void __launch_bounds__(kFamThreads)
 k_fam_res_col(int n, int m, int B, const int *__restrict__ cp, const int *__restrict__ ri,
               const double *__restrict__ vc, const double *__restrict__ LAM, const double *__restrict__ c,
               const double *__restrict__ D, const T *__restrict__ Z, const int *__restrict__ run,
               const FShared *__restrict__ sh, double *__restrict__ part)
 {
-    constexpr int G = fam_group<T>(), SEG = kFamThreads / G;
+    constexpr int SEG = kFamThreads / G;
     int g, blk;
     if (sh->active == 0 || !fam_unit(B / G, kResBlocks, g, blk)) return;
     const int lane = threadIdx.x % G;
@@ -548,13 +553,12 @@ k_fam_start(size_t len, const double *__restrict__ LAM, T *__restrict__ U, doubl
 // Warm start from predicted (x, lambda): z = max(x, 0),
 // delta = max(c + A'lambda, 0) (the dual-feasible part of the stationarity
 // condition c + A'lambda - delta = 0), u = -lambda/mu.
-template <typename T>
+template <typename T, int G>
 __global__ void __launch_bounds__(kFamThreads)
 k_fam_dual_start(int n, int m, int ng, int nb, const int *__restrict__ cp, const int *__restrict__ ri,
                  const double *__restrict__ vc, const double *__restrict__ LAM, const double *__restrict__ c,
                  const T *__restrict__ X, T *__restrict__ Z, double *__restrict__ D)
 {
-    constexpr int G = fam_group<T>();
     int g, blk;
     if (!fam_unit(ng, nb, g, blk)) return;
     const int lane = threadIdx.x % G, j = blk * (kFamThreads / G) + threadIdx.x / G;
@@ -768,11 +772,11 @@ T *falloc(uv_family *h, size_t count)
         if ((expr) != hipSuccess) return UV_EHIP;  \
     } while (0)
 
-template <typename T>
+template <typename T, int G>
 void fam_iteration_t(uv_family *h, hipStream_t st, bool check)
 {
     const double mu = h->o.mu, im = 1.0 / h->o.mu;
-    const int ng = h->B / h->G, wc = fam_segs(h->n, ng, h->G), wr = fam_segs(h->m, ng, h->G);
+    const int ng = h->B / G, wc = fam_segs(h->n, ng, G), wr = fam_segs(h->m, ng, G);
     const int bc = fam_blocks(h->n, wc), br = fam_blocks(h->m, wr);
 #define UV_COL_ARGS                                                                                               \
     h->n, h->m, ng, bc, wc, h->cp, h->ri, (const T *)h->vc, (const T *)h->U, (T *)h->X, (T *)h->Z, h->D,          \
@@ -780,16 +784,16 @@ void fam_iteration_t(uv_family *h, hipStream_t st, bool check)
 #define UV_ROW_ARGS                                                                                               \
     h->m, h->n, ng, br, wr, h->rp, h->ci, (const T *)h->va, (const T *)h->X, (const T *)h->BV, (const T *)h->fu, \
         h->LAM, (T *)h->U, h->run, mu, im, h->sh
-    if (h->big) k_fam_col<T, true><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(UV_COL_ARGS);
-    else k_fam_col<T, false><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(UV_COL_ARGS);
+    if (h->big) k_fam_col<T, G, true><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(UV_COL_ARGS);
+    else k_fam_col<T, G, false><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(UV_COL_ARGS);
     if (!check) {
-        if (h->big) k_fam_row<T, true><<<fam_grid(ng, br), kFamThreads, 0, st>>>(UV_ROW_ARGS);
-        else k_fam_row<T, false><<<fam_grid(ng, br), kFamThreads, 0, st>>>(UV_ROW_ARGS);
+        if (h->big) k_fam_row<T, G, true><<<fam_grid(ng, br), kFamThreads, 0, st>>>(UV_ROW_ARGS);
+        else k_fam_row<T, G, false><<<fam_grid(ng, br), kFamThreads, 0, st>>>(UV_ROW_ARGS);
     } else {
-        k_fam_row_check<T><<<fam_grid(ng, kResBlocks), kFamThreads, 0, st>>>(
+        k_fam_row_check<T, G><<<fam_grid(ng, kResBlocks), kFamThreads, 0, st>>>(
             h->m, h->n, h->B, h->rp, h->ci, h->va64, (const T *)h->X, (const T *)h->Z, (const T *)h->BV, h->BV64,
             (const T *)h->fu, h->LAM, (T *)h->U, h->run, mu, im, h->sh, h->prow);
-        k_fam_res_col<T><<<fam_grid(ng, kResBlocks), kFamThreads, 0, st>>>(
+        k_fam_res_col<T, G><<<fam_grid(ng, kResBlocks), kFamThreads, 0, st>>>(
             h->n, h->m, h->B, h->cp, h->ri, h->vc64, h->LAM, h->c64, h->D, (const T *)h->Z, h->run, h->sh, h->pcol);
         const int nf = kResBlocks / kFold;
         k_fam_fold<<<blocks_for((int64_t)nf * 5 * h->B, 256), 256, 0, st>>>(h->B, kResBlocks, h->prow, h->pcol,
@@ -801,8 +805,9 @@ void fam_iteration_t(uv_family *h, hipStream_t st, bool check)
 
 void fam_iteration(uv_family *h, hipStream_t st, bool check)
 {
-    if (h->o.precision == UV_MIXED) fam_iteration_t<float>(h, st, check);
-    else fam_iteration_t<double>(h, st, check);
+    if (h->o.precision == UV_MIXED) fam_iteration_t<float, 32>(h, st, check);
+    else if (h->G == 16) fam_iteration_t<double, 16>(h, st, check);
+    else fam_iteration_t<double, 32>(h, st, check);
 }
 
 int fam_sync(uv_family *h)
@@ -902,7 +907,7 @@ int family_create(const uv_csr *A, const double *c, int32_t B, const uv_opts *op
     const int m = h->m, n = h->n, nnz = h->nnz;
     const bool mixed = o.precision == UV_MIXED;
     const size_t ts = mixed ? 4 : 8;
-    h->G = mixed ? fam_group<float>() : fam_group<double>();
+    h->G = fam_group(!mixed, B, m);
     h->big = (size_t)B * ((2 * ts + 8) * n + (2 * ts + 8) * m) > ((size_t)256 << 20);
     if (o.hip_stream) h->stream = (hipStream_t)o.hip_stream;
     else {
@@ -1074,11 +1079,12 @@ int family_set_start_predicted(uv_family *h, const float *xl_dev, int64_t ld, in
     const int ng = B / h->G, bc = (h->n + kFamThreads / h->G - 1) / (kFamThreads / h->G);
     const double im = 1.0 / h->o.mu;
     if (h->o.precision == UV_MIXED) {
-        k_fam_dual_start<float><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(
+        k_fam_dual_start<float, 32><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(
             h->n, h->m, ng, bc, h->cp, h->ri, h->vc64, h->LAM, h->c64, (const float *)h->X, (float *)h->Z, h->D);
         k_fam_start<float><<<blocks_for(Bm, 256), 256, 0, st>>>(Bm, h->LAM, (float *)h->U, im);
     } else {
-        k_fam_dual_start<double><<<fam_grid(ng, bc), kFamThreads, 0, st>>>(
+        auto *dual = h->G == 16 ? k_fam_dual_start<double, 16> : k_fam_dual_start<double, 32>;
+        dual<<<fam_grid(ng, bc), kFamThreads, 0, st>>>(
             h->n, h->m, ng, bc, h->cp, h->ri, h->vc64, h->LAM, h->c64, (const double *)h->X, (double *)h->Z, h->D);
         k_fam_start<double><<<blocks_for(Bm, 256), 256, 0, st>>>(Bm, h->LAM, (double *)h->U, im);
     }

@@ -72,3 +72,60 @@ def test_stopped_groups_are_left_alone():
         assert np.array_equal(before[q][:32], after[q][:32]), q
         assert not np.array_equal(before[q][32:], after[q][32:]), q
     assert {r["status"] for r in res[:32]} == {"max_iter"} and {r["iter"] for r in res[32:]} == {10}
+
+
+@pytest.mark.parametrize("m,n,B", [(16_384, 17_001, 128), (16_385, 17_001, 128), (16_390, 17_001, 192)])
+def test_fp64_groups_match_oracle(m, n, B):
+    """Both sides of the rule for groups of 16 and 32 instances in FP64,
+    started from predicted points on the device and refilled."""
+    import torch
+    rng = np.random.default_rng(m + B)
+    A = sp.csr_matrix((rng.standard_normal(5 * n), (rng.integers(0, m, 5 * n), np.repeat(np.arange(n), 5))), shape=(m, n))
+    A.sum_duplicates()
+    A.sort_indices()
+    nb = B - 7
+    b = np.stack([A @ np.maximum(rng.standard_normal(n), 0.0) for _ in range(nb)])
+    c = A.T @ rng.standard_normal(m) + rng.uniform(0.0, 1.0, n)
+    args = (m, n, A.indptr.astype(np.int64), A.indices.astype(np.int32), A.data, c)
+    start = rng.standard_normal((nb, n + m)).astype(np.float32)
+    with Family(*args, B=B, precision="fp64", eps=0.0, check_every=4) as F:
+        F.set_rhs(b)
+        xl = torch.from_numpy(start).cuda()
+        F.set_start_predicted(xl.data_ptr(), n + m)
+        F.iterate(9)
+        sol = F.solution()
+    worst = 0.0
+    for l in (0, 15, 16, 31, 32, nb - 1):
+        x, lam = start[l, :n].astype(np.float64), start[l, n:].astype(np.float64)
+        o = oracle.Oracle(m, n, args[2], args[3], args[4], b[l], c, n, np.zeros(0, np.int32))
+        o.set_start(x, np.maximum(x, 0.0), np.maximum(c + A.T @ lam, 0.0), lam)
+        o.iterate(9)
+        s = o.state()
+        worst = max(worst, max(rel(sol[q][l], s[q]) for q in KEYS))
+    sys.__stderr__.write(f"[gpu-test] family FP64 groups m={m} B={B}: {worst}\n")
+    assert worst <= 1e-9
+
+
+def test_fp64_family_of_long_segments_keeps_its_speed():
+    """60 entries a column: FP64 at most 1.85 times mixed precision, twice the
+    bytes (groups of 16 instances, which run twice the instructions: 2.03)."""
+    import time
+    m, n, B = 2000, 4000, 128
+    rng = np.random.default_rng(7)
+    A = sp.csr_matrix((rng.standard_normal(60 * n), (rng.integers(0, m, 60 * n), np.repeat(np.arange(n), 60))), shape=(m, n))
+    A.sum_duplicates()
+    A.sort_indices()
+    us = {}
+    for precision in ("fp64", "mixed"):
+        with Family(m, n, A.indptr.astype(np.int64), A.indices.astype(np.int32), A.data, np.ones(n), B=B,
+                    precision=precision, eps=0.0) as F:
+            F.set_rhs(rng.standard_normal((B, m)))
+            F.iterate(50)
+            best = 1e9
+            for _ in range(5):
+                t0 = time.perf_counter()
+                F.iterate(100)
+                best = min(best, time.perf_counter() - t0)
+            us[precision] = best * 1e4
+    sys.__stderr__.write(f"[gpu-test] family of long segments: {us} us an iteration\n")
+    assert us["fp64"] <= 1.85 * us["mixed"], us
