@@ -5,7 +5,7 @@
 // PCA of the solution matrix Y (N samples x D features, D large):
 //   mean, center Y in place, Z = Y Omega (Omega Gaussian, D x l),
 //   q rounds of Z <- orth(Y (orth(Y' Z))),  Q = orth(Z),  B = Q' Y (l x D),
-//   B B' = U S^2 U' (Jacobi),  basis = top-k rows of S^{-1} U' B,
+//   B B' = U S^2 U' (Jacobi),  basis = top-k rows of S^{-1} U' B, orthonormalized,
 // i.e. the randomized range finder with power iterations of Halko,
 // Martinsson and Tropp; orth() is Cholesky QR of FP64 Gram matrices, applied
 // until the columns are orthonormal, with a random column for a dependent one.
@@ -536,6 +536,13 @@ std::vector<double> inv_lower(const std::vector<double> &L, int l)
     return X;
 }
 
+// Largest l whose eigenproblem is left to the host: its time grows as l^3, the
+// device's as l with about 4 us a round.  A fit of 300 x 3000 samples, device /
+// host, us: l = 16 1277 / 869, 32 1786 / 1150, 48 2398 / 1605, 64 3087 / 2774 (2552
+// / 2572 with a falling spectrum), 72 3722 / 3577 (3071 / 2980), 80 3885 / 4732, 128
+// 6747 / 20329.
+constexpr int kHostEig = 64;
+
 // Eigenvalues (descending) and eigenvectors (columns of the row-major V) of
 // the symmetric l x l matrix G, by k_jacobi; dev: 3 l^2 + 2 doubles of
 // device scratch.
@@ -774,7 +781,8 @@ int pca_fit(float *Y, int64_t N, int64_t D, int64_t ld, int32_t k, int32_t overs
         bool finite = false;
         if ((rc = gram(Bm, l, D, 1, D, finite)) != UV_OK) break;                                             // G = Bm Bm'
         std::vector<double> w(l, std::nan("")), V(ll, std::nan(""));
-        if (finite && (rc = sym_eig_device(l, G, eig, w, V, st)) != UV_OK) break;
+        if (finite && l <= kHostEig) uvla_sym_eig(l, gd.data(), w.data(), V.data());
+        else if (finite && (rc = sym_eig_device(l, G, eig, w, V, st)) != UV_OK) break;
         // basis row c = (V[:, c]' Bm) / sigma_c for the top k
         std::vector<float> P((size_t)k * l);
         for (int c = 0; c < k; ++c) {
