@@ -679,7 +679,8 @@ def main():
         slab_search = {"rule": {"slabs_row": main_r["slabs_row"], "slabs_col": main_r["slabs_col"]},
                        "search": {"slabs_row": rec["slabs_row"], "slabs_col": rec["slabs_col"]},
                        "trials": rec["trials"]}
-    floor = gather_floor(m, n, nnz, main_r["slabs_row"], main_r["slabs_col"])
+    gathers = main_r["product_row"] in ("lanes", "slabs") and main_r["product_col"] in ("lanes", "slabs")
+    floor = gather_floor(m, n, nnz, main_r["slabs_row"], main_r["slabs_col"]) if gathers else None
     log(f"gather floor (ms): {floor}")
     row_b, col_b = alg_bytes(m, n, nnz, "fp64")
     kern = {"col": (col_b, main_r["ms_col"]), "row": (row_b, main_r["ms_row"])}
@@ -752,7 +753,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"{args.workload}: {describe(inst)}, mu={args.mu}, check_every={args.check_every}",
                    "launch": {k: main_r[k] for k in ("lanes_row", "unroll_row", "lanes_col", "slabs_row", "slabs_col",
-                                                     "unroll_col")}},
+                                                     "unroll_col", "product_row", "product_col")}},
         "time_to_1e-4_s": main_r["ttk_s"],
         "iters_to_1e-4": main_r["ttk_iters"],
         "time_to_1e-4_full_checks_s": main_r.get("ttk_full_checks_s"),
@@ -766,8 +767,10 @@ def main():
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(dom),
                      "alg_bytes_per_launch": kern[dom][0], "ms_per_launch": kern[dom][1],
+                     # a binned or staged product gathers from LDS: the probe is no floor of it
                      "gather_floor": {"ms_per_launch": floor[dom], "frac": floor[dom] / kern[dom][1],
-                                      "what": "random-gather probe with the same pairs, table and slabs"}},
+                                      "what": "random-gather probe with the same pairs, table and slabs"}
+                     if floor else None},
         "mixed": extra,
         "batched": batched,
         "learned_warm_start": parametric,

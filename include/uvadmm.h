@@ -102,7 +102,11 @@ typedef struct {
     int32_t lanes_row;    /* lanes per row in the A x pass without slabs or
                              with slab_kernel 2 (0 = automatic; else 1, 2,
                              4, 8, 16, 32 or 64); the chunked slab passes do
-                             not use lanes_* or unroll_* */
+                             not use lanes_* or unroll_*.  A pass with any of
+                             lanes_*, unroll_*, slabs_* or slab_kernel set
+                             runs as they say: the binned and the staged
+                             product are automatic choices only (see
+                             solver_products) */
     int32_t lanes_col;    /* lanes per column in the A'u pass (same values) */
     int32_t use_graph;    /* 1 = replay check_every iterations as one captured
                              HIP graph; 0 = launch kernels one by one */
@@ -110,11 +114,18 @@ typedef struct {
                              (0 = automatic; else 1, 2, 4 or 8) */
     int32_t unroll_col;   /* same for the A'u pass */
     int32_t slabs_row;    /* XCD slabs of x in the A x pass: 0 = automatic
-                             (none up to 2 MiB of x, two up to 6 MiB, else
-                             four), 1 = none, 2, 4, 8 */
+                             (S = 1, none, up to 2 MiB of x, two up to 6
+                             MiB, else four; the binned product instead
+                             where S > 1 and nnz + 2 S m >= 5.6e6, unless a
+                             row has more than 5120 entries; the staged
+                             product where S = 1, x fits eight parts of
+                             160,000 bytes, P of them, nnz >= 9e5 and nnz >=
+                             10 P m), 1 = none, 2, 4, 8 */
     int32_t slabs_col;    /* XCD slabs of u in the A'u pass: 0 = automatic
                              (none up to 2 MiB of u, two up to 16 MiB, else
-                             four), 1 = none, 2, 4, 8 */
+                             four; the other products by the same rules with
+                             n in place of m, u held as FP64 in the parts),
+                             1 = none, 2, 4, 8 */
     int32_t criterion;    /* UV_CRIT_KKT, UV_CRIT_INF or UV_CRIT_POGS */
     double eps_abs;       /* absolute tolerance of UV_CRIT_INF; the bound
                              on ||A x - b||_2 of UV_CRIT_POGS */
@@ -320,11 +331,23 @@ int solver_time_kernels(uv_solver *s, int32_t iters, double *ms_col,
 /* The resolved launch shape: shape[0] lanes per row and shape[1] gathers in
  * flight per lane in the row pass, shape[2], shape[3] the same for the
  * column pass, shape[4], shape[5] the XCD slab counts of the row and column
- * passes, shape[6] 1 on the resident path (shape holds 7 entries).  On the
+ * passes (1 where a pass has none, also because its product is binned),
+ * shape[6] 1 on the resident path (shape holds 7 entries).  On the
  * resident path solver_iterate runs the resident kernel; the other calls
  * (residual queries between checks, resume, solver_time_kernels) use the
  * sweep kernels on the same state. */
 int solver_launch_shape(const uv_solver *s, int32_t *shape);
+
+/* The sparse product of the row pass (kind[0]) and of the column pass
+ * (kind[1]): lane groups over the matrix as it is, one product per XCD slab of
+ * the gathered vector, the binned product (the entries of a part of the vector
+ * multiplied from LDS, then summed by groups of segments) or the staged one
+ * (long segments over a vector held in LDS). */
+#define UV_PRODUCT_LANES  0
+#define UV_PRODUCT_SLABS  1
+#define UV_PRODUCT_BINNED 2
+#define UV_PRODUCT_STAGED 3
+int solver_products(const uv_solver *s, int32_t *kind);
 
 /* ------------------------------------------------------------------------
  * Batched solver: many independent problems with the orthant cone
@@ -529,7 +552,8 @@ int standard_iterate(uv_standard *h, int64_t k, int32_t *done);
 int standard_residuals(uv_standard *h, uv_residuals *r, int64_t *cg_steps);
 int standard_solution(uv_standard *h, double *x1, double *x2, double *lam,
                       double *nu, double *delta);
-/* Slab counts of the row and column products (either may be NULL). */
+/* Slab counts of the row and column products, 1 for one that is binned (either
+ * may be NULL). */
 int standard_launch_shape(uv_standard *h, int32_t *slabs_row, int32_t *slabs_col);
 void standard_destroy(uv_standard *h);
 

@@ -3190,9 +3190,19 @@ int solver_launch_shape(const uv_solver *s, int32_t *shape)
     shape[1] = s->E_row;
     shape[2] = s->L_col;
     shape[3] = s->E_col;
-    shape[4] = s->S_row;
-    shape[5] = s->S_col;
+    shape[4] = s->bin_row.on() ? 1 : s->S_row;
+    shape[5] = s->bin_col.on() ? 1 : s->S_col;
     shape[6] = s->resident ? 1 : 0;
+    return UV_OK;
+}
+
+int solver_products(const uv_solver *s, int32_t *kind)
+{
+    if (!s || !kind) return UV_EINVAL;
+    kind[0] = s->bin_row.on() ? UV_PRODUCT_BINNED : s->stg_row.on() ? UV_PRODUCT_STAGED
+              : s->S_row > 1 ? UV_PRODUCT_SLABS : UV_PRODUCT_LANES;
+    kind[1] = s->bin_col.on() ? UV_PRODUCT_BINNED : s->stg_col.on() ? UV_PRODUCT_STAGED
+              : s->S_col > 1 ? UV_PRODUCT_SLABS : UV_PRODUCT_LANES;
     return UV_OK;
 }
 

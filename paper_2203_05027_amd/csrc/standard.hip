@@ -837,8 +837,8 @@ int standard_solution(uv_standard *h, double *x1, double *x2, double *lam, doubl
 int standard_launch_shape(uv_standard *h, int32_t *slabs_row, int32_t *slabs_col)
 {
     if (!h) return UV_EINVAL;
-    if (slabs_row) *slabs_row = h->S_row;
-    if (slabs_col) *slabs_col = h->S_col;
+    if (slabs_row) *slabs_row = h->parts_row();
+    if (slabs_col) *slabs_col = h->parts_col();
     return UV_OK;
 }
 

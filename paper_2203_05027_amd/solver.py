@@ -129,6 +129,8 @@ def lib():
     L.solver_time_kernels.restype = ctypes.c_int
     L.solver_launch_shape.argtypes = [P, ctypes.POINTER(i32)]
     L.solver_launch_shape.restype = ctypes.c_int
+    L.solver_products.argtypes = [P, ctypes.POINTER(i32)]
+    L.solver_products.restype = ctypes.c_int
     L.solver_set_rhs.argtypes = [P, P]
     L.solver_set_rhs.restype = ctypes.c_int
     L.solver_history.argtypes = [P, i32, ctypes.POINTER(UvHistory), ctypes.POINTER(i32)]
@@ -229,6 +231,9 @@ def solve(inst, iters, noalloc=False, **kw):
     res = {k: getattr(r, k) for k, _ in UvResiduals._fields_}
     res["status"] = STATUS.get(res["status"], res["status"])
     return rc, {"x": x, "z": z, "delta": d, "lambda": lam}, res
+
+
+_PRODUCTS = ("lanes", "slabs", "binned", "staged")
 
 
 class Solver:
@@ -338,11 +343,14 @@ class Solver:
         return [{k: getattr(buf[i], k) for k, _ in UvHistory._fields_} for i in range(cnt.value)]
 
     def launch_shape(self) -> dict:
-        """Lanes and gathers in flight per lane of the row and column passes."""
-        a = (ctypes.c_int32 * 7)()
+        """Lanes and gathers in flight per lane of the row and column passes,
+        their slabs and products ("lanes", "slabs", "binned" or "staged")."""
+        a, k = (ctypes.c_int32 * 7)(), (ctypes.c_int32 * 2)()
         _check(lib().solver_launch_shape(self._h, a), "solver_launch_shape")
+        _check(lib().solver_products(self._h, k), "solver_products")
         return {"lanes_row": a[0], "unroll_row": a[1], "lanes_col": a[2], "unroll_col": a[3],
-                "slabs_row": a[4], "slabs_col": a[5], "resident": bool(a[6])}
+                "slabs_row": a[4], "slabs_col": a[5], "resident": bool(a[6]),
+                "product_row": _PRODUCTS[k[0]], "product_col": _PRODUCTS[k[1]]}
 
 
 def _bind_batch(L):
