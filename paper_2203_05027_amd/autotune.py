@@ -92,26 +92,36 @@ SLABS = (1, 2, 4, 8)
 
 
 def slab_signature(inst, precision: str) -> str:
-    """Shape key of a single problem: sizes rounded to powers of two, cone mix."""
+    """Shape key of a single problem: sizes rounded to powers of two, cone mix
+    (the number after "slabs" changes with what a record means)."""
     def r(v):
         return 0 if v <= 0 else 2 ** round(math.log2(v))
     soc = inst.get("soc_sizes")
     cones = "orthant" if soc is None or len(soc) == 0 else f"soc{r(len(soc))}"
-    return f"slabs|{precision}|m={r(inst['m'])}|n={r(inst['n'])}|nnz={r(inst['nnz'])}|{cones}"
+    return f"slabs2|{precision}|m={r(inst['m'])}|n={r(inst['n'])}|nnz={r(inst['nnz'])}|{cones}"
 
 
 def tune_slabs(inst, precision: str = "fp64", iters: int = 20, cache_path: str | None = DEFAULT_CACHE,
                slabs=SLABS, log=None) -> dict:
     """Times the column and row passes of ``inst`` (solver_time_kernels) for
-    every slab count of the gathered vectors and returns the fastest pair
-    {"slabs_row", "slabs_col", "ms_row", "ms_col"}; the two passes are
-    independent, so each count is chosen on its own pass.  Cached by shape."""
+    every slab count of the gathered vectors and as the solver would run them
+    by itself, and returns {"slabs_row", "slabs_col"} to create it with: per
+    pass the fastest count, or 0 where the automatic choice is as fast (it may
+    be a product without slabs; always 0 on the resident path, which slab
+    counts switch off).  "ms_row", "ms_col" are the fastest counts' times,
+    "auto_ms_row", "auto_ms_col" the automatic choice's.  Cached by shape."""
     from .solver import Solver
 
     key = slab_signature(inst, precision)
     cache = _load(cache_path) if cache_path else {}
     if key in cache:
         return dict(cache[key], cached=True)
+    with Solver.from_instance(inst, precision=precision, eps=0.0) as s:
+        s.iterate(2)
+        auto_col, auto_row = s.time_kernels(iters)
+        resident = s.launch_shape()["resident"]
+    if log:
+        log(f"automatic: row pass {auto_row:.4f} ms, column pass {auto_col:.4f} ms")
     best_row = best_col = None
     trials = []
     for S in slabs:
@@ -127,8 +137,11 @@ def tune_slabs(inst, precision: str = "fp64", iters: int = 20, cache_path: str |
             best_row = (S, ms_row)
         if best_col is None or ms_col < best_col[1]:
             best_col = (S, ms_col)
-    rec = {"slabs_row": best_row[0], "slabs_col": best_col[0], "ms_row": best_row[1], "ms_col": best_col[1],
-           "iters": iters}
+    def choice(best, auto):  # a count has to be faster by more than two timings of one kernel differ
+        return 0 if resident or auto <= 1.02 * best[1] else best[0]
+
+    rec = {"slabs_row": choice(best_row, auto_row), "slabs_col": choice(best_col, auto_col), "ms_row": best_row[1],
+           "ms_col": best_col[1], "auto_ms_row": auto_row, "auto_ms_col": auto_col, "iters": iters}
     if cache_path:
         cache = _load(cache_path)
         cache[key] = rec

@@ -1491,7 +1491,7 @@ struct uv_solver {
     int E_row = 4, E_col = 4;   // gathers in flight per lane
     int S_row = 1, S_col = 1;   // XCD slabs of x (row pass) and of u (column pass)
     bool chunked = true;        // slab passes by 64-segment chunks (else lane groups)
-    bool forced = false;        // a launch shape of the sweep kernels was asked for
+    bool forced_row = false, forced_col = false;  // a launch shape of that pass's kernels was asked for
     bool batch8 = true;         // chunk batches of eight 64-entry steps (else four)
     int *srp = nullptr, *sci = nullptr;  // row-pass slab copy (S_row * m + 1 offsets)
     void *sva = nullptr;
@@ -2210,8 +2210,8 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
         s->c = s->c64;
     }
     s->nblk_row = (int)blocks_for(m, kWG / s->L_row);
-    const int stg_r = s->resident || s->forced || s->S_row > 1 ? 0 : staged_parts(n, (int)ts);
-    const int stg_c = s->resident || s->forced || s->S_col > 1 ? 0 : staged_parts(m, 8);  // the check gathers FP64 lambda
+    const int stg_r = s->resident || s->forced_row || s->S_row > 1 ? 0 : staged_parts(n, (int)ts);
+    const int stg_c = s->resident || s->forced_col || s->S_col > 1 ? 0 : staged_parts(m, 8);  // the check gathers FP64 lambda
     const bool use_r = staged_pays(stg_r, m, nnz), use_c = staged_pays(stg_c, n, nnz);
     s->nblk_row_fused = s->S_row > 1 || use_r ? (int)blocks_for(m, kWG) : s->nblk_row;
     s->nblk_rescol = (int)blocks_for(n, kWG / s->L_col);
@@ -2298,12 +2298,12 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
     // Column-major copy of A.
     if (!build_csc(m, n, nnz, s->rp, s->ci, s->va64, s->cp, s->ri, s->vc64, cnt, bsum, st)) return UV_EHIP;
 
-    // Binned products in place of slabs where they pay and no launch shape is
-    // forced.
-    if (!s->forced) {
+    // Binned products in place of slabs where they pay and no launch shape of
+    // the pass is forced.
+    {
         for (int pass = 0; pass < 2; ++pass) {
             const int S = pass == 0 ? s->S_row : s->S_col;
-            if (S == 1 || !bins_pay(S, pass == 0 ? m : n, nnz)) continue;
+            if (S == 1 || (pass == 0 ? s->forced_row : s->forced_col) || !bins_pay(S, pass == 0 ? m : n, nnz)) continue;
             auto get = [&](size_t bytes) { return (void *)dalloc<char>(s, bytes); };
             const BinBuilt r = pass == 0 ? build_bins(m, n, nnz, s->rp, s->ci, s->va64, mixed, get, st, &s->bin_row)
                                          : build_bins(n, m, nnz, s->cp, s->ri, s->vc64, mixed, get, st, &s->bin_col);
@@ -2547,9 +2547,9 @@ int solver_create(const uv_csr *A, const double *b, const double *c, const uv_co
             return UV_EINVAL;
         }
         // automatic only when no launch shape of the sweep kernels is forced
-        s->forced = o.lanes_row || o.lanes_col || o.unroll_row || o.unroll_col || o.slabs_row || o.slabs_col ||
-                    o.slab_kernel;
-        s->resident = fits && (o.resident == 2 || (o.resident == 0 && !s->forced));
+        s->forced_row = o.lanes_row || o.unroll_row || o.slabs_row || o.slab_kernel;
+        s->forced_col = o.lanes_col || o.unroll_col || o.slabs_col || o.slab_kernel;
+        s->resident = fits && (o.resident == 2 || (o.resident == 0 && !s->forced_row && !s->forced_col));
         s->res_lr = resident_lanes(A->m, A->nnz);
         s->res_lc = resident_lanes(A->n, A->nnz);
         if (s->resident) {

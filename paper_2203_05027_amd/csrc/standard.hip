@@ -661,7 +661,7 @@ int standard_create(const uv_csr *A, const double *b, const double *c, const uv_
     h->scp = h->cp; h->sri = h->ri; h->svc = h->vc;
     for (int pass = 0; pass < 2; ++pass) {
         const int S = pass == 0 ? h->S_row : h->S_col, nr = pass == 0 ? m : n;
-        if (S == 1 || o.slabs_row || o.slabs_col || !bins_pay(S, nr, nnz)) continue;
+        if (S == 1 || (pass == 0 ? o.slabs_row : o.slabs_col) || !bins_pay(S, nr, nnz)) continue;
         auto get = [&](size_t bytes) { return (void *)salloc<char>(h, bytes); };
         const BinBuilt r = pass == 0 ? build_bins(m, n, nnz, h->rp, h->ci, h->va, false, get, st, &h->bin_row)
                                      : build_bins(n, m, nnz, h->cp, h->ri, h->vc, false, get, st, &h->bin_col);
