@@ -404,13 +404,24 @@ k_batch_norms(BInst *inst, const double *__restrict__ b64, const double *__restr
 
 __global__ void k_batch_reset(int *queue) { *queue = 0; }
 
-// u = -lambda/mu on one instance's rows (the start mapping).
+// One instance's start from (pinned host) memory in the device's numbering, laid
+// out as k_batch_out's vectors: x, z, delta, lambda where `have` has bit 0, 1, 2, 3
+// and zeros elsewhere, and u = -lambda/mu (the start mapping).
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_batch_start_u(int r0, int m, const double *__restrict__ lam, T *__restrict__ u, double inv_mu)
+k_batch_in(int c0, int n, int r0, int m, int have, const double *__restrict__ in, T *__restrict__ x, T *__restrict__ z,
+           double *__restrict__ delta, double *__restrict__ lam, T *__restrict__ u, double inv_mu)
 {
-    int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < m) u[r0 + i] = (T)(-lam[r0 + i] * inv_mu);
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t < n) {
+        x[c0 + t] = have & 1 ? (T)in[t] : (T)0;
+        z[c0 + t] = have & 2 ? (T)in[n + t] : (T)0;
+        delta[c0 + t] = have & 4 ? in[2 * n + t] : 0.0;
+    } else if (t < n + m) {
+        const double l = have & 8 ? in[2 * n + t] : 0.0;  // 3 n + (t - n)
+        lam[r0 + t - n] = l;
+        u[r0 + t - n] = (T)(-l * inv_mu);
+    }
 }
 
 template <typename T, bool ZC>
@@ -653,11 +664,11 @@ struct uv_batch {
     bool sliced = false;         // their padding's zeros fit LDS with x and u
     std::vector<int> rmap, cmap; // instance-local numbers of the caller for the device's rows and columns
     int *rmap_d = nullptr, *cmap_d = nullptr;
-    double *out = nullptr;       // pinned: one instance's solution
+    double *out = nullptr;       // pinned: one instance's solution or start
     double *va64 = nullptr, *vc64 = nullptr, *b64 = nullptr, *c64 = nullptr;
     void *va = nullptr, *vc = nullptr, *b = nullptr, *c = nullptr, *fu = nullptr;
     void *x = nullptr, *z = nullptr, *u = nullptr;
-    double *lam = nullptr, *delta = nullptr, *scratch = nullptr;
+    double *lam = nullptr, *delta = nullptr;
     BInst *inst = nullptr;
     BInst *inst_host = nullptr;  // pinned mirror
     int *order = nullptr, *queue = nullptr, *budget = nullptr;
@@ -985,7 +996,6 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
     h->c64 = balloc<double>(h, N);
     h->lam = balloc<double>(h, M);
     h->delta = balloc<double>(h, N);
-    h->scratch = balloc<double>(h, std::max(M, N));
     h->x = balloc<char>(h, ts * N);
     h->z = balloc<char>(h, ts * N);
     h->u = balloc<char>(h, ts * M);
@@ -1011,7 +1021,7 @@ int batch_create(int32_t count, const uv_csr *A, const double *const *b, const d
     int *cnt = balloc<int>(h, N);
     int *bsum = balloc<int>(h, blocks_for(N, 4 * kWG));
     for (void *p : {(void *)h->rp, (void *)h->ci, (void *)h->va64, (void *)h->cp, (void *)h->ri, (void *)h->vc64, (void *)h->cl, (void *)h->rl,
-                    (void *)h->b64, (void *)h->c64, (void *)h->lam, (void *)h->delta, (void *)h->scratch, h->x,
+                    (void *)h->b64, (void *)h->c64, (void *)h->lam, (void *)h->delta, h->x,
                     h->z, h->u, h->fu, h->va, h->vc, h->b, h->c, (void *)h->inst, (void *)h->order,
                     (void *)h->queue, (void *)h->budget, (void *)h->rmap_d, (void *)h->cmap_d, (void *)h->ccnt,
                     (void *)cnt, (void *)bsum})
@@ -1265,41 +1275,24 @@ int batch_set_start(uv_batch *h, int32_t i, const double *x, const double *z, co
     if (!h || i < 0 || i >= h->count) return UV_EINVAL;
     BInst &I = h->inst_host[i];
     hipStream_t st = h->stream;
-    const bool mixed = h->o.precision == UV_MIXED;
-    const size_t ts = mixed ? 4 : 8;
-    // in the device's numbering, by way of the pinned buffer
-    auto order = [&](const double *src, const std::vector<int> &map, int off, int len) -> const double * {
-        if (!src) return nullptr;
-        for (int q = 0; q < len; ++q) h->out[q] = src[map[(size_t)off + q]];
-        return h->out;
-    };
-    auto put_t = [&](void *dst, const double *src, int off, int len) -> int {
-        char *d = (char *)dst + ts * off;
-        if (!src) return hipMemsetAsync(d, 0, ts * len, st) == hipSuccess ? UV_OK : UV_EHIP;
-        src = order(src, h->cmap, I.col_off, I.n);
-        if (!mixed) return hipMemcpyAsync(d, src, 8 * (size_t)len, hipMemcpyHostToDevice, st) == hipSuccess &&
-                                   hipStreamSynchronize(st) == hipSuccess
-                               ? UV_OK : UV_EHIP;
-        if (hipMemcpyAsync(h->scratch, src, 8 * (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess)
-            return UV_EHIP;
-        k_narrow<float><<<blocks_for(len, kWG), kWG, 0, st>>>(len, h->scratch, (float *)d);
-        return hipStreamSynchronize(st) == hipSuccess ? UV_OK : UV_EHIP;
-    };
-    int rc;
-    if ((rc = put_t(h->x, x, I.col_off, I.n)) != UV_OK) return rc;
-    if ((rc = put_t(h->z, z, I.col_off, I.n)) != UV_OK) return rc;
-    if (delta) {
-        UV_BTRY(hipMemcpyAsync(h->delta + I.col_off, order(delta, h->cmap, I.col_off, I.n), 8 * (size_t)I.n,
-                               hipMemcpyHostToDevice, st));
-        UV_BTRY(hipStreamSynchronize(st));
-    } else UV_BTRY(hipMemsetAsync(h->delta + I.col_off, 0, 8 * (size_t)I.n, st));
-    if (lambda)
-        UV_BTRY(hipMemcpyAsync(h->lam + I.row_off, order(lambda, h->rmap, I.row_off, I.m), 8 * (size_t)I.m,
-                               hipMemcpyHostToDevice, st));
-    else UV_BTRY(hipMemsetAsync(h->lam + I.row_off, 0, 8 * (size_t)I.m, st));
-    const double im = 1.0 / h->o.mu;
-    if (mixed) k_batch_start_u<float><<<blocks_for(I.m, 256), 256, 0, st>>>(I.row_off, I.m, h->lam, (float *)h->u, im);
-    else k_batch_start_u<double><<<blocks_for(I.m, 256), 256, 0, st>>>(I.row_off, I.m, h->lam, (double *)h->u, im);
+    // into the device's numbering on the way to the pinned buffer, then one launch and one wait
+    const double *src[4] = {x, z, delta, lambda};
+    int have = 0;
+    double *to = h->out;
+    for (int q = 0; q < 4; ++q) {
+        const int len = q < 3 ? I.n : I.m, *map = q < 3 ? h->cmap.data() + I.col_off : h->rmap.data() + I.row_off;
+        if (src[q]) {
+            have |= 1 << q;
+            for (int k = 0; k < len; ++k) to[k] = src[q][map[k]];
+        }
+        to += len;
+    }
+    const unsigned g = blocks_for((int64_t)I.n + I.m, 256);
+#define UV_IN_ARGS(T)                                                                                            \
+    I.col_off, I.n, I.row_off, I.m, have, h->out, (T *)h->x, (T *)h->z, h->delta, h->lam, (T *)h->u, 1.0 / h->o.mu
+    if (h->o.precision == UV_MIXED) k_batch_in<float><<<g, 256, 0, st>>>(UV_IN_ARGS(float));
+    else k_batch_in<double><<<g, 256, 0, st>>>(UV_IN_ARGS(double));
+#undef UV_IN_ARGS
     UV_BTRY(hipGetLastError());
     I.iter = 0;
     I.check_iter = -1;
