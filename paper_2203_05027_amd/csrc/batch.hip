@@ -834,29 +834,29 @@ int occupancy_grid(uv_batch *h)
 
 // The default tiles.  A workgroup's time for an iteration of an instance with
 // w = rows + columns + entries on T threads is about 2.5 + 0.2 w / T us (0.27 on
-// 1024; in FP64 a fifth more), and a compute unit cannot do it in less than 0.25
-// + 0.0005 w us (0.35 + 0.0007 w in FP64) whatever the number of workgroups that share it; a sweep
-// takes what the workgroups need that fetch the instances one by one, or the
-// compute units, whichever is longer.  Large or few instances want the
-// widest workgroup, many small ones as many workgroups as a compute unit
-// holds.  Measured (us a sweep, mixed, T = 128 / 256 / 512 / 1024): 4096 of 20 x
-// 40 6.4 / 9.1 / 19 / 37, of 50 x 100 10.6 / 11.3 / 23 / 42, of 200 x 400 31 /
-// 29 / 37 / 50, 1024 of 1200 x 2400 43 / 36 / 35 / 38, of 5000 x 10000 - / 318 /
-// 192 / 146; 64 of 200 x 400 7.7 / 3.9 / 3.5 / 3.2.
+// 1024; in FP64 a fifth more), and a compute unit cannot do it in less than 0.2 +
+// 0.0005 w + 0.0008 T us (0.28 + 0.0007 w + 0.0011 T in FP64) however many
+// workgroups share it; a sweep takes about the root of the squares of what the
+// workgroups need that fetch the instances one by one and of what the compute
+// units do.  Large or few instances want the widest workgroup, many small ones
+// as many narrow workgroups as a compute unit holds.  Measured (us a sweep, mixed, T = 64 / 128 / 256 / 512 /
+// 1024): 4096 of 20 x 40 5.3 / 6.4 / 9.1 / 19 / 37, of 50 x 100 9.7 / 10.6 / 11.3 /
+// 23 / 42, of 200 x 400 30 / 30 / 29 / 37 / 50, 1024 of 1200 x 2400 69 / 43 / 36 /
+// 35 / 38, of 5000 x 10000 - / - / 318 / 192 / 146; 64 of 200 x 400 8.5 / 5.5 / 3.9
+// / 3.5 / 3.2.
 // Rows: the sliced copy, but four lanes while an instance has fewer rows than
 // the workgroup about a quarter of its threads (200 rows on 1024: 3.2 against
-// 3.7 us; on 256: 5.6 against 3.9), two on the narrow workgroup (4096 of 20 x 40
-// 6.4 against 7.4 us sliced and 6.0 with four, of 100 x 200 17.5 against 17.3
-// and 18.3).
+// 3.7 us; on 256: 5.6 against 3.9), two on narrow workgroups (4096 of 100 x 200 on
+// 64: 16.4 against 18.9 us sliced and 17.2 with four; in FP64 up to 512 rows, of
+// 200 x 400 on 128: 38.9 against 44.6 and 39.1).
 int default_tiles(uv_batch *h, const std::vector<double> &weight)  // the instances', longest first
 {
-    static const int rows[4][2] = {{2, 2}, {4, 1}, {4, 1}, {4, 4}};  // buckets 0 and 1 on 128, 256, 512, 1024 threads
     const bool fp64 = h->o.precision == UV_FP64;
     int dev = 0, cus = 0, best_t = 1024;
     UV_BTRY(hipGetDevice(&dev));
     UV_BTRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     double best = 0.0;
-    for (int t = 1024, rc; t >= 128; t /= 2) {
+    for (int t = 1024, rc; t >= 64; t /= 2) {
         h->threads = t;
         if ((rc = occupancy_grid(h)) != UV_OK) return rc;
         std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
@@ -869,17 +869,17 @@ int default_tiles(uv_batch *h, const std::vector<double> &weight)  // the instan
             }
             free_at.push(at);
             last = std::max(last, at);
-            cu += fp64 ? 0.35 + 0.0007 * w : 0.25 + 0.0005 * w;
+            cu += fp64 ? 0.28 + 0.0007 * w + 0.0011 * t : 0.2 + 0.0005 * w + 0.0008 * t;
         }
-        const double us = std::max(last, cu / cus);
-        if (t == 1024 || us < 0.97 * best) {  // a wider one unless a narrower is clearly faster
+        const double us = std::hypot(last, cu / cus);
+        if (t == 1024 || us < 0.9 * best) {  // a wider one unless a narrower is clearly faster
             best = us;
             best_t = t;
         }
     }
     h->threads = best_t;
-    const int *r = rows[best_t == 128 ? 0 : best_t == 256 ? 1 : best_t == 512 ? 2 : 3];
-    const int tiles[2 * 4] = {r[0], 0, r[1], 0, 1, 0, 1, 0};
+    const int narrow = best_t <= 128;
+    const int tiles[2 * 4] = {narrow ? 2 : 4, 0, best_t == 1024 ? 4 : narrow && fp64 ? 2 : 1, 0, 1, 0, 1, 0};
     std::memcpy(h->tiles, tiles, sizeof(tiles));
     return UV_OK;
 }
