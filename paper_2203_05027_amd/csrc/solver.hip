@@ -1024,7 +1024,7 @@ k_resident(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict__ rp
            const double *__restrict__ c64, const T *__restrict__ fu, T *__restrict__ x, T *__restrict__ z,
            T *__restrict__ u, double *__restrict__ lam, double *__restrict__ delta, double mu, long long iters,
            int mode, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
-           HistRing hist, int gated)
+           HistRing hist, int gated, const unsigned short *)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ double red[10][kResThreads / 64], sv[10], nrm[4];
@@ -1313,7 +1313,7 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
                const double *__restrict__ c64, const T *__restrict__ fu, T *__restrict__ x, T *__restrict__ z,
                T *__restrict__ u, double *__restrict__ lam, double *__restrict__ delta, double mu, long long iters,
                int mode, int check_every, double eps, double eps_abs, double eps_gap, int crit, DevStatus *st,
-               HistRing hist, int gated)
+               HistRing hist, int gated, const unsigned short *__restrict__ order)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ double red[10][kResThreads / 64], sv[10], nrm[4];
@@ -1345,15 +1345,22 @@ k_resident_reg(int m, int n, ResLayout L, int Lr, int Lc, const int *__restrict_
         nrm[3] = st->cinf;
     }
     __syncthreads();
-    // own column and row; the orders lie where x and u will
+    // own column and row: from the handle's order (columns, then rows), or
+    // ordered here, where x and u will lie
     const int gc = tid / Lc, lc = tid % Lc, gr = tid / Lr, lr = tid % Lr;
-    unsigned short *ord = (unsigned short *)(lds_raw + L.x);
-    res_order(n, Lc, cps, (unsigned char *)red, ord);
-    const int jc = gc < n ? ord[gc] : -1;
-    ord = (unsigned short *)(lds_raw + L.u);
-    res_order(m, Lr, rps, (unsigned char *)red, ord);
-    const int ic = gr < m ? ord[gr] : -1;
-    __syncthreads();
+    int jc = -1, ic = -1;
+    if (order) {
+        if (gc < n) jc = order[gc];
+        if (gr < m) ic = order[n + gr];
+    } else {
+        unsigned short *ord = (unsigned short *)(lds_raw + L.x);
+        res_order(n, Lc, cps, (unsigned char *)red, ord);
+        if (gc < n) jc = ord[gc];
+        ord = (unsigned short *)(lds_raw + L.u);
+        res_order(m, Lr, rps, (unsigned char *)red, ord);
+        if (gr < m) ic = ord[gr];
+        __syncthreads();
+    }
     for (int j = tid; j < n; j += NT) {
         xs[j] = x[j];
         zs[j] = z[j];
@@ -1510,6 +1517,7 @@ struct uv_solver {
     ResLayout rlay{};
     int res_lr = 1, res_lc = 1;  // lanes per row and per column of k_resident
     bool res_reg = false;        // k_resident_reg, not k_resident
+    unsigned short *res_order = nullptr;  // its columns and rows in lane-group order
     HistRec *hist = nullptr;     // residual history ring (opts.history records)
     double clock_khz = 0.0;      // rate of the GPU wall clock
     hipGraph_t graph = nullptr;
@@ -1999,6 +2007,7 @@ struct ResArgs {
     double mu, eps, eps_abs, eps_gap;
     int check_every, crit;
     int gated;  // checks primal half first (no history, opts.full_checks = 0)
+    const unsigned short *order;  // of k_resident_reg's columns and rows (null: ordered in the kernel)
 };
 
 // Whether a resident problem takes the register form: every lane group has at
@@ -2024,6 +2033,16 @@ bool resident_registers(const uv_csr *A)
     const int Lr = resident_lanes(m, A->nnz), Lc = resident_lanes(n, A->nnz);
     return std::max((row + Lr - 1) / Lr - kResRegs, 0) + std::max((col + Lc - 1) / Lc - kResRegs, 0) <=
            16 + A->nnz / 300;
+}
+
+// res_order on the host: the same keys and the same stable order.
+void order_segments(int cnt, int L, const int *len, unsigned short *order)
+{
+    int first[33] = {};
+    auto key = [&](int i) { return 31 - std::min((len[i] + L - 1) / L, 31); };
+    for (int i = 0; i < cnt; ++i) first[key(i) + 1] += 1;
+    for (int k = 0; k < 32; ++k) first[k + 1] += first[k];
+    for (int i = 0; i < cnt; ++i) order[first[key(i)]++] = (unsigned short)i;
 }
 
 template <typename T>
@@ -2056,7 +2075,7 @@ void resident_launch(const ResArgs &a, hipStream_t st, int64_t iters, int mode)
     a.m, a.n, a.L, a.Lr, a.Lc, a.rp, a.ci, (const T *)a.va, a.cp, a.ri, (const T *)a.vc, a.va64, a.vc64,         \
         (const T *)a.b, a.b64, (const T *)a.c, a.c64, (const T *)a.fu, (T *)a.x, (T *)a.z, (T *)a.u, a.lam,        \
         a.delta, a.mu, q, what, a.check_every, a.eps, a.eps_abs, a.eps_gap, a.crit, a.st, a.hist,  \
-        a.gated
+        a.gated, a.order
         if (a.mixed) resident_kernel<float>(a.reg)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(float));
         else resident_kernel<double>(a.reg)<<<1, kResThreads, a.L.bytes, st>>>(UV_RES_ARGS(double));
 #undef UV_RES_ARGS
@@ -2095,6 +2114,7 @@ ResArgs res_args(const uv_solver *s)
     a.gated = s->o.full_checks == 0 && !s->hist ? 1 : 0;
     a.mixed = s->o.precision == UV_MIXED;
     a.reg = s->res_reg;
+    a.order = s->res_order;
     a.mu = s->o.mu;
     a.eps = s->o.eps_kkt;
     a.eps_abs = s->o.eps_abs;
@@ -2297,6 +2317,20 @@ int setup(uv_solver *s, const uv_csr *A, const double *b, const double *c, const
 
     // Column-major copy of A.
     if (!build_csc(m, n, nnz, s->rp, s->ci, s->va64, s->cp, s->ri, s->vc64, cnt, bsum, st)) return UV_EHIP;
+
+    // k_resident_reg's order, made once: in the kernel it costs every launch
+    // 6.7 us (an iteration and its status, 500x1000: 31.1 -> 25.1 us).
+    if (s->resident && s->res_reg) {
+        int len[2 * kResThreads] = {};
+        unsigned short order[2 * kResThreads];
+        for (int k = 0; k < nnz; ++k) len[A->col_idx[k]] += 1;
+        for (int i = 0; i < m; ++i) len[n + i] = (int)(A->row_ptr[i + 1] - A->row_ptr[i]);
+        order_segments(n, s->res_lc, len, order);
+        order_segments(m, s->res_lr, len + n, order + n);
+        s->res_order = dalloc<unsigned short>(s, (size_t)n + m);
+        if (!s->res_order) return UV_ENOMEM;
+        UV_TRY(hipMemcpy(s->res_order, order, 2 * ((size_t)n + m), hipMemcpyHostToDevice));
+    }
 
     // Binned products in place of slabs where they pay and no launch shape of
     // the pass is forced.
