@@ -375,20 +375,21 @@ inline bool bins_pay(int S, int nseg, int nnz)
     return (int64_t)nnz + (int64_t)2 * S * nseg >= 5600000 && nnz <= INT32_MAX - (1 << 20);
 }
 
-// Device scratch of a plan's set-up, given back at its end.
+// A block of device scratch of a plan's set-up, given back at its end.
 struct BinScratch {
-    std::vector<void *> held;
+    unsigned char *p = nullptr;
+    size_t at = 0;
+    bool reserve(size_t bytes) { return uv::dev_malloc(&p, bytes) == hipSuccess; }
     template <typename T>
-    T *get(size_t count)
+    T *take(size_t count)
     {
-        T *p = nullptr;
-        if (uv::dev_malloc(&p, std::max<size_t>(count, 1) * sizeof(T)) != hipSuccess) return nullptr;
-        held.push_back(p);
-        return p;
+        T *q = (T *)(p + at);
+        at += (count * sizeof(T) + 255) / 256 * 256;
+        return q;
     }
     ~BinScratch()
     {
-        for (void *p : held) (void)hipFree(p);
+        if (p) (void)hipFree(p);
     }
 };
 
@@ -411,9 +412,10 @@ BinBuilt build_bins(int nseg, int len, int nnz, const int *ptr, const int *idx, 
     if (nnz < 1 || p.parts > kMaxParts) return BIN_NO;
 #define UV_BIN(expr) \
     if ((expr) != hipSuccess) return BIN_HIP
-    BinScratch tmp;
-    int longest = 0, *dl = tmp.get<int>(1);
-    if (!dl) return BIN_NOMEM;
+    BinScratch one, two;  // what the groups need, and the cells
+    const size_t most = (size_t)(nnz / (kCap / 2) + 2);  // groups before they are cut, at most
+    if (!one.reserve(4 * most + 1024)) return BIN_NOMEM;
+    int longest = 0, *dl = one.take<int>(1);
     UV_BIN(hipMemsetAsync(dl, 0, 4, st));
     k_bin_longest<<<blocks_for(nseg, kWG), kWG, 0, st>>>(nseg, ptr, dl);
     UV_BIN(hipMemcpyAsync(&longest, dl, 4, hipMemcpyDeviceToHost, st));
@@ -425,8 +427,7 @@ BinBuilt build_bins(int nseg, int len, int nnz, const int *ptr, const int *idx, 
     // pass 69 us, and 1165 us with 9e5 empty rows after them (slabs 102); cut,
     // 77 us.
     const int rough = (int)(((int64_t)nnz + step - 1) / step);
-    int *droug = tmp.get<int>((size_t)rough + 1);
-    if (!droug) return BIN_NOMEM;
+    int *droug = one.take<int>((size_t)rough + 1);
     k_bin_groups<<<blocks_for(rough + 1, kWG), kWG, 0, st>>>(nseg, ptr, rough, step, droug);
     std::vector<int> hg((size_t)rough + 1), gs(1, 0);
     UV_BIN(hipMemcpyAsync(hg.data(), droug, 4 * hg.size(), hipMemcpyDeviceToHost, st));
@@ -439,12 +440,13 @@ BinBuilt build_bins(int nseg, int len, int nnz, const int *ptr, const int *idx, 
     const int64_t cells = (int64_t)p.groups * p.parts;
     if (cells >= (1 << 28)) return BIN_NO;
     p.gseg = (int *)alloc(4 * ((size_t)p.groups + 1));
-    int *cnt = tmp.get<int>(cells), *off = tmp.get<int>(cells + 1), *dest = tmp.get<int>(cells);
-    int *bsum = tmp.get<int>((size_t)blocks_for(cells, 4 * kWG));
-    int *start = tmp.get<int>((size_t)p.parts + 1), *adj = tmp.get<int>((size_t)p.parts);
+    if (!two.reserve(13 * (size_t)cells + 8 * ((size_t)p.parts + 1) + 8192)) return BIN_NOMEM;
+    int *cnt = two.take<int>(cells), *off = two.take<int>(cells + 1), *dest = two.take<int>(cells);
+    int *bsum = two.take<int>((size_t)blocks_for(cells, 4 * kWG));
+    int *start = two.take<int>((size_t)p.parts + 1), *adj = two.take<int>((size_t)p.parts);
     p.pend = (int *)alloc(4 * (size_t)p.parts);
     p.shift = (int *)alloc(4 * cells);
-    if (!p.gseg || !cnt || !off || !dest || !bsum || !start || !adj || !p.pend || !p.shift) return BIN_NOMEM;
+    if (!p.gseg || !p.pend || !p.shift) return BIN_NOMEM;
     UV_BIN(hipMemcpyAsync(p.gseg, gs.data(), 4 * gs.size(), hipMemcpyHostToDevice, st));
     k_bin_count<<<p.groups, kWG, 0, st>>>(ptr, idx, p.groups, p.parts, p.gseg, cnt);
     if (!scan_exclusive((int)cells, cnt, off, bsum, st)) return BIN_HIP;
