@@ -366,7 +366,8 @@ typedef struct uv_batch uv_batch;
 
 /* count instances; A[i] in CSR, b[i] (A[i].m doubles), c[i] (A[i].n
  * doubles).  opts as for solver_create (lanes and unroll fields unused; the
- * tiles below set the lanes).  Everything is copied.  UV_ETOOBIG if an
+ * tiles below set the lanes and the threads, at first by an estimate of each
+ * width's time).  Everything is copied.  UV_ETOOBIG if an
  * instance's x and u do not fit in LDS or the totals reach 2^31. */
 int batch_create(int32_t count, const uv_csr *A, const double *const *b,
                  const double *const *c, const uv_opts *opts, uv_batch **out);
@@ -379,8 +380,8 @@ int batch_iterate(uv_batch *h, int64_t k, int32_t *n_active);
  * uv_residuals; the infinity-norm fields, pobj_x and gap_x are not evaluated
  * by the batched solver and read 0).  With opts.full_checks = 0 a check whose
  * r_prim exceeds eps_kkt (it cannot stop the instance) skips its column half
- * and records nothing; the check that stops an instance is always whole.  Returns UV_ENUMERIC (with *r filled) when that instance stopped on a
- * NaN or Inf. */
+ * and records nothing; the check that stops an instance is always whole.
+ * Returns UV_ENUMERIC (with *r filled) when that instance stopped on a NaN or Inf. */
 int batch_residuals(uv_batch *h, int32_t i, uv_residuals *r);
 
 /* Iterate of instance i into caller-owned host buffers (any may be NULL):
@@ -400,7 +401,11 @@ int batch_set_start(uv_batch *h, int32_t i, const double *x, const double *z,
  * columns whose t-th entries are stored side by side, so every entry load
  * is one coalesced access; the sums are those of one lane per column, bit
  * for bit.  Lanes per row 1 selects a sliced copy of the rows likewise, with
- * the sums of two lanes per row.  UV_EINVAL for any other value. */
+ * the sums of two lanes per row.  An instance whose sliced copy would hold more
+ * than 4 nnz + 8192 places (a few rows or columns much longer than the others),
+ * or whose x and u leave no room in LDS for two zeros, takes those one or two
+ * lanes instead.  The copies are made when a tile first asks for them.
+ * UV_EINVAL for any other value. */
 int batch_set_tiles(uv_batch *h, int32_t threads, const int32_t *lanes);
 int batch_get_tiles(const uv_batch *h, int32_t *threads, int32_t *lanes);
 
@@ -419,8 +424,9 @@ void batch_destroy(uv_batch *h);
 /* ------------------------------------------------------------------------
  * Parametric family: one A and c (orthant cone), B right-hand sides
  * b_1..b_B iterated together.  Per-instance vectors live instance-fastest on
- * the device in groups of 128 bytes, so every nonzero of A is read once per
- * group and its gather is one cache line.  Each instance is checked every
+ * the device in groups of 32 (16 for UV_FP64 with at most 128 instances of more
+ * than 16,384 rows), so every nonzero of A is read once per group and its gather
+ * is one or two whole cache lines.  Each instance is checked every
  * check_every iterations and frozen once it stops.
  * Host arrays below are instance-major: instance l's vector starts at
  * l * length.
@@ -598,7 +604,10 @@ int mul_row_vector(int64_t N, int64_t D, float *Y_dev, int64_t ld,
  * device; CENTERED IN PLACE): mean_dev (D), basis_dev (k x D, orthonormal
  * rows, the top-k right singular vectors of the centered Y) and sv (k
  * singular values, host), by a randomized range finder with power_iters
- * power iterations and k + oversample (<= 1024) probe vectors. */
+ * power iterations and k + oversample (<= 1024) probe vectors.  The rows of
+ * the basis are orthonormal also beyond the rank of the centered Y: those
+ * directions are arbitrary and their singular values at rounding's size.  A
+ * NaN or Inf in Y comes back as NaN. */
 int pca_fit(float *Y_dev, int64_t N, int64_t D, int64_t ld, int32_t k,
             int32_t oversample, int32_t power_iters, uint64_t seed,
             float *mean_dev, float *basis_dev, float *sv, void *stream);

@@ -2696,8 +2696,6 @@ struct Carve {
     }
 };
 
-// int64 row offsets (m + 1, validated below 2^31) to the 32-bit device form.
-
 // Device buffers of one no-allocation solve.
 struct NoAlloc {
     DevStatus *st;
@@ -2742,7 +2740,7 @@ constexpr int kSetupThreads = 1024;
 // workgroup 2 the row factors and the narrowed values and vectors.  Fifteen
 // launches and fills of a few microseconds each came before, and a launch of
 // its own for the last residuals after (150x331 with 100 iterations: 378 ->
-// 277 us a call).
+// 267 us a call).
 // Workgroup 0 counts, scans and scatters the entries' rows in LDS; an entry's
 // place in its column is the number of smaller rows there, so the order does
 // not depend on the scatter's.
